@@ -334,7 +334,9 @@ __global__ __launch_bounds__(kBlock) void k_residual_upper_mc(
 // ---------------------------------------------------------------------------
 // Cell levels. Workgroup = one cell: lane group g (GL lanes) sums the
 // off-cell part of row g for every column; the cell matrix is staged in LDS;
-// then thread k < K runs column k's sequential sweep over the cell's unknowns.
+// then wavefronts run the columns' sequential sweeps over the cell's unknowns.
+// blockIdx.y selects a batch of K columns, `batch` elements apart (the tables of
+// dense.hpp are built from many batches at once; a block solve has one).
 // ---------------------------------------------------------------------------
 template <typename T, int D, int K>
 struct CellLds {
@@ -440,9 +442,13 @@ __device__ __forceinline__ void mc_cell_sweep_pair(int k0, int v0, int n, const 
 template <typename T, int D, int K, int GL, int MODE>
 __global__ __launch_bounds__(CellShape<D>::NV * GL) void k_gs_cell_mc(
     int cell0, const int* __restrict__ cell_ptr, Part<T> L, Part<T> U,
-    const T* __restrict__ cellM, const T* __restrict__ b, T* x, T* __restrict__ s_save) {
+    const T* __restrict__ cellM, const T* __restrict__ b, T* x, T* __restrict__ s_save,
+    int64_t batch) {
   constexpr int NU = CellShape<D>::NU;
   __shared__ CellLds<T, D, K> sh;
+  b += blockIdx.y * batch;
+  x += blockIdx.y * batch;
+  if (s_save) s_save += blockIdx.y * batch;
   const int c = cell0 + xcd_block();
   const int v0 = cell_ptr[c], m = cell_ptr[c + 1] - v0, n = m * D;
   const T* Mc = cellM + static_cast<int64_t>(c) * NU * NU;
@@ -459,10 +465,13 @@ __global__ __launch_bounds__(CellShape<D>::NV * GL) void k_gs_cell_mc(
 template <typename T, int D, int K, int GL>
 __global__ __launch_bounds__(CellShape<D>::NV * GL) void k_cell_residual_mc(
     const int* __restrict__ cell_ptr, Part<T> L, Part<T> U, const T* __restrict__ cellM,
-    const T* __restrict__ s_save, const T* __restrict__ x, T* __restrict__ r) {
+    const T* __restrict__ s_save, const T* __restrict__ x, T* __restrict__ r, int64_t batch) {
   constexpr int DP = D;   // coarse-level vectors: packed
   constexpr int NU = CellShape<D>::NU;
   __shared__ CellLds<T, D, K> sh;
+  s_save += blockIdx.y * batch;
+  x += blockIdx.y * batch;
+  r += blockIdx.y * batch;
   __shared__ T shx[NU][K];
   const int c = xcd_block();
   const int v0 = cell_ptr[c], m = cell_ptr[c + 1] - v0, n = m * D;
@@ -493,7 +502,9 @@ __global__ __launch_bounds__(kBlock) void k_restrict_mc(int nc, const int* __res
                                                         const int* __restrict__ idx,
                                                         const T* __restrict__ w,
                                                         const T* __restrict__ r,
-                                                        T* __restrict__ bc) {
+                                                        T* __restrict__ bc, int64_t batch_f) {
+  r += blockIdx.y * batch_f;
+  bc += blockIdx.y * (static_cast<int64_t>(nc) * K * D);
   const int k = threadIdx.x % K;
   const int I = xcd_block() * (kBlock / K) + threadIdx.x / K;
   if (I >= nc) return;
@@ -515,7 +526,10 @@ __global__ __launch_bounds__(kBlock) void k_prolong_mc(int nf, const int* __rest
                                                        const int* __restrict__ idx,
                                                        const T* __restrict__ w,
                                                        const T* __restrict__ e, T* x,
-                                                       const uint8_t* __restrict__ fixed) {
+                                                       const uint8_t* __restrict__ fixed,
+                                                       int64_t batch_c) {
+  e += blockIdx.y * batch_c;
+  x += blockIdx.y * (static_cast<int64_t>(nf) * K * VF);
   const int k = threadIdx.x % K;
   const int i = xcd_block() * (kBlock / K) + threadIdx.x / K;
   if (i >= nf) return;
@@ -578,6 +592,8 @@ __global__ __launch_bounds__(kBlock) void k_coarse_apply_mc(int n, const double*
                                                             T* __restrict__ x) {
   __shared__ double y[kCoarseMax];
   const int nk = n * K;
+  b += blockIdx.y * (static_cast<int64_t>(nk) / D * VS);
+  x += blockIdx.y * (static_cast<int64_t>(nk) / D * VS);
   for (int e = threadIdx.x; e < nk; e += blockDim.x) {
     const int i = e / K, k = e % K;
     y[e] = static_cast<double>(b[((i / D) * K + k) * VS + i % D]);

@@ -30,6 +30,7 @@
 namespace vasmg {
 void set_host_threads(int n);   // setup.cpp: OpenMP threads of the calling thread's setups
 int host_thread_budget();       // setup.cpp: the default OpenMP team size
+int64_t admission_bytes(vasmg_handle h, int64_t budget);   // vasmg.hip
 }
 
 namespace {
@@ -127,7 +128,7 @@ struct vasmg_server {
       int st = vasmg_setup(&m, &o, &h);
       if (st != VASMG_OK) note(r, "setup", vasmg_last_error());
       int64_t bytes = 0;
-      if (st == VASMG_OK) st = vasmg_device_bytes(h, &bytes);
+      if (st == VASMG_OK) bytes = vasmg::admission_bytes(h, budget);
       if (st == VASMG_OK) {
         int32_t nl = 0, dim = 0;
         int64_t nd = 0, nvc = 0, nb = 0, pn = 0;

@@ -28,6 +28,7 @@
 #include "kernels.hpp"
 #include "block.hpp"
 #include "packed.hpp"
+#include "dense.hpp"
 
 using namespace vasmg;
 using dev::Scalars;
@@ -177,6 +178,20 @@ struct vasmg_ctx {
   int64_t bottom_vec = 0, bottom_int = 0;   // its LDS elements: vectors (T), pointers (int)
   dev::BottomLevel<float>* bottom32 = nullptr;
   dev::BottomLevel<double>* bottom64 = nullptr;
+  // dense tables (dense.hpp) of the cycle from level dense_lo down: B of levels
+  // bottom_lo.. (dense[0]) and, when dense_lo < bottom_lo, R (dense[1]) and
+  // [S Q] (dense[2]) of levels dense_lo .. bottom_lo - 1; -1 when the cycle has none
+  struct DenseTable {
+    void* M = nullptr;              // V-cycle precision
+    dev::DenseSeg one;              // the only segment of a single problem
+    dev::DenseSeg* segs = nullptr;  // packed: one per part
+    int nseg = 1, max_rows = 0, max_ld = 0;
+    int64_t elems = 0;
+  };
+  int dense_lo = -1;
+  bool no_dense = false;            // left out (a server's budget)
+  DenseTable dense[3];
+  dev::DenseMap dense_map[2];       // vertices of bottom_lo and dense_lo in part order
   int64_t n_coarse = 0;
   double upload_ms[3] = {0.0, 0.0, 0.0};   // last upload's layouts, autotune, graph capture
   // PCG state (FP64, padded, fine device numbering)
@@ -209,6 +224,7 @@ struct vasmg_ctx {
   int nseg = 0;
   std::vector<int64_t> seg_vertex_off;   // [nseg + 1] mesh-vertex offsets of the parts
   std::vector<int64_t> seg_free_off;     // [nseg + 1] fine canonical vertex offsets
+  std::vector<std::vector<int64_t>> seg_level_off;   // the same on every level
   int *seg_ptr = nullptr, *seg_rows = nullptr, *seg_of_row = nullptr;
   Scalars* ssc = nullptr;                // [nseg]
   int* seg_running = nullptr;            // segments still iterating
@@ -548,6 +564,18 @@ struct TempDev {
       else
         (void)hipFree(q);
     }
+  }
+  template <class T>
+  T* get(size_t n) {
+    void* q = nullptr;
+    const size_t bytes = std::max<size_t>(n, 1) * sizeof(T);
+    const hipError_t e = ordered ? hipMallocAsync(&q, bytes, st) : hipMalloc(&q, bytes);
+    if (e != hipSuccess)
+      throw vasmg::Error{e == hipErrorOutOfMemory ? VASMG_ENOMEM : VASMG_EDEVICE,
+                         "transient device allocation of " + std::to_string(bytes) +
+                             " bytes failed: " + hipGetErrorString(e)};
+    p.push_back(q);
+    return static_cast<T*>(q);
   }
   template <class T>
   T* up(const T* src, size_t n) {
@@ -1222,6 +1250,18 @@ struct BottomOf<double> {
   static const dev::BottomLevel<double>* get(const vasmg_ctx& C) { return C.bottom64; }
 };
 
+// out = table `which` applied to v1 (and v2): levels as in build_dense.
+template <typename T, int D>
+void launch_dense(const vasmg_ctx& C, int which, const T* v1, const T* v2, T* out, hipStream_t st) {
+  const vasmg_ctx::DenseTable& t = C.dense[which];
+  const int* lo = C.dense_map[0].list;
+  const int* hi = C.dense_map[1].list;
+  const dim3 grid(grid_for(t.max_rows, dev::kDenseWaves), t.nseg), blk(64 * dev::kDenseWaves);
+  hipLaunchKernelGGL((dev::k_dense<T, D>), grid, blk, t.max_ld * sizeof(T), st, t.one, t.segs,
+                     static_cast<const T*>(t.M), v1, which == 0 ? lo : hi, v2, lo, out,
+                     which == 2 ? hi : lo);
+}
+
 // One V-cycle: lev[0].b -> lev[0].x (Algorithm 3, recursive, zero initial guess).
 // One visit of level l of the multiplicative cycle (Algorithm 3, recursive):
 // smoothing from zero (zero_guess) or from the current x, residual, restriction,
@@ -1252,6 +1292,20 @@ void enqueue_level(vasmg_ctx& C, int l, bool zero_guess, const int* done, hipStr
   T* s = static_cast<T*>(lv.s);
   T* r = static_cast<T*>(lv.r);
   const LevelBytes by = prof ? level_bytes(C, l, tb) : LevelBytes{};
+  if (l == C.dense_lo) {
+    const int lo = C.bottom_lo;
+    T* bl = static_cast<T*>(C.lev[lo].b);
+    T* xl = static_cast<T*>(C.lev[lo].x);
+    if (l < lo)
+      run_phase(prof, "dense_down", l, 1, C.dense[1].elems * static_cast<double>(tb),
+                [&] { launch_dense<T, D>(C, 1, b, nullptr, bl, st); });
+    run_phase(prof, "bottom", lo, 1, C.dense[0].elems * static_cast<double>(tb),
+              [&] { launch_dense<T, D>(C, 0, bl, nullptr, xl, st); });
+    if (l < lo)
+      run_phase(prof, "dense_up", l, 1, C.dense[2].elems * static_cast<double>(tb),
+                [&] { launch_dense<T, D>(C, 2, b, xl, x, st); });
+    return;
+  }
   const dev::BottomLevel<T>* bottom = BottomOf<T>::get(C);
   if (l == C.bottom_lo && bottom) {
     dev::BottomArgs<T> a;
@@ -1501,6 +1555,7 @@ void autotune(vasmg_ctx& C) {
   const int last = C.opt.preconditioner == VASMG_PRECOND_VASMG ? C.L - 1 : -1;
   for (int l = 0; l <= last; ++l) {
     DevLevel& lv = C.lev[l];
+    if (C.dense_lo > 0 && l >= C.dense_lo) break;   // the solve takes these levels as tables
     const int64_t len = static_cast<int64_t>(lv.n) * C.DP;
     if (C.vc32) {
       launch_fill<float>(static_cast<float*>(lv.b), len, 1.0f, st);
@@ -1912,9 +1967,11 @@ int launch_spmv_mc(const vasmg_ctx& C, const double* x, double* y, double* parti
   return grid;
 }
 
+// GLv: lanes per block row; nbatch batches of K columns (cell levels only).
 template <typename T, int D, int K>
-void launch_gs_sweep_mc(const DevLevel& lv, bool backward, bool zero_guess, const T* b, T* x,
-                        T* s, hipStream_t st) {
+void launch_gs_sweep_mc(const DevLevel& lv, int GLv, int nbatch, bool backward, bool zero_guess,
+                        const T* b, T* x, T* s, hipStream_t st) {
+  const int64_t batch = static_cast<int64_t>(lv.n) * K * D;
   const dev::Part<T> Lp = LevelMats<T>::L(lv), Up = LevelMats<T>::U(lv);
   for (int q = 0; q < lv.ncolors; ++q) {
     const int c = backward ? lv.ncolors - 1 - q : q;
@@ -1923,21 +1980,21 @@ void launch_gs_sweep_mc(const DevLevel& lv, bool backward, bool zero_guess, cons
     if (nr <= 0) continue;
     if (lv.cells) {
       const T* M = LevelMats<T>::cellM(lv);
-      DISPATCH_CELL_GL(lv.mcGL, {
-        const dim3 grid(nr), blk((1 << D) * GL);
+      DISPATCH_CELL_GL(GLv, {
+        const dim3 grid(nr, nbatch), blk((1 << D) * GL);
         if (mode == 0)
           hipLaunchKernelGGL((dev::k_gs_cell_mc<T, D, K, GL, 0>), grid, blk, 0, st, r0, lv.cell_ptr,
-                             Lp, Up, M, b, x, s);
+                             Lp, Up, M, b, x, s, batch);
         else if (mode == 1)
           hipLaunchKernelGGL((dev::k_gs_cell_mc<T, D, K, GL, 1>), grid, blk, 0, st, r0, lv.cell_ptr,
-                             Lp, Up, M, b, x, s);
+                             Lp, Up, M, b, x, s, batch);
         else
           hipLaunchKernelGGL((dev::k_gs_cell_mc<T, D, K, GL, 2>), grid, blk, 0, st, r0, lv.cell_ptr,
-                             Lp, Up, M, b, x, static_cast<T*>(nullptr));
+                             Lp, Up, M, b, x, static_cast<T*>(nullptr), batch);
       });
     } else {
       const T* dg = LevelMats<T>::diag(lv);
-      DISPATCH_POINT_GL(lv.mcGL, {
+      DISPATCH_POINT_GL(GLv, {
         const dim3 grid(grid_for(nr, dev::kBlock / GL)), blk(dev::kBlock);
         if (mode == 0)
           hipLaunchKernelGGL((dev::k_gs_color_mc<T, D, K, GL, 0>), grid, blk, 0, st, r0, nr, Lp,
@@ -1955,15 +2012,17 @@ void launch_gs_sweep_mc(const DevLevel& lv, bool backward, bool zero_guess, cons
 
 // r = b - A x of a level from the forward sweep's saved lower sums s
 template <typename T, int D, int K>
-void launch_residual_mc(const DevLevel& lv, const T* s, const T* x, T* r, hipStream_t st) {
+void launch_residual_mc(const DevLevel& lv, int GLv, int nbatch, const T* s, const T* x, T* r,
+                        hipStream_t st) {
   if (lv.cells) {
-    DISPATCH_CELL_GL(lv.mcGL, {
-      hipLaunchKernelGGL((dev::k_cell_residual_mc<T, D, K, GL>), dim3(lv.ncells), dim3((1 << D) * GL), 0,
-                         st, lv.cell_ptr, LevelMats<T>::L(lv), LevelMats<T>::U(lv),
-                         LevelMats<T>::cellM(lv), s, x, r);
+    DISPATCH_CELL_GL(GLv, {
+      hipLaunchKernelGGL((dev::k_cell_residual_mc<T, D, K, GL>), dim3(lv.ncells, nbatch),
+                         dim3((1 << D) * GL), 0, st, lv.cell_ptr, LevelMats<T>::L(lv),
+                         LevelMats<T>::U(lv), LevelMats<T>::cellM(lv), s, x, r,
+                         static_cast<int64_t>(lv.n) * K * D);
     });
   } else {
-    DISPATCH_POINT_GL(lv.mcGL, {
+    DISPATCH_POINT_GL(GLv, {
       hipLaunchKernelGGL((dev::k_residual_upper_mc<T, D, K, GL>), dim3(grid_for(lv.n, dev::kBlock / GL)),
                          dim3(dev::kBlock), 0, st, lv.n, LevelMats<T>::U(lv), LevelMats<T>::diag(lv), s, x,
                          r);
@@ -1980,17 +2039,18 @@ void enqueue_vcycle_mc(vasmg_ctx& C, hipStream_t st) {
     T* x = static_cast<T*>(C.kx[l]);
     T* s = static_cast<T*>(C.ks[l]);
     T* r = static_cast<T*>(C.kr[l]);
-    for (int k = 0; k < C.opt.n_pre; ++k) launch_gs_sweep_mc<T, D, K>(lv, false, k == 0, b, x, s, st);
-    launch_residual_mc<T, D, K>(lv, s, x, r, st);
+    for (int k = 0; k < C.opt.n_pre; ++k)
+      launch_gs_sweep_mc<T, D, K>(lv, lv.mcGL, 1, false, k == 0, b, x, s, st);
+    launch_residual_mc<T, D, K>(lv, lv.mcGL, 1, s, x, r, st);
     const dim3 rgrid(grid_for(lv.nnext, dev::kBlock / K));
     if (l == 0)
       hipLaunchKernelGGL((dev::k_restrict_mc<T, D, K, dev::Pad<D>::value>), rgrid, dim3(dev::kBlock),
                          0, st, lv.nnext, lv.pt_ptr, lv.pt_idx, LevelMats<T>::ptw(lv), r,
-                         static_cast<T*>(C.kb[l + 1]));
+                         static_cast<T*>(C.kb[l + 1]), int64_t(0));
     else
       hipLaunchKernelGGL((dev::k_restrict_mc<T, D, K, D>), rgrid, dim3(dev::kBlock), 0, st,
                          lv.nnext, lv.pt_ptr, lv.pt_idx, LevelMats<T>::ptw(lv), r,
-                         static_cast<T*>(C.kb[l + 1]));
+                         static_cast<T*>(C.kb[l + 1]), int64_t(0));
   }
   const int nco = static_cast<int>(C.n_coarse);
   const T* bL = static_cast<const T*>(C.kb[L]);
@@ -2015,13 +2075,15 @@ void enqueue_vcycle_mc(vasmg_ctx& C, hipStream_t st) {
     if (l == 0)
       hipLaunchKernelGGL((dev::k_prolong_mc<T, D, K, dev::Pad<D>::value>), pgrid, dim3(dev::kBlock),
                          0, st, lv.n, lv.p_ptr, lv.p_idx, LevelMats<T>::pw(lv),
-                         static_cast<const T*>(C.kx[l + 1]), x, static_cast<const uint8_t*>(lv.fixed));
+                         static_cast<const T*>(C.kx[l + 1]), x, static_cast<const uint8_t*>(lv.fixed),
+                         int64_t(0));
     else
       hipLaunchKernelGGL((dev::k_prolong_mc<T, D, K, D>), pgrid, dim3(dev::kBlock), 0, st, lv.n,
                          lv.p_ptr, lv.p_idx, LevelMats<T>::pw(lv),
-                         static_cast<const T*>(C.kx[l + 1]), x, static_cast<const uint8_t*>(lv.fixed));
+                         static_cast<const T*>(C.kx[l + 1]), x, static_cast<const uint8_t*>(lv.fixed),
+                         int64_t(0));
     for (int k = 0; k < C.opt.n_post; ++k)
-      launch_gs_sweep_mc<T, D, K>(lv, true, false, b, x, nullptr, st);
+      launch_gs_sweep_mc<T, D, K>(lv, lv.mcGL, 1, true, false, b, x, nullptr, st);
   }
 }
 
@@ -2175,6 +2237,274 @@ int solve_block(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d
   return worst;
 }
 
+// -------------------------------------------------------------------------
+// Dense tables of the small levels (dense.hpp)
+// -------------------------------------------------------------------------
+// Largest part (DOFs) a table is built for, and largest tables together. A
+// level of 2,187 DOFs costs 115 us per visit as colour launches and 6 us as
+// tables, which take about 1.3 ms to build: paid back by one solve of a dozen
+// iterations. The next level up in 3D has eight times the DOFs, 64 times the
+// table: its products would cost what its launches do.
+constexpr int64_t kDenseMaxDofs = 2304;
+constexpr int64_t kDenseMaxBytes = int64_t(256) << 20;
+constexpr int64_t kDenseWorkBytes = int64_t(384) << 20;   // transient vectors of one chunk
+
+// Vertex offsets of the parts on level l.
+std::vector<int64_t> part_offsets(const vasmg_ctx& C, int l) {
+  if (C.nseg > 0) return C.seg_level_off[l];
+  return {0, C.H.levels[l].n};
+}
+
+// Elements of the tables that start at level ld over a bottom of vertex
+// offsets `lo` (padding included); -1 if a part is too large.
+int64_t dense_elems(const vasmg_ctx& C, const std::vector<int64_t>& hi, const std::vector<int64_t>& lo,
+                    bool split) {
+  const int64_t Q = C.vc32 ? 4 : 2;
+  auto pad = [&](int64_t n) { return (n + Q - 1) / Q * Q; };
+  int64_t e = 0;
+  for (size_t p = 0; p + 1 < hi.size(); ++p) {
+    const int64_t n = (hi[p + 1] - hi[p]) * C.d, m = (lo[p + 1] - lo[p]) * C.d;
+    if (n > kDenseMaxDofs || m > kDenseMaxDofs) return -1;
+    e += m * pad(m) + (split ? m * pad(n) + n * (pad(n) + pad(m)) : 0);
+  }
+  return e;
+}
+
+// Upper bound of the tables' bytes before the levels are on the device (any
+// bottom level at or below the tables' first level), and of the construction's
+// transient vectors; 0 when the cycle takes none.
+int64_t dense_bytes_bound(const vasmg_ctx& C, int64_t* work) {
+  *work = 0;
+  const int L = static_cast<int>(C.H.levels.size()) - 1;
+  if (C.no_dense || C.opt.preconditioner != VASMG_PRECOND_VASMG || C.opt.cycle == VASMG_CYCLE_W ||
+      C.opt.smoother != VASMG_SMOOTHER_GS || C.opt.n_pre < 1 || L < 2)
+    return 0;
+  for (int l = 1; l < L; ++l) {
+    const int64_t e = dense_elems(C, part_offsets(C, l), part_offsets(C, std::min(l + 1, L - 1)), true);
+    if (e < 0) continue;
+    int64_t per_batch = 0, part = 0;   // vectors of one column batch, the largest part
+    for (int q = l; q <= L; ++q)
+      per_batch += C.H.levels[q].n * dev::kDenseCols * C.d * (C.vc32 ? 4 : 8) * 4;
+    const std::vector<int64_t> off = part_offsets(C, l);
+    for (size_t p = 0; p + 1 < off.size(); ++p) part = std::max(part, off[p + 1] - off[p]);
+    *work = std::min(std::max(kDenseWorkBytes, per_batch),
+                     (2 * part * C.d / dev::kDenseCols + 1) * per_batch);
+    const int64_t rows = C.H.levels[l].n * 12;   // part order, packed only
+    return std::min(e * (C.vc32 ? 4 : 8), kDenseMaxBytes) + (C.nseg > 0 ? 2 * rows + 1024 * C.nseg : 0);
+  }
+  return 0;
+}
+
+// The cycle on column batches: b of level l0 -> down to level l1's b (levels
+// l0 .. l1 - 1), then from level l1's x up to level l0's x. Vectors per level
+// in w (b, x, s, r).
+struct DenseWork {
+  void* v[4] = {nullptr, nullptr, nullptr, nullptr};
+};
+
+template <typename T, int D>
+void dense_down(vasmg_ctx& C, std::vector<DenseWork>& w, int l0, int l1, int nb, hipStream_t st) {
+  constexpr int K = dev::kDenseCols;
+  for (int l = l0; l < l1; ++l) {
+    const DevLevel& lv = C.lev[l];
+    T *b = static_cast<T*>(w[l].v[0]), *x = static_cast<T*>(w[l].v[1]);
+    T *s = static_cast<T*>(w[l].v[2]), *r = static_cast<T*>(w[l].v[3]);
+    for (int k = 0; k < C.opt.n_pre; ++k)
+      launch_gs_sweep_mc<T, D, K>(lv, dev::kCellLanesNarrow, nb, false, k == 0, b, x, s, st);
+    launch_residual_mc<T, D, K>(lv, dev::kCellLanesNarrow, nb, s, x, r, st);
+    hipLaunchKernelGGL((dev::k_restrict_mc<T, D, K, D>), dim3(grid_for(lv.nnext, dev::kBlock / K), nb),
+                       dim3(dev::kBlock), 0, st, lv.nnext, lv.pt_ptr, lv.pt_idx, LevelMats<T>::ptw(lv), r,
+                       static_cast<T*>(w[l + 1].v[0]), static_cast<int64_t>(lv.n) * K * D);
+  }
+}
+
+template <typename T, int D>
+void dense_up(vasmg_ctx& C, std::vector<DenseWork>& w, int l0, int l1, int nb, hipStream_t st) {
+  constexpr int K = dev::kDenseCols;
+  for (int l = l1 - 1; l >= l0; --l) {
+    const DevLevel& lv = C.lev[l];
+    T *b = static_cast<T*>(w[l].v[0]), *x = static_cast<T*>(w[l].v[1]);
+    hipLaunchKernelGGL((dev::k_prolong_mc<T, D, K, D>), dim3(grid_for(lv.n, dev::kBlock / K), nb),
+                       dim3(dev::kBlock), 0, st, lv.n, lv.p_ptr, lv.p_idx, LevelMats<T>::pw(lv),
+                       static_cast<const T*>(w[l + 1].v[1]), x, static_cast<const uint8_t*>(lv.fixed),
+                       static_cast<int64_t>(lv.nnext) * K * D);
+    for (int k = 0; k < C.opt.n_post; ++k)
+      launch_gs_sweep_mc<T, D, K>(lv, dev::kCellLanesNarrow, nb, true, false, b, x,
+                                  static_cast<T*>(nullptr), st);
+  }
+}
+
+template <typename T, int D>
+void build_dense(vasmg_ctx& C, hipStream_t st) {
+  constexpr int K = dev::kDenseCols;
+  using Shape = dev::DenseShape<T>;
+  const int lo = C.bottom_lo, L = C.L;
+  const std::vector<int64_t> off_lo = part_offsets(C, lo);
+  auto fits = [&](int64_t e) {
+    return e >= 0 && e * static_cast<int64_t>(sizeof(T)) <= kDenseMaxBytes;
+  };
+  if (!fits(dense_elems(C, off_lo, off_lo, false))) return;
+  int ld = lo;
+  while (ld - 1 >= 1 && C.lev[ld - 1].cells && !C.lev[ld - 1].blocks &&
+         fits(dense_elems(C, part_offsets(C, ld - 1), off_lo, true)))
+    --ld;
+  const std::vector<int64_t> off_hi = part_offsets(C, ld);
+  const int np = static_cast<int>(off_lo.size()) - 1;
+  // part order of the two levels' vertices (canonical order is part by part)
+  if (C.nseg > 0) {
+    for (int q = 0; q < 2; ++q) {
+      const int l = q == 0 ? lo : ld;
+      const std::vector<int64_t>& off = q == 0 ? off_lo : off_hi;
+      const int n = C.lev[l].n;
+      std::vector<int> perm(n), list(n), loc(n), seg(n);
+      C.copy(perm.data(), C.lev[l].perm, sizeof(int) * n, hipMemcpyDeviceToHost);
+      for (int i = 0; i < n; ++i) {
+        const int p = static_cast<int>(std::upper_bound(off.begin(), off.end(), perm[i]) - off.begin()) - 1;
+        list[perm[i]] = i;
+        loc[i] = static_cast<int>(perm[i] - off[p]);
+        seg[i] = p;
+      }
+      C.dense_map[q].list = C.upload(list);
+      C.dense_map[q].loc = C.upload(loc);
+      C.dense_map[q].seg = C.upload(seg);
+    }
+  }
+  auto table = [&](int which, const std::vector<int64_t>& ro, const std::vector<int64_t>& ao,
+                   const std::vector<int64_t>* co) {
+    vasmg_ctx::DenseTable& t = C.dense[which];
+    std::vector<dev::DenseSeg> segs(np);
+    int64_t m = 0;
+    for (int p = 0; p < np; ++p) {
+      dev::DenseSeg& g = segs[p];
+      g.m0 = m;
+      g.r0 = static_cast<int>(ro[p]);
+      g.nr = static_cast<int>(ro[p + 1] - ro[p]);
+      g.a0 = static_cast<int>(ao[p]);
+      g.na = static_cast<int>(ao[p + 1] - ao[p]);
+      g.c0 = co ? static_cast<int>((*co)[p]) : 0;
+      g.nc = co ? static_cast<int>((*co)[p + 1] - (*co)[p]) : 0;
+      g.ld = Shape::pad(g.na * D) + Shape::pad(g.nc * D);
+      m += static_cast<int64_t>(g.nr) * D * g.ld;
+      t.max_rows = std::max(t.max_rows, g.nr * D);
+      t.max_ld = std::max(t.max_ld, g.ld);
+    }
+    t.one = segs[0];
+    t.nseg = np;
+    t.elems = m;
+    if (C.nseg > 0) t.segs = C.upload(segs);
+  };
+  table(0, off_lo, off_lo, nullptr);
+  if (ld < lo) {
+    table(1, off_lo, off_hi, nullptr);
+    table(2, off_hi, off_hi, &off_lo);
+  }
+  {
+    const int64_t m = C.dense[0].elems + C.dense[1].elems + C.dense[2].elems;
+    T* M = C.dalloc<T>(m);
+    launch_fill<T>(M, m, T(0), st);   // the row padding
+    for (auto& t : C.dense) {
+      t.M = M;
+      M += t.elems;
+    }
+  }
+  auto max_part = [&](const std::vector<int64_t>& off) {
+    int64_t m = 0;
+    for (int p = 0; p < np; ++p) m = std::max(m, off[p + 1] - off[p]);
+    return static_cast<int>(m) * D;
+  };
+  const int n_lo = max_part(off_lo), n_hi = max_part(off_hi);
+  // column batches per chunk, within the transient vectors' bound
+  int64_t per_batch = 0;
+  for (int l = ld; l <= L; ++l)
+    per_batch += static_cast<int64_t>(C.lev[l].n) * K * D * sizeof(T) * (l == L ? 2 : 4);
+  const int cols = std::max(n_lo, ld < lo ? n_hi + n_lo : 0);
+  const int nbmax = static_cast<int>(
+      std::min<int64_t>((cols + K - 1) / K, std::max<int64_t>(1, kDenseWorkBytes / per_batch)));
+  TempDev tmp(st, C.alloc_stream != nullptr);
+  std::vector<DenseWork> w(L + 1);
+  T* slab = tmp.get<T>(per_batch / sizeof(T) * nbmax);   // one: freeing each on its own takes longer
+  for (int l = ld; l <= L; ++l) {
+    const int64_t len = static_cast<int64_t>(C.lev[l].n) * K * D * nbmax;
+    for (int q = 0; q < (l == L ? 2 : 4); ++q) {
+      w[l].v[q] = slab;
+      slab += len;
+    }
+    // the zero padding blocks of a row multiply the row's own entry of x before
+    // the first sweep has written it
+    launch_fill<T>(static_cast<T*>(w[l].v[1]), len, T(0), st);
+  }
+  auto unit = [&](int l, int q, int v, int nb, int col0, int shift) {
+    const int64_t e = static_cast<int64_t>(C.lev[l].n) * K * D;
+    hipLaunchKernelGGL((dev::k_dense_unit<T, D>), dim3(grid_for(e, dev::kBlock), nb), dim3(dev::kBlock), 0,
+                       st, C.lev[l].n, C.dense_map[q].loc, col0, shift, static_cast<T*>(w[l].v[v]));
+  };
+  auto extract = [&](int which, int l, int q, int v, int nb, int col0, int shift, int second) {
+    const int64_t e = static_cast<int64_t>(C.lev[l].n) * K * D;
+    hipLaunchKernelGGL((dev::k_dense_extract<T, D>), dim3(grid_for(e, dev::kBlock), nb), dim3(dev::kBlock),
+                       0, st, C.lev[l].n, C.dense_map[q], C.dense[which].one, C.dense[which].segs, col0,
+                       shift, second, static_cast<const T*>(w[l].v[v]), static_cast<T*>(C.dense[which].M));
+  };
+  const int nco = static_cast<int>(C.n_coarse);
+  for (int c0 = 0; c0 < n_lo; c0 += nbmax * K) {   // B: the cycle from level lo on unit vectors
+    const int nb = std::min(nbmax, (n_lo - c0 + K - 1) / K);
+    unit(lo, 0, 0, nb, c0, 0);
+    dense_down<T, D>(C, w, lo, L, nb, st);
+    hipLaunchKernelGGL((dev::k_coarse_apply_mc<T, D, K, D>), dim3(1, nb), dim3(dev::kBlock), 0, st, nco,
+                       C.cinv, static_cast<const T*>(w[L].v[0]), static_cast<T*>(w[L].v[1]));
+    dense_up<T, D>(C, w, lo, L, nb, st);
+    extract(0, lo, 0, 1, nb, c0, 0, 0);
+  }
+  if (ld < lo) {
+    // R and S: unit vectors in b_ld with x_lo = 0; Q: unit vectors in x_lo with b_ld = 0
+    for (int c0 = 0; c0 < n_hi + n_lo; c0 += nbmax * K) {
+      const int nb = std::min(nbmax, (n_hi + n_lo - c0 + K - 1) / K);
+      unit(ld, 1, 0, nb, c0, 0);
+      dense_down<T, D>(C, w, ld, lo, nb, st);
+      extract(1, lo, 0, 0, nb, c0, 0, 0);
+      unit(lo, 0, 1, nb, c0, n_hi);
+      dense_up<T, D>(C, w, ld, lo, nb, st);
+      extract(2, ld, 1, 1, nb, c0, 0, 0);
+      extract(2, ld, 1, 1, nb, c0, n_hi, 1);
+    }
+  }
+  HIP_CHECK(hipGetLastError());
+  HIP_CHECK(hipStreamSynchronize(st));
+  C.dense_lo = ld;
+}
+
+// Tables where the cycle has a fused bottom to extend (Gauss-Seidel V-cycle or
+// the additive form, whose coarse part is one; the W-cycle revisits its levels
+// from a nonzero iterate and keeps k_bottom). Without memory for them the
+// handle goes on without.
+void make_dense(vasmg_ctx& C) {
+  if (C.bottom_lo < 0 || C.no_dense || C.opt.cycle == VASMG_CYCLE_W) return;
+  hipStream_t st = C.alloc_stream;
+  if (!st && C.gdev) {   // the level layouts are still being written on the setup's stream
+    st = static_cast<hipStream_t>(galerkin_device_stream(C.gdev));
+    HIP_CHECK(hipStreamSynchronize(nullptr));
+  }
+  const size_t kept = C.allocs.size();
+  const int64_t bytes = C.dev_bytes;
+  try {
+    if (C.d == 2)
+      C.vc32 ? build_dense<float, 2>(C, st) : build_dense<double, 2>(C, st);
+    else
+      C.vc32 ? build_dense<float, 3>(C, st) : build_dense<double, 3>(C, st);
+  } catch (const vasmg::Error& e) {
+    if (e.status != VASMG_ENOMEM) throw;
+    (void)hipGetLastError();
+    for (; C.allocs.size() > kept; C.allocs.pop_back()) {
+      if (C.alloc_stream)
+        (void)hipFreeAsync(C.allocs.back(), C.alloc_stream);
+      else
+        (void)hipFree(C.allocs.back());
+    }
+    C.dev_bytes = bytes;
+    for (auto& t : C.dense) t = {};
+    for (auto& m : C.dense_map) m = {};
+  }
+}
+
 bool device_available();
 
 // Device upload of a host-built hierarchy (+ block vectors, autotuning).
@@ -2196,9 +2526,9 @@ double time_level_mc(vasmg_ctx& C, int l, hipStream_t st) {
   std::vector<float> t;
   for (int rep = 0; rep < 4; ++rep) {
     HIP_CHECK(hipEventRecord(e0, st));
-    launch_gs_sweep_mc<T, D, K>(lv, false, true, b, x, s, st);
-    launch_residual_mc<T, D, K>(lv, s, x, r, st);
-    launch_gs_sweep_mc<T, D, K>(lv, true, false, b, x, s, st);
+    launch_gs_sweep_mc<T, D, K>(lv, lv.mcGL, 1, false, true, b, x, s, st);
+    launch_residual_mc<T, D, K>(lv, lv.mcGL, 1, s, x, r, st);
+    launch_gs_sweep_mc<T, D, K>(lv, lv.mcGL, 1, true, false, b, x, s, st);
     if (l == 0) launch_spmv_mc<D, K>(C, C.kP, C.kQ, nullptr, st);
     HIP_CHECK(hipEventRecord(e1, st));
     HIP_CHECK(hipEventSynchronize(e1));
@@ -2250,6 +2580,7 @@ void upload_device(vasmg_ctx& C, hipStream_t alloc_stream) {
   auto t = Clock::now();
   upload_all(C);
   if (C.opt.block_rhs != 0) upload_block(C, C.opt.block_rhs);
+  make_dense(C);
   C.upload_ms[0] = ms_since(t);
   t = Clock::now();
   if (C.opt.autotune) {
@@ -2321,6 +2652,9 @@ int64_t estimate_device_bytes(const vasmg_ctx& C) {
     const Level& lv = H.levels[l];
     transient = std::max(transient, lv.A.nnzb() * (4 + dd * 8) + (lv.n + 1) * 8 + 6 * lv.n * 4);
   }
+  int64_t dense_work = 0;
+  b += dense_bytes_bound(C, &dense_work);
+  transient = std::max(transient, dense_work);
   b += transient;
   const int64_t n0p = H.levels[0].n * DP;
   b += 6 * n0p * 8 + H.levels[0].n * 4 + H.n_coarse_dofs * H.n_coarse_dofs * 16;   // factor + inverse
@@ -2341,6 +2675,20 @@ bool device_available() {
 }
 
 }  // namespace
+
+namespace vasmg {
+// Device bytes a server admits a host-built handle by. The dense tables are
+// left out (here and at the upload) when they would take the request over the
+// whole budget, so that what fits without them is still served.
+int64_t admission_bytes(vasmg_handle h, int64_t budget) {
+  int64_t b = estimate_device_bytes(*h);
+  if (b > budget && !h->no_dense) {
+    h->no_dense = true;
+    b = estimate_device_bytes(*h);
+  }
+  return b;
+}
+}  // namespace vasmg
 
 // ---------------------------------------------------------------------------
 // Staging of the no-allocation host-pointer solve (vasmg_solve_noalloc): one
@@ -2705,6 +3053,14 @@ vasmg_status vasmg_pack(const vasmg_handle* parts, int32_t n_parts, vasmg_handle
     for (int i = 0; i < n_parts; ++i) {
       C->seg_vertex_off.push_back(C->seg_vertex_off.back() + parts[i]->H.n_mesh_vertices);
       C->seg_free_off.push_back(C->seg_free_off.back() + parts[i]->H.levels[0].n);
+      C->no_dense = C->no_dense || parts[i]->no_dense;
+    }
+    C->seg_level_off.resize(C->L + 1);
+    for (int l = 0; l <= C->L; ++l) {   // a part shallower than l repeats its coarsest level
+      std::vector<int64_t>& off = C->seg_level_off[l];
+      off.assign(1, 0);
+      for (const Hierarchy* p : hs)
+        off.push_back(off.back() + p->levels[std::min<size_t>(l, p->levels.size() - 1)].n);
     }
     C->H.phase_ms.emplace_back(
         "pack", std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count());

@@ -1,0 +1,108 @@
+"""The small levels of the cycle as dense tables: the preconditioner application
+against the oracle where the tables start at the fused bottom's level, above it,
+at their largest part, in the additive form, with unequal sweep counts, on
+constrained components, and in a pack whose parts differ in depth; and the same
+answers without them, where a server's budget has no room for the tables."""
+import numpy as np
+import pytest
+
+from oracle import Oracle, OracleOptions
+from workloads import small2d, small3d
+
+torch = pytest.importorskip("torch")
+from paper_2505_09064_amd import vasmg as V  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+MAX_DOFS = 2304
+
+
+def _first_table_level(s):
+    """(first level the tables cover, first level of the fused bottom)."""
+    ph = s.profile_iteration(1)
+    lo = [p["level"] for p in ph if p["name"] == "bottom"]
+    up = [p["level"] for p in ph if p["name"] == "dense_up"]
+    down = [p["level"] for p in ph if p["name"] == "dense_down"]
+    assert len(lo) == 1 and up == down and len(up) <= 1
+    return (up or lo)[0], lo[0]
+
+
+# name: mesh, options, oracle options
+CASES = {
+    "bottom only, 2D": (lambda: small2d(9, seed=1), {}, {}),
+    "above the bottom, 2D rollers": (lambda: small2d(34, seed=2, fix="symmetry"), {}, {}),
+    "above the bottom, 3D": (lambda: small3d(9, seed=3), {}, {}),
+    "rollers, 3D": (lambda: small3d(8, seed=4, fix="symmetry"), {}, {}),
+    "near the largest, 3D": (lambda: small3d(13, seed=5), {}, {}),
+    "past the largest on level 1, 3D": (lambda: small3d(17, seed=6), {}, {}),
+    "additive": (lambda: small3d(9, seed=7), dict(cycle=V.CYCLE_ADDITIVE), dict(cycle="additive")),
+    "sweeps (2, 1)": (lambda: small3d(9, seed=8), dict(n_pre=2, n_post=1), dict(n_pre=2, n_post=1)),
+    "sweeps (1, 0)": (lambda: small2d(21, seed=9), dict(n_pre=1, n_post=0), dict(n_pre=1, n_post=0)),
+}
+
+
+@pytest.mark.parametrize("prec", [V.FP64, V.FP32_PRECOND])
+@pytest.mark.parametrize("name", list(CASES))
+def test_dense_tables_match_oracle(name, prec):
+    """FP64: 1e-11 of the norm, the cycle's own bar. FP32: the operators' float32
+    rounding enters as often as in the oracle's FP32 mode, so the distance to the
+    FP64 cycle is at most 4 times that mode's (and 16 float32 units)."""
+    make, kw, okw = CASES[name]
+    m = make()
+    o = Oracle(m.coords, m.elems, m.E, m.nu, m.fixed, OracleOptions(**okw))
+    s = V.Solver.from_mesh(m, precision=prec, **kw)
+    first, lo = _first_table_level(s)
+    sizes = [s.level_info(l)["n_vertices"] * m.dim for l in range(s.hierarchy_info()[0])]
+    assert sizes[first] <= MAX_DOFS and (first == 1 or sizes[first - 1] > MAX_DOFS), (sizes, first, lo)
+    n = o.A[0].shape[0] // m.dim
+    r = np.random.default_rng(6).normal(size=(n, m.dim))
+    z = torch.zeros((n, m.dim), dtype=torch.float64, device="cuda")
+    s.apply_precond_device(torch.from_numpy(r).cuda(), z)
+    again = torch.zeros_like(z)
+    s.apply_precond_device(torch.from_numpy(r).cuda(), again)
+    assert torch.equal(z, again)
+    ref = o.apply_precond(r.ravel(), precision="fp64")
+    err = np.linalg.norm(z.cpu().numpy().ravel() - ref) / np.linalg.norm(ref)
+    if prec == V.FP64:
+        assert err < 1e-11
+    else:
+        ref32 = o.apply_precond(r.ravel(), precision="fp32")
+        gap = np.linalg.norm(ref32 - ref) / np.linalg.norm(ref)
+        assert err <= max(4 * gap, 16 * 2.0 ** -24), (err, gap)
+    s.free()
+
+
+@pytest.mark.parametrize("prec", [V.FP64, V.FP32_PRECOND])
+def test_dense_tables_of_a_pack(prec):
+    """Parts of different depth and size, one of them a single small part: every
+    part against its own solve alone (the bars of the packed solves)."""
+    for ms in ([small3d(5, seed=1), small3d(11, seed=2, fix="symmetry"), small3d(7, seed=3)],
+               [small2d(30, seed=4), small2d(8, seed=5), small2d(17, seed=6, fix="symmetry")],
+               [small3d(6, seed=7)]):
+        parts = [V.Solver.from_mesh(m, precision=prec, host_only=1) for m in ms]
+        pk = V.PackedSolver(parts)
+        assert any(p["name"] == "bottom" for p in pk.profile_iteration(1))
+        xs, infos = pk.solve_packed([m.rhs[0] for m in ms], 1e-8)
+        for m, x, i in zip(ms, xs, infos):
+            with V.Solver.from_mesh(m, precision=prec) as s:
+                xa, ia = s.solve(m.rhs[0], 1e-8)
+            assert i["status"] == V.OK and abs(i["iterations"] - ia["iterations"]) <= 1
+            assert np.linalg.norm(x - xa) / np.linalg.norm(xa) <= (1e-10 if prec == V.FP64 else 1e-5)
+        pk.free()
+
+
+def test_budget_without_room_for_tables():
+    """A server's budget that holds the hierarchy but not its tables still serves
+    the request (as it did when there were none), to the oracle's bars."""
+    m = small3d(11, seed=9)
+    s = V.Solver.from_mesh(m, host_only=1)
+    b = V.C.c_int64()
+    V._check(V.lib().vasmg_device_bytes(s._h, V.C.byref(b)))
+    s.free()
+    srv = V.Server(slots=1, setup_workers=1, hbm_budget_bytes=b.value - (1 << 20))
+    x, res = srv.wait(srv.submit(m, m.rhs[0], 1e-8))
+    srv.close()
+    assert res["status"] == V.OK and res["device_bytes"] < b.value - (1 << 20), res
+    xo, io = Oracle(m.coords, m.elems, m.E, m.nu, m.fixed).solve(m.rhs[0], 1e-8)
+    assert abs(res["info"]["iterations"] - io["iterations"]) <= 1
+    assert np.linalg.norm(x - xo) / np.linalg.norm(xo) <= 1e-8
