@@ -18,7 +18,7 @@
 // vectors gives column j of every part at once.
 #pragma once
 
-#include "kernels.hpp"
+#include "block.hpp"
 
 namespace vasmg {
 namespace dev {
@@ -119,6 +119,96 @@ __global__ __launch_bounds__(64 * kDenseWaves) void k_dense(
     const int i = s.r0 + row / D;
     out[static_cast<int64_t>(list_out ? list_out[i] : i) * DP + row % D] = sum;
   }
+}
+
+// ---- several columns -------------------------------------------------------
+// The same product for the K columns of a block solve, vectors [vertex][K][D].
+// A contraction of 16 rows x cols x K columns: matrix instructions, 16 x 16
+// output values per workgroup, its wavefronts taking turns over groups of four
+// vertices (their D components are the D steps of the group: a lane loads a
+// vertex's components of its matrix row and of its column in one go, both
+// contiguous over the wavefront); their partial results meet in LDS and are
+// added in wavefront order. The table streams once for all columns.
+constexpr int kDenseMcWaves = 8;
+
+typedef float dfloat4 __attribute__((ext_vector_type(4)));
+typedef double ddouble4 __attribute__((ext_vector_type(4)));
+
+template <typename T>
+struct Mfma16;
+template <>
+struct Mfma16<float> {
+  using Acc = dfloat4;
+  static __device__ __forceinline__ Acc step(float a, float b, Acc c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int lane, int q) { return 4 * (lane >> 4) + q; }
+};
+template <>
+struct Mfma16<double> {
+  using Acc = ddouble4;
+  static __device__ __forceinline__ Acc step(double a, double b, Acc c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int lane, int q) { return (lane >> 4) + 4 * q; }
+};
+
+// acc += M[row][cols of one input] v: nv vertices, the first at index v0 of v,
+// matrix row m (this lane's). Groups of four vertices wave, wave + waves, ...
+template <typename T, int D, int K>
+__device__ __forceinline__ void dense_mc_input(const T* __restrict__ m, const T* __restrict__ v, int v0,
+                                               int nv, int wave, int lane,
+                                               typename Mfma16<T>::Acc& acc) {
+  constexpr int UN = sizeof(T) == 4 ? 4 : 2;
+  const int n = lane & 15, g = lane >> 4;
+  const int groups = (nv + 3) / 4;
+  for (int q0 = wave; q0 < groups; q0 += UN * kDenseMcWaves) {
+    T a[UN][D], b[UN][D];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int i = 4 * (q0 + u * kDenseMcWaves) + g;
+      const bool in = i < nv;
+      const int ic = in ? i : nv - 1;
+      BlockVecIO<T, D, D>::load(m + ic * D, a[u]);
+      BlockVecIO<T, D, D>::load(v + (static_cast<int64_t>(v0 + ic) * K + n % K) * D, b[u]);
+#pragma unroll
+      for (int c = 0; c < D; ++c) {
+        if (!in) a[u][c] = T(0);
+        if (!in || n >= K) b[u][c] = T(0);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+#pragma unroll
+      for (int c = 0; c < D; ++c) acc = Mfma16<T>::step(a[u][c], b[u][c], acc);
+    }
+  }
+}
+
+// out = M [v1; v2] for K columns of a single problem (segment s).
+template <typename T, int D, int K>
+__global__ __launch_bounds__(64 * kDenseMcWaves) void k_dense_mc(DenseSeg s, const T* __restrict__ M,
+                                                                 const T* __restrict__ v1,
+                                                                 const T* __restrict__ v2,
+                                                                 T* __restrict__ out) {
+  static_assert(K <= 16, "one column per matrix column");
+  __shared__ T part[kDenseMcWaves][16][16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int rows = s.nr * D, row0 = blockIdx.x * 16;
+  const T* m = M + s.m0 + static_cast<int64_t>(min(row0 + (lane & 15), rows - 1)) * s.ld;
+  typename Mfma16<T>::Acc acc = {T(0), T(0), T(0), T(0)};
+  dense_mc_input<T, D, K>(m, v1, s.a0, s.na, wave, lane, acc);
+  if (s.nc > 0)
+    dense_mc_input<T, D, K>(m + DenseShape<T>::pad(s.na * D), v2, s.c0, s.nc, wave, lane, acc);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) part[wave][Mfma16<T>::row(lane, q)][lane & 15] = acc[q];
+  __syncthreads();
+  const int r = threadIdx.x >> 4, n = threadIdx.x & 15, row = row0 + r;
+  if (r >= 16 || n >= K || row >= rows) return;
+  T sum = part[0][r][n];
+#pragma unroll
+  for (int w = 1; w < kDenseMcWaves; ++w) sum += part[w][r][n];
+  out[(static_cast<int64_t>(s.r0 + row / D) * K + n) * D + row % D] = sum;
 }
 
 // ---- construction ---------------------------------------------------------

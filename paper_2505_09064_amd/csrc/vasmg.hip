@@ -2030,10 +2030,20 @@ void launch_residual_mc(const DevLevel& lv, int GLv, int nbatch, const T* s, con
   }
 }
 
+// out = table `which` applied to the K columns of v1 (and v2).
+template <typename T, int D, int K>
+void launch_dense_mc(const vasmg_ctx& C, int which, const void* v1, const void* v2, void* out,
+                     hipStream_t st) {
+  const vasmg_ctx::DenseTable& t = C.dense[which];
+  hipLaunchKernelGGL((dev::k_dense_mc<T, D, K>), dim3(grid_for(t.max_rows, 16)),
+                     dim3(64 * dev::kDenseMcWaves), 0, st, t.one, static_cast<const T*>(t.M),
+                     static_cast<const T*>(v1), static_cast<const T*>(v2), static_cast<T*>(out));
+}
+
 template <typename T, int D, int K>
 void enqueue_vcycle_mc(vasmg_ctx& C, hipStream_t st) {
-  const int L = C.L;
-  for (int l = 0; l < L; ++l) {
+  const int L = C.L, top = C.dense_lo > 0 ? C.dense_lo : C.L;   // levels smoothed one by one
+  for (int l = 0; l < top; ++l) {
     const DevLevel& lv = C.lev[l];
     T* b = static_cast<T*>(C.kb[l]);
     T* x = static_cast<T*>(C.kx[l]);
@@ -2052,10 +2062,14 @@ void enqueue_vcycle_mc(vasmg_ctx& C, hipStream_t st) {
                          lv.nnext, lv.pt_ptr, lv.pt_idx, LevelMats<T>::ptw(lv), r,
                          static_cast<T*>(C.kb[l + 1]), int64_t(0));
   }
-  const int nco = static_cast<int>(C.n_coarse);
+  const int nco = static_cast<int>(C.n_coarse), lo = C.bottom_lo;
   const T* bL = static_cast<const T*>(C.kb[L]);
   T* xL = static_cast<T*>(C.kx[L]);
-  if (L == 0 && C.cinv)
+  if (top < L) {
+    if (top < lo) launch_dense_mc<T, D, K>(C, 1, C.kb[top], nullptr, C.kb[lo], st);
+    launch_dense_mc<T, D, K>(C, 0, C.kb[lo], nullptr, C.kx[lo], st);
+    if (top < lo) launch_dense_mc<T, D, K>(C, 2, C.kb[top], C.kx[lo], C.kx[top], st);
+  } else if (L == 0 && C.cinv)
     hipLaunchKernelGGL((dev::k_coarse_apply_mc<T, D, K, dev::Pad<D>::value>), dim3(1),
                        dim3(dev::kBlock), 0, st, nco, C.cinv, bL, xL);
   else if (L == 0)
@@ -2067,7 +2081,7 @@ void enqueue_vcycle_mc(vasmg_ctx& C, hipStream_t st) {
   else
     hipLaunchKernelGGL((dev::k_coarse_solve_mc<T, D, K, D>), dim3(1), dim3(dev::kBlock), 0, st, nco,
                        C.chol, bL, xL);
-  for (int l = L - 1; l >= 0; --l) {
+  for (int l = top - 1; l >= 0; --l) {
     const DevLevel& lv = C.lev[l];
     T* b = static_cast<T*>(C.kb[l]);
     T* x = static_cast<T*>(C.kx[l]);
@@ -2545,7 +2559,7 @@ double time_level_mc(vasmg_ctx& C, int l, hipStream_t st) {
 template <int D, int K>
 void autotune_block(vasmg_ctx& C) {
   hipStream_t st = C.cap_stream;
-  for (int l = 0; l < C.L; ++l) {
+  for (int l = 0; l < (C.dense_lo > 0 ? C.dense_lo : C.L); ++l) {
     DevLevel& lv = C.lev[l];
     const bool fine64 = l == 0 && !C.vc32;
     int best_gl = lv.mcGL;

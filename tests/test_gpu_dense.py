@@ -91,6 +91,26 @@ def test_dense_tables_of_a_pack(prec):
         pk.free()
 
 
+@pytest.mark.parametrize("K", [4, 8, 16])
+@pytest.mark.parametrize("prec", [V.FP64, V.FP32_PRECOND])
+def test_dense_tables_of_a_block_solve(prec, K):
+    """The products for K columns, with and without tables above the bottom, row
+    and vertex counts off the matrix tile: every column of a block solve against
+    its single-column solve (the tables are the same, the sums in another order)."""
+    for m in (small3d(9, seed=3), small3d(11, seed=5, fix="symmetry"), small2d(9, seed=1),
+              small2d(35, seed=2), small3d(17, seed=6)):
+        nf = m.n_vertices
+        F = np.random.default_rng(K).normal(size=(K + 1, nf, m.dim)) * np.abs(m.rhs[0]).max()
+        s = V.Solver.from_mesh(m, precision=prec, block_rhs=K)
+        _first_table_level(s)
+        x, infos = s.solve(F, 1e-8)
+        for k in (0, K - 1, K):
+            xa, ia = s.solve(F[k], 1e-8)
+            assert infos[k]["status"] == V.OK and abs(infos[k]["iterations"] - ia["iterations"]) <= 1
+            assert np.linalg.norm(x[k] - xa) / np.linalg.norm(xa) <= (1e-10 if prec == V.FP64 else 1e-6)
+        s.free()
+
+
 def test_budget_without_room_for_tables():
     """A server's budget that holds the hierarchy but not its tables still serves
     the request (as it did when there were none), to the oracle's bars."""
