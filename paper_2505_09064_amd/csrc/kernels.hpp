@@ -21,6 +21,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+#include <utility>
+
 namespace vasmg {
 namespace dev {
 
@@ -97,10 +100,46 @@ __device__ __forceinline__ int xcd_block() {
   return (k < r) ? k * (q + 1) + j : r * (q + 1) + (k - r) * q + j;
 }
 
+// f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>).
+template <class F, int... I>
+__device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_seq(f, std::make_integer_sequence<int, N>());
+}
+
+// v moved between the lanes of a row of 16 (data-parallel primitive CTRL): a few
+// cycles, where a shuffle goes through LDS (about 100).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp(static_cast<int>(b), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(static_cast<int>(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
+}
+constexpr int kDppXor1 = 0xB1;         // quad_perm [1, 0, 3, 2]
+constexpr int kDppXor2 = 0x4E;         // quad_perm [2, 3, 0, 1]
+constexpr int kDppHalfMirror = 0x141;  // lane i of 8 <- 7 - i: the other quad
+constexpr int kDppMirror = 0x140;      // lane i of 16 <- 15 - i: the other half
+constexpr int kDppBcast = 0x150;       // + u: lane u of the row to all 16
+
+// Sum over groups of G lanes, the same in every lane. Inside a row of 16 the
+// pairs, quads and halves meet by mirrored moves (the partial sums they fetch
+// are uniform over what they mirror); rows meet by shuffles.
 template <typename T, int G>
 __device__ __forceinline__ T group_sum(T v) {
+  if constexpr (G > 1) v += dpp<kDppXor1>(v);
+  if constexpr (G > 2) v += dpp<kDppXor2>(v);
+  if constexpr (G > 4) v += dpp<kDppHalfMirror>(v);
+  if constexpr (G > 8) v += dpp<kDppMirror>(v);
 #pragma unroll
-  for (int off = G / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, G);
+  for (int off = 16; off < G; off <<= 1) v += __shfl_xor(v, off, G);
   return v;
 }
 
@@ -448,15 +487,16 @@ struct CellPack {
   static constexpr int threads = CT * CPW;
 };
 
-// Value of lane u of the calling lane's cell segment (segment = cell slot):
-// the wavefront-wide read-lane when one cell owns the wavefront, else a
-// shuffle; every lane of the wavefront must call it.
-template <int CPW, int CT, typename T>
-__device__ __forceinline__ T cell_bcast(T v, int slot, int u) {
+// Value of lane u of the calling lane's cell segment (CT lanes; several cells
+// share a wavefront where CPW > 1); every lane of the wavefront calls it.
+template <int CPW, int CT, int U, typename T>
+__device__ __forceinline__ T cell_bcast(T v) {
   if constexpr (CPW == 1)
-    return bcast(v, u);
+    return bcast(v, U);
+  else if constexpr (CT == 16)
+    return dpp<kDppBcast + U>(v);
   else
-    return __shfl(v, slot * CT + u, 64);
+    return __shfl(v, U, CT);
 }
 
 // Reciprocal of the lane's own diagonal entry Mrow[t] (1 for lanes without a
@@ -471,122 +511,221 @@ __device__ __forceinline__ T own_reciprocal(const T* Mrow, int t, bool own) {
   return own ? T(1) / dg : T(1);
 }
 
-// Per-cell block of NV * GR threads: lane group g (GR lanes, inside one
-// wavefront) sums the off-cell part of the cell's g-th row; the sums meet in
-// LDS; wavefront 0 then runs the sequential sweep over the cell's unknowns.
-// On colour-block levels (E, F non-null) the lower sums take E with L and the
-// upper sums F with U.
-template <typename T, int D, int GR>
-__device__ __forceinline__ void cell_offcell_sums(int v0, int m, const Part<T>& L,
-                                                  const Part<T>& U, const T* __restrict__ x,
-                                                  bool want_lo, bool want_up, T (*sh_lo)[D],
-                                                  T (*sh_up)[D], int tc, const Part<T>* E = nullptr,
-                                                  const Part<T>* F = nullptr) {
-  const int g = tc / GR, gl = tc % GR;
-  T lo[D], up[D];
-#pragma unroll
-  for (int a = 0; a < D; ++a) { lo[a] = T(0); up[a] = T(0); }
-  if (g < m) {
-    const int i = v0 + g;
-    if (want_lo) part_quad_product<T, D, GR>(L, i, gl, x, lo);
-    if (want_lo && E) part_quad_product<T, D, GR>(*E, i, gl, x, lo);
-    if (want_up) part_quad_product<T, D, GR>(U, i, gl, x, up);
-    if (want_up && F) part_quad_product<T, D, GR>(*F, i, gl, x, up);
+// One lane's share of a row of a cell level, positions [kb, ke) of a part: steps
+// of kStep consecutive blocks, one 16-byte load per matrix plane (FP32: a quad,
+// FP64: a pair; rows are padded to quads) and the columns in one load.
+template <typename T>
+struct CellStep {
+  static constexpr int B = 16 / sizeof(T);
+  using Cols = std::conditional_t<B == 4, int4, int2>;
+  static __device__ __forceinline__ Cols cols(const int* col, int q) {
+    return reinterpret_cast<const Cols*>(col)[q];
   }
-#pragma unroll
-  for (int a = 0; a < D; ++a) {
-    if (want_lo) lo[a] = group_sum<T, GR>(lo[a]);
-    if (want_up) up[a] = group_sum<T, GR>(up[a]);
+  static __device__ __forceinline__ int at(const Cols& j, int k) {
+    if constexpr (B == 4)
+      return k == 0 ? j.x : k == 1 ? j.y : k == 2 ? j.z : j.w;
+    else
+      return k == 0 ? j.x : j.y;
   }
-  if (gl == 0) {
+};
+
+template <typename T>
+struct alignas(16) StepVals {
+  T v[16 / sizeof(T)];
+};
+
+// A lane's walk over its steps of a row part. The first step is unconditional
+// and taken in pieces (open: columns and matrix values as soon as the row's range
+// is known; then its neighbours; then the products), so that the caller can put
+// all loads that need no other load's answer in flight before it waits: behind a
+// branch the compiler sinks and serialises them. A lane without a step reads the
+// row's last one (the part's first where there is none before: allocated even for
+// an empty part), which its neighbours fetch anyway, and multiplies it by zeros.
+template <typename T, int D, int G>
+struct RowWalk {
+  static constexpr int DP = Pad<D>::value, B = CellStep<T>::B;
+  int q, qe, q0;
+  typename CellStep<T>::Cols j;
+  StepVals<T> m[D * D];
+  __device__ __forceinline__ void columns(const Part<T>& p, int kb, int ke, int lane) {
+    q = kb / B + lane;
+    qe = ke / B;
+    q0 = max(min(q, qe - 1), 0);
+    j = CellStep<T>::cols(p.col, q0);
+  }
+  __device__ __forceinline__ void values(const Part<T>& p, int qq) {
 #pragma unroll
-    for (int a = 0; a < D; ++a) {
-      sh_lo[g][a] = lo[a];
-      sh_up[g][a] = up[a];
+    for (int e = 0; e < D * D; ++e)
+      m[e] = reinterpret_cast<const StepVals<T>*>(p.val + static_cast<int64_t>(e) * p.nnz)[qq];
+  }
+  __device__ __forceinline__ void product(const Part<T>& p, const T* __restrict__ x, T* acc) {
+    T xv[B][D];
+#pragma unroll
+    for (int k = 0; k < B; ++k)
+      VecIO<T, D>::load(x + static_cast<int64_t>(CellStep<T>::at(j, k)) * DP, xv[k]);
+    __builtin_amdgcn_sched_barrier(0);
+    const bool in = q < qe;
+#pragma unroll
+    for (int k = 0; k < B; ++k) {
+#pragma unroll
+      for (int b = 0; b < D; ++b) {
+        if (!in) xv[k][b] = T(0);
+#pragma unroll
+        for (int a = 0; a < D; ++a) acc[a] += m[a * D + b].v[k] * xv[k][b];
+      }
     }
   }
-  __syncthreads();
-}
+  __device__ __forceinline__ void rest(const Part<T>& p, const T* __restrict__ x, T* acc) {
+    for (q += G; q < qe; q += G) {
+      j = CellStep<T>::cols(p.col, q);
+      values(p, q);
+      __builtin_amdgcn_sched_barrier(0);
+      product(p, x, acc);
+    }
+  }
+};
+
+// What the sweeps and the residual of a cell have in common. Lane group g (GR
+// lanes) sums the off-cell part of the cell's row g; the sums and the cell
+// matrix meet in LDS; wavefront 0 then owns the cell's unknowns, one per lane.
+// A launch of a small level is one pass through this chain of dependent loads
+// (cell -> row ranges -> columns -> neighbours), so nothing waits that need not:
+// both parts' ranges are fetched first and together, then both parts' first
+// columns; the cell matrix goes to LDS in 16-byte pieces by all threads (kept
+// in the 24 registers of each sweeping lane from the start it left too few for
+// the products' loads, and its loads stood before the row ranges).
+// Backward launch, before -> after: level 1 of a 65^3 mesh (1,331 cells a colour,
+// rows of 120 blocks) FP32 17.4 -> 15.5 us, FP64 45.1 -> 24.9; a level of 19,369 rows
+// (141 cells a colour) FP32 6.8 -> 5.1; 2D rows of 22 blocks 7.5 -> 6.6.
+template <typename T, int D, int GR>
+struct CellSums {
+  static constexpr int NV = CellShape<D>::NV, NU = CellShape<D>::NU;
+  static constexpr int CPW = CellPack<D, GR>::CPW, CT = CellPack<D, GR>::CT;
+  static constexpr int PC = NU * NU * static_cast<int>(sizeof(T)) / 16;   // 16-byte pieces of M
+  static constexpr int PR = (PC + CT - 1) / CT;
+  struct Lds {
+    T M[CPW][NU * NU];
+    T lo[CPW][NV][D], up[CPW][NV][D];
+  };
+  // t: thread inside its cell; LO / UP: which parts to sum; own(): loads of the
+  // caller's, issued after the row ranges'. Ends in a barrier. E, F (colour-block
+  // levels): taken with L and U.
+  template <bool LO, bool UP, class Own>
+  static __device__ __forceinline__ void run(Lds& sh, int slot, int t, int c, int v0, int m,
+                                             const Part<T>& L, const Part<T>& U, const Part<T>* E,
+                                             const Part<T>* F, const T* __restrict__ cellM,
+                                             const T* __restrict__ x, Own&& own) {
+    const int g = t / GR, gl = t % GR;
+    const bool has = g < m;
+    const int i = has ? v0 + g : v0;
+    int lb = 0, le = 0, ub = 0, ue = 0;
+    if constexpr (LO) { lb = L.ptr[i]; le = L.ptr[i + 1]; }
+    if constexpr (UP) { ub = U.ptr[i]; ue = U.ptr[i + 1]; }
+    StepVals<T> piece[PR];
+    const StepVals<T>* Mc = reinterpret_cast<const StepVals<T>*>(cellM + static_cast<int64_t>(c) * NU * NU);
+#pragma unroll
+    for (int r = 0; r < PR; ++r) piece[r] = Mc[min(t + r * CT, PC - 1)];
+    own();
+    __builtin_amdgcn_sched_barrier(0);
+    T lo[D], up[D];
+#pragma unroll
+    for (int a = 0; a < D; ++a) { lo[a] = T(0); up[a] = T(0); }
+    RowWalk<T, D, GR> wl, wu;
+    if constexpr (LO) wl.columns(L, lb, has ? le : lb, gl);
+    if constexpr (UP) wu.columns(U, ub, has ? ue : ub, gl);
+    if constexpr (LO) wl.values(L, wl.q0);
+    else wu.values(U, wu.q0);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < PR; ++r)
+      reinterpret_cast<StepVals<T>*>(sh.M[slot])[min(t + r * CT, PC - 1)] = piece[r];
+    if constexpr (LO) {
+      wl.product(L, x, lo);
+      wl.rest(L, x, lo);
+      if constexpr (UP) wu.values(U, wu.q0);
+    }
+    if constexpr (UP) {
+      wu.product(U, x, up);
+      wu.rest(U, x, up);
+    }
+    if (has) {
+      if (LO && E) part_quad_product<T, D, GR>(*E, i, gl, x, lo);
+      if (UP && F) part_quad_product<T, D, GR>(*F, i, gl, x, up);
+    }
+#pragma unroll
+    for (int a = 0; a < D; ++a) {
+      if (LO) lo[a] = group_sum<T, GR>(lo[a]);
+      if (UP) up[a] = group_sum<T, GR>(up[a]);
+    }
+    if (gl == 0) {
+#pragma unroll
+      for (int a = 0; a < D; ++a) {
+        if (LO) sh.lo[slot][g][a] = lo[a];
+        if (UP) sh.up[slot][g][a] = up[a];
+      }
+    }
+    __syncthreads();
+  }
+};
 
 template <typename T, int D, int GR, int MODE>
 __global__ __launch_bounds__((CellPack<D, GR>::threads)) void k_gs_cell(
     int cell0, int ncell, const int* __restrict__ cell_ptr, Part<T> L, Part<T> U,
-    const T* __restrict__ cellM, const T* __restrict__ b, T* x, T* __restrict__ s_save,
-    const int* __restrict__ done) {
-  if (done && *done) return;
+    const T* __restrict__ cellM, const T* __restrict__ b, T* x, T* __restrict__ s_save) {
   constexpr int DP = Pad<D>::value;
-  constexpr int NV = CellShape<D>::NV, NU = CellShape<D>::NU;
-  constexpr int CT = CellPack<D, GR>::CT, CPW = CellPack<D, GR>::CPW;
-  __shared__ T sh_lo[CPW][NV][D], sh_up[CPW][NV][D];
+  using Sums = CellSums<T, D, GR>;
+  constexpr int NV = Sums::NV, NU = Sums::NU, CT = Sums::CT, CPW = Sums::CPW;
+  __shared__ __align__(16) typename Sums::Lds sh;
   const int slot = CPW == 1 ? 0 : threadIdx.x / CT;
   const int t = CPW == 1 ? threadIdx.x : threadIdx.x % CT;
   const int ci = xcd_block() * CPW + slot;
   const bool live = CPW == 1 || ci < ncell;   // the last workgroup may hold fewer cells
   const int c = cell0 + (live ? ci : 0);
   const int v0 = cell_ptr[c], m = live ? cell_ptr[c + 1] - v0 : 0, n = m * D;
-  // the sweeping wavefront fetches its part of the in-cell solve first, so these
-  // loads overlap the off-cell products
   const bool own = t < n;
   const int k = own ? t / D : 0, a = own ? t % D : 0;
   const int64_t xi = static_cast<int64_t>(v0 + k) * DP + a;
-  T Mrow[NU];
   T bt = T(0), xc = T(0);
-  if (threadIdx.x < 64) {
-    const T* Mc = cellM + static_cast<int64_t>(c) * NU * NU;
-#pragma unroll
-    for (int u = 0; u < NU; ++u) Mrow[u] = (own && u < n) ? Mc[u * NU + t] : T(0);
-    if (own) {
-      bt = b[xi];
-      if (MODE != 0) xc = x[xi];
-    }
-  }
-  cell_offcell_sums<T, D, GR>(v0, m, L, U, x, true, MODE != 0, sh_lo[slot], sh_up[slot], t);
+  Sums::template run<true, MODE != 0>(sh, slot, t, c, v0, m, L, U, nullptr, nullptr, cellM, x, [&] {
+    bt = b[xi];
+    if (MODE != 0) xc = x[xi];
+  });
   if (threadIdx.x >= 64) return;          // wavefront 0 finishes the cell(s)
-  const T s_t = own ? bt - sh_lo[slot][k][a] : T(0);
-  const T sup = (own && MODE != 0) ? sh_up[slot][k][a] : T(0);
+  if (!own) xc = T(0);
+  const int tc = min(t, NU - 1);
+  T Mrow[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) Mrow[u] = sh.M[slot][u * NU + tc];
+  const T rdg = own ? T(1) / sh.M[slot][tc * NU + tc] : T(1);
+  const T s_t = own ? bt - sh.lo[slot][k][a] : T(0);
   if (MODE != 2 && s_save && own) s_save[xi] = s_t;
-  T acc = s_t - sup;
-  const T rdg = own_reciprocal<T, NU>(Mrow, t, own);
-  // with one cell per wavefront n is uniform and the guards below are the loop
-  // bounds; with several, every lane takes part in each broadcast
+  // acc: the unknown's residual. Each unknown in turn moves by residual /
+  // diagonal and the others' residuals follow: one multiply, one broadcast and
+  // one multiply-add on the chain per step. Lanes without an unknown hold zeros
+  // (the cell matrix is zero outside the cell's unknowns).
+  T acc = own && MODE != 0 ? s_t - sh.up[slot][k][a] : s_t;
   if (MODE != 0) {
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      if (CPW > 1 || u < n) {
-        const T xu = cell_bcast<CPW, CT>(xc, slot, u);
-        if (u != t && u < n) acc -= Mrow[u] * xu;
-      }
-    }
+    T mx[2] = {T(0), T(0)};
+    static_for<NV>([&](auto vi) {
+      constexpr int v = decltype(vi)::value;
+      if (CPW > 1 || v < m)
+        static_for<D>([&](auto ai) {
+          constexpr int u = v * D + decltype(ai)::value;
+          mx[u % 2] += Mrow[u] * cell_bcast<CPW, CT, u>(xc);
+        });
+    });
+    acc = own ? acc - (mx[0] + mx[1]) : T(0);
   }
-  if (MODE != 2) {
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      if (CPW > 1 || u < n) {
-        T delta = T(0);
-        if (t == u && u < n) {
-          const T xn = acc * rdg;
-          delta = xn - xc;
-          xc = xn;
-        }
-        delta = cell_bcast<CPW, CT>(delta, slot, u);
-        if (t != u && u < n) acc -= Mrow[u] * delta;
-      }
-    }
-  } else {
-#pragma unroll
-    for (int u = NU - 1; u >= 0; --u) {
-      if (CPW > 1 || u < n) {
-        T delta = T(0);
-        if (t == u && u < n) {
-          const T xn = acc * rdg;
-          delta = xn - xc;
-          xc = xn;
-        }
-        delta = cell_bcast<CPW, CT>(delta, slot, u);
-        if (t != u && u < n) acc -= Mrow[u] * delta;
-      }
-    }
-  }
+  static_for<NV>([&](auto vi) {
+    constexpr int v = MODE == 2 ? NV - 1 - decltype(vi)::value : decltype(vi)::value;
+    if (CPW > 1 || v < m)
+      static_for<D>([&](auto ai) {
+        constexpr int u = v * D + (MODE == 2 ? D - 1 - decltype(ai)::value : decltype(ai)::value);
+        const T step = acc * rdg;
+        if (t == u) xc += step;
+        acc -= Mrow[u] * cell_bcast<CPW, CT, u>(step);
+      });
+  });
   if (own) x[xi] = xc;
 }
 
@@ -817,50 +956,41 @@ template <typename T, int D, int GR, int KIND, bool BLK>
 __global__ __launch_bounds__((CellPack<D, GR>::threads)) void k_cell_apply(
     int ncell, const int* __restrict__ cell_ptr, Part<T> L, Part<T> U, Part<T> E, Part<T> F,
     const T* __restrict__ cellM, const T* __restrict__ base, const T* __restrict__ x,
-    T* __restrict__ out, const int* __restrict__ done) {
-  if (done && *done) return;
+    T* __restrict__ out) {
   constexpr int DP = Pad<D>::value;
-  constexpr int NV = CellShape<D>::NV, NU = CellShape<D>::NU;
-  constexpr int CT = CellPack<D, GR>::CT, CPW = CellPack<D, GR>::CPW;
-  __shared__ T sh_lo[CPW][NV][D], sh_up[CPW][NV][D];
+  using Sums = CellSums<T, D, GR>;
+  constexpr int NV = Sums::NV, NU = Sums::NU, CT = Sums::CT, CPW = Sums::CPW;
+  __shared__ __align__(16) typename Sums::Lds sh;
   const int slot = CPW == 1 ? 0 : threadIdx.x / CT;
   const int t = CPW == 1 ? threadIdx.x : threadIdx.x % CT;
   const int ci = xcd_block() * CPW + slot;
   const bool live = CPW == 1 || ci < ncell;
   const int c = live ? ci : 0;
   const int v0 = cell_ptr[c], m = live ? cell_ptr[c + 1] - v0 : 0, n = m * D;
-  // wavefront 0 fetches the in-cell block row, x and the base first
   const bool own = t < n;
   const int k = own ? t / D : 0, a = own ? t % D : 0;
   const int64_t xi = static_cast<int64_t>(v0 + k) * DP + a;
-  T Mrow[NU];
   T xt = T(0), bt = T(0);
-  if (threadIdx.x < 64) {
-    const T* Mc = cellM + static_cast<int64_t>(c) * NU * NU;
-#pragma unroll
-    for (int u = 0; u < NU; ++u) Mrow[u] = (own && u < n) ? Mc[u * NU + t] : T(0);
-    if (own) {
-      xt = x[xi];
-      if (KIND != 2) bt = base[xi];
-    }
-  }
-  cell_offcell_sums<T, D, GR>(v0, m, L, U, x, KIND != 0, true, sh_lo[slot], sh_up[slot], t,
-                              BLK ? &E : nullptr, BLK ? &F : nullptr);
+  Sums::template run<KIND != 0, true>(sh, slot, t, c, v0, m, L, U, BLK ? &E : nullptr,
+                                      BLK ? &F : nullptr, cellM, x, [&] {
+                                        xt = x[xi];
+                                        if (KIND != 2) bt = base[xi];
+                                      });
   if (threadIdx.x >= 64) return;
-  const T off = own ? (KIND != 0 ? sh_lo[slot][k][a] : T(0)) + sh_up[slot][k][a] : T(0);
-  T mx = T(0);
-#pragma unroll
-  for (int u = 0; u < NU; ++u) {
-    if (CPW > 1 || u < n) {
-      const T xu = cell_bcast<CPW, CT>(xt, slot, u);
-      if (u < n) mx += Mrow[u] * xu;
-    }
-  }
+  if (!own) xt = T(0);
+  const int tc = min(t, NU - 1);
+  T mx[2] = {T(0), T(0)};
+  static_for<NV>([&](auto vi) {
+    constexpr int v = decltype(vi)::value;
+    if (CPW > 1 || v < m)
+      static_for<D>([&](auto ai) {
+        constexpr int u = v * D + decltype(ai)::value;
+        mx[u % 2] += sh.M[slot][u * NU + tc] * cell_bcast<CPW, CT, u>(xt);
+      });
+  });
   if (!own) return;
-  if (KIND == 2)
-    out[xi] = off + mx;
-  else
-    out[xi] = bt - off - mx;
+  const T off = (KIND != 0 ? sh.lo[slot][k][a] : T(0)) + sh.up[slot][k][a];
+  out[xi] = KIND == 2 ? off + (mx[0] + mx[1]) : bt - off - (mx[0] + mx[1]);
 }
 
 // ---------------------------------------------------------------------------

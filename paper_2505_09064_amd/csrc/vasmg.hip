@@ -523,15 +523,20 @@ void upload_level(vasmg_ctx& C, int l, bool need32, bool need64, const std::vect
   }
 }
 
-// Lanes per block row from the mean off-cell blocks per row: about two blocks per
-// lane; 3D cell levels use 16..64; 2D cell levels (short rows) about two quads of
-// 4 blocks per lane, 4..64, several cells sharing a wavefront below 16.
+// Lanes per block row from the mean off-cell blocks per row. Point levels: about
+// two blocks per lane. 3D cell levels: about a quad of 4 blocks per lane and part,
+// 16 or 32 (forward sweep + residual + backward sweep of a level, 8 / 16 / 32 / 64
+// lanes: 218,053 rows of 120 blocks 1.07 / 0.91 / 0.86 / 1.14 ms in FP32 and 1.85 /
+// 1.53 / 1.39 / 1.52 in FP64, 19,369 rows of 90 blocks 0.34 / 0.28 / 0.25 / 0.27, 4,624 rows of
+// 79 blocks 0.071 / 0.074 / 0.067 / 0.078). 2D cell levels (short rows): about two
+// quads per lane, 4..64, several cells sharing a wavefront below 16 (137,528 rows
+// of 22 blocks, 4 / 8 / 16 lanes: 0.169 / 0.197 / 0.268).
 void set_lanes(DevLevel& dl) {
   const double avg = dl.n > 0 ? static_cast<double>(dl.nnz) / dl.n : 1.0;
-  if (dl.cells && dl.d == 2)
-    dl.G = std::min(64, std::max(4, pow2_ceil(static_cast<int>(std::ceil(avg / 8.0)))));
-  else
-    dl.G = std::min(64, std::max(dl.cells ? 16 : 4, pow2_ceil(static_cast<int>(std::ceil(avg / 2.0)))));
+  auto lanes = [&](double blocks, int lo, int hi) {
+    return std::min(hi, std::max(lo, pow2_ceil(static_cast<int>(std::ceil(avg / blocks)))));
+  };
+  dl.G = !dl.cells ? lanes(2.0, 4, 64) : dl.d == 2 ? lanes(8.0, 4, 64) : lanes(4.0, 16, 32);
   dl.Gspmv = dl.G;
 }
 
@@ -665,8 +670,8 @@ void upload_level_device(vasmg_ctx& C, int l, bool need32, bool need64, const st
   dl.Ustride = nU;
   dl.Lptr = C.upload(Lptr);
   dl.Uptr = C.upload(Uptr);
-  dl.Lcol = C.dalloc<int>(nL);
-  dl.Ucol = C.dalloc<int>(nU);
+  dl.Lcol = C.dalloc<int>(std::max<int64_t>(nL, dev::kQuad));   // a first step to read (RowWalk)
+  dl.Ucol = C.dalloc<int>(std::max<int64_t>(nU, dev::kQuad));
   int64_t nE = 0, nF = 0;
   if (dl.blocks) {
     const std::vector<int> Eptr = padded_ptr(cnt[kPartE], true), Fptr = padded_ptr(cnt[kPartF], true);
@@ -682,8 +687,8 @@ void upload_level_device(vasmg_ctx& C, int l, bool need32, bool need64, const st
   if (dl.cells) dl.cell_ptr = C.upload(cell_ptr);
   const int64_t m_len = dl.cells ? static_cast<int64_t>(dl.ncells) * NU * NU : static_cast<int64_t>(n) * dd;
   if (need64) {
-    dl.Lval64 = C.dalloc<double>(nL * dd);
-    dl.Uval64 = C.dalloc<double>(nU * dd);
+    dl.Lval64 = C.dalloc<double>(std::max<int64_t>(nL * dd, dev::kQuad));
+    dl.Uval64 = C.dalloc<double>(std::max<int64_t>(nU * dd, dev::kQuad));
     if (dl.blocks) {
       dl.Eval64 = C.dalloc<double>(nE * dd);
       dl.Fval64 = C.dalloc<double>(nF * dd);
@@ -692,8 +697,8 @@ void upload_level_device(vasmg_ctx& C, int l, bool need32, bool need64, const st
     dl.has64 = true;
   }
   if (need32) {
-    dl.Lval32 = C.dalloc<float>(nL * dd);
-    dl.Uval32 = C.dalloc<float>(nU * dd);
+    dl.Lval32 = C.dalloc<float>(std::max<int64_t>(nL * dd, dev::kQuad));
+    dl.Uval32 = C.dalloc<float>(std::max<int64_t>(nU * dd, dev::kQuad));
     if (dl.blocks) {
       dl.Eval32 = C.dalloc<float>(nE * dd);
       dl.Fval32 = C.dalloc<float>(nF * dd);
@@ -1042,13 +1047,13 @@ void launch_gs_cells(const DevLevel& lv, int c, int mode, const T* b, T* x, T* s
     const dim3 blk(Pack::threads), grid((nc + Pack::CPW - 1) / Pack::CPW);
     if (mode == 0)
       hipLaunchKernelGGL((dev::k_gs_cell<T, D, GR, 0>), grid, blk, 0, st, c0, nc, lv.cell_ptr,
-                         Lp, Up, M, b, x, s_save, done);
+                         Lp, Up, M, b, x, s_save);
     else if (mode == 1)
       hipLaunchKernelGGL((dev::k_gs_cell<T, D, GR, 1>), grid, blk, 0, st, c0, nc, lv.cell_ptr,
-                         Lp, Up, M, b, x, s_save, done);
+                         Lp, Up, M, b, x, s_save);
     else
       hipLaunchKernelGGL((dev::k_gs_cell<T, D, GR, 2>), grid, blk, 0, st, c0, nc, lv.cell_ptr,
-                         Lp, Up, M, b, x, s_save, done);
+                         Lp, Up, M, b, x, s_save);
   });
 }
 
@@ -1062,11 +1067,11 @@ void launch_cell_apply(const DevLevel& lv, const T* base, const T* x, T* out, co
     if (lv.blocks)
       hipLaunchKernelGGL((dev::k_cell_apply<T, D, GR, KIND, true>), grid, blk, 0, st, lv.ncells,
                          lv.cell_ptr, LevelMats<T>::L(lv), LevelMats<T>::U(lv), Ep, Fp,
-                         LevelMats<T>::cellM(lv), base, x, out, done);
+                         LevelMats<T>::cellM(lv), base, x, out);
     else
       hipLaunchKernelGGL((dev::k_cell_apply<T, D, GR, KIND, false>), grid, blk, 0, st, lv.ncells,
                          lv.cell_ptr, LevelMats<T>::L(lv), LevelMats<T>::U(lv), Ep, Fp,
-                         LevelMats<T>::cellM(lv), base, x, out, done);
+                         LevelMats<T>::cellM(lv), base, x, out);
   });
 }
 
