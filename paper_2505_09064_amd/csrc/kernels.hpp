@@ -100,6 +100,14 @@ __device__ __forceinline__ int xcd_block() {
   return (k < r) ? k * (q + 1) + j : r * (q + 1) + (k - r) * q + j;
 }
 
+// LDS written by some lanes of a wavefront is read by others of it (a wavefront's
+// LDS accesses run in program order; the compiler must keep them so).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // f(integral_constant<int, 0>) ... f(integral_constant<int, N - 1>).
 template <class F, int... I>
 __device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, I...>) {
@@ -108,6 +116,50 @@ __device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int,
 template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) {
   static_for_seq(f, std::make_integer_sequence<int, N>());
+}
+
+// v of the lane that CTRL names, kept from `old` where there is none or the row of
+// 16 is not in ROWS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_from(int old, int v) {
+  return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_from(float old, float v) {
+  return __int_as_float(dpp_from<CTRL, ROWS>(__float_as_int(old), __float_as_int(v)));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_from(double old, double v) {
+  const long long o = __double_as_longlong(old), b = __double_as_longlong(v);
+  const int lo = dpp_from<CTRL, ROWS>(static_cast<int>(o), static_cast<int>(b));
+  const int hi = dpp_from<CTRL, ROWS>(static_cast<int>(o >> 32), static_cast<int>(b >> 32));
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
+}
+constexpr int kDppRowShr = 0x110;      // + n: lane i of 16 <- i - n
+constexpr int kDppBcast15 = 0x142;     // last lane of a row of 16 to the next row
+constexpr int kDppBcast31 = 0x143;     // lane 31 to the upper half
+
+// One step of the scan below: add the fetched values where the keys agree.
+template <int CTRL, int ROWS, typename T, int D>
+__device__ __forceinline__ void segment_step(int key, T (&v)[D]) {
+  const bool same = dpp_from<CTRL, ROWS>(-1, key) == key;
+#pragma unroll
+  for (int a = 0; a < D; ++a) {
+    const T o = dpp_from<CTRL, ROWS>(T(0), v[a]);
+    v[a] += same ? o : T(0);
+  }
+}
+
+// Inclusive sums over runs of equal keys (ascending over the wavefront, >= 0):
+// a run's last lane ends with the run's sum. All lanes take part.
+template <typename T, int D>
+__device__ __forceinline__ void segment_scan(int key, T (&v)[D]) {
+  segment_step<kDppRowShr + 1, 0xf>(key, v);
+  segment_step<kDppRowShr + 2, 0xf>(key, v);
+  segment_step<kDppRowShr + 4, 0xf>(key, v);
+  segment_step<kDppRowShr + 8, 0xf>(key, v);
+  segment_step<kDppBcast15, 0xa>(key, v);
+  segment_step<kDppBcast31, 0xc>(key, v);
 }
 
 // v moved between the lanes of a row of 16 (data-parallel primitive CTRL): a few
@@ -529,6 +581,8 @@ struct CellStep {
   }
 };
 
+typedef int Vec16 __attribute__((ext_vector_type(4)));   // 16 bytes on the way through registers
+
 template <typename T>
 struct alignas(16) StepVals {
   T v[16 / sizeof(T)];
@@ -585,28 +639,133 @@ struct RowWalk {
   }
 };
 
-// What the sweeps and the residual of a cell have in common. Lane group g (GR
-// lanes) sums the off-cell part of the cell's row g; the sums and the cell
-// matrix meet in LDS; wavefront 0 then owns the cell's unknowns, one per lane.
-// A launch of a small level is one pass through this chain of dependent loads
-// (cell -> row ranges -> columns -> neighbours), so nothing waits that need not:
-// both parts' ranges are fetched first and together, then both parts' first
-// columns; the cell matrix goes to LDS in 16-byte pieces by all threads (kept
-// in the 24 registers of each sweeping lane from the start it left too few for
-// the products' loads, and its loads stood before the row ranges).
-// Backward launch, before -> after: level 1 of a 65^3 mesh (1,331 cells a colour,
-// rows of 120 blocks) FP32 17.4 -> 15.5 us, FP64 45.1 -> 24.9; a level of 19,369 rows
-// (141 cells a colour) FP32 6.8 -> 5.1; 2D rows of 22 blocks 7.5 -> 6.6.
+// What the sweeps and the residual of a cell have in common: the off-cell products
+// of its rows (their sums end in LDS) and the cell matrix (staged in LDS);
+// wavefront 0 then owns the cell's unknowns, one per lane. A launch of a small
+// level is one pass through a chain of dependent loads (cell -> row ranges ->
+// columns -> neighbours), so nothing waits that need not: both parts' ranges are
+// fetched first and together, then columns and matrix values; the cell matrix goes
+// to LDS in 16-byte pieces by all threads.
+//
+// One cell per workgroup (3D): the rows of a cell are one contiguous run of steps
+// in each part, and the workgroup's threads take the steps of both runs in order,
+// whichever row they belong to: every lane has a step and every load of a
+// wavefront is one contiguous kilobyte. A step's row is found among the cell's row
+// ranges (scalars); the sums of a wavefront's rows come from a segmented scan.
+// With a group of lanes per row a cell waited for its longest row (up to six
+// rounds of 16 lanes where the mean row has one) with half its lanes idle:
+// backward launch of level 1 of a 65^3 mesh (1,331 cells a colour, 42.6 MB) FP32
+// 17.4 us at the start of this form, 15.5 with a group of lanes per row and the
+// loads first, 13.7 flat (3.1 TB/s; the launch itself and the cell's own chain
+// are about 5 us of it); 4,092 cells a colour 30.1 -> 26.6 us (4.8 TB/s; a plain
+// read of ten such planes streams at 6.1); its residual 194 -> 176 us.
+// Several cells per wavefront (2D, rows of a few steps): a group of GR lanes per row.
 template <typename T, int D, int GR>
 struct CellSums {
   static constexpr int NV = CellShape<D>::NV, NU = CellShape<D>::NU;
   static constexpr int CPW = CellPack<D, GR>::CPW, CT = CellPack<D, GR>::CT;
   static constexpr int PC = NU * NU * static_cast<int>(sizeof(T)) / 16;   // 16-byte pieces of M
   static constexpr int PR = (PC + CT - 1) / CT;
+  static constexpr int NW = CPW == 1 ? CT / 64 : 1;   // partial sums of a row
   struct Lds {
     T M[CPW][NU * NU];
-    T lo[CPW][NV][D], up[CPW][NV][D];
+    T sum[CPW][NW][2 * NV][D];   // lower parts of the rows, then upper parts
+    __device__ __forceinline__ T total(int slot, int row, int a) const {
+      T v = sum[slot][0][row][a];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v += sum[slot][w][row][a];
+      return v;
+    }
+    __device__ __forceinline__ T lo(int slot, int k, int a) const { return total(slot, k, a); }
+    __device__ __forceinline__ T up(int slot, int k, int a) const { return total(slot, NV + k, a); }
   };
+
+  // One step of the flat walk over both parts of a cell.
+  template <bool LO, bool UP>
+  struct Flat {
+    static constexpr int B = CellStep<T>::B, DP = Pad<D>::value;
+    int pl[NV + 1], pu[NV + 1];   // row ranges in steps (uniform)
+    int nl, total;
+    int key, end, q;
+    bool in;
+    typename CellStep<T>::Cols j;
+    StepVals<T> m[D * D];
+    // one vector load for both parts' row ranges, read into scalars lane by lane
+    // (as 18 scalar loads per wavefront they missed the scalar cache: the backward
+    // launch of 1,331 cells took 56 us instead of 15)
+    int pv;
+    __device__ __forceinline__ void load_ranges(const Part<T>& L, const Part<T>& U, int v0, int m_) {
+      const int lane = threadIdx.x & 63;
+      const int* ptr = !LO || (UP && lane >= 16) ? U.ptr : L.ptr;
+      pv = ptr[v0 + min(lane & 15, m_)];
+    }
+    __device__ __forceinline__ void ranges() {
+      static_for<NV + 1>([&](auto ri) {
+        constexpr int r = decltype(ri)::value;
+        pl[r] = LO ? __builtin_amdgcn_readlane(pv, r) / B : 0;
+        pu[r] = UP ? __builtin_amdgcn_readlane(pv, LO ? 16 + r : r) / B : 0;
+      });
+      nl = pl[NV] - pl[0];
+      total = nl + pu[NV] - pu[0];
+    }
+    __device__ __forceinline__ void fetch(const Part<T>& L, const Part<T>& U, int f) {
+      in = f < total;
+      const int fc = max(min(f, total - 1), 0);
+      const bool u = !LO || (UP && fc >= nl);
+      q = u ? pu[0] + fc - nl : pl[0] + fc;
+      // a cell without off-cell blocks reads the step before its (empty) run, or
+      // the part's first (present and zero even in an empty part)
+      if (total == 0) q = max(q - 1, 0);
+      // row: the row ranges at or below the step (either part's, constant indices:
+      // arrays chosen between at run time would go to scratch memory)
+      int kl = 0, ku = 0, el = pl[NV], eu = pu[NV];
+      static_for<NV - 1>([&](auto ri) {
+        constexpr int r = NV - 1 - decltype(ri)::value;
+        if constexpr (LO) {
+          kl += q >= pl[r];
+          el = q < pl[r] ? pl[r] : el;
+        }
+        if constexpr (UP) {
+          ku += q >= pu[r];
+          eu = q < pu[r] ? pu[r] : eu;
+        }
+      });
+      end = u ? eu : el;
+      key = in ? (u ? ku + NV : kl) : 2 * NV;
+      const int* col = u ? U.col : L.col;
+      const T* val = u ? U.val : L.val;
+      const int64_t nnz = u ? U.nnz : L.nnz;
+      j = CellStep<T>::cols(col, q);
+#pragma unroll
+      for (int e = 0; e < D * D; ++e)
+        m[e] = reinterpret_cast<const StepVals<T>*>(val + static_cast<int64_t>(e) * nnz)[q];
+    }
+    __device__ __forceinline__ void add(const T* __restrict__ x, T (*sum)[D]) {
+      T xv[B][D];
+#pragma unroll
+      for (int k = 0; k < B; ++k)
+        VecIO<T, D>::load(x + static_cast<int64_t>(CellStep<T>::at(j, k)) * DP, xv[k]);
+      __builtin_amdgcn_sched_barrier(0);
+      T acc[D];
+#pragma unroll
+      for (int a = 0; a < D; ++a) acc[a] = T(0);
+#pragma unroll
+      for (int k = 0; k < B; ++k) {
+#pragma unroll
+        for (int b = 0; b < D; ++b) {
+#pragma unroll
+          for (int a = 0; a < D; ++a) acc[a] += m[a * D + b].v[k] * xv[k][b];
+        }
+      }
+      segment_scan<T, D>(key, acc);
+      if (in && (q + 1 == end || (threadIdx.x & 63) == 63)) {
+#pragma unroll
+        for (int a = 0; a < D; ++a) sum[key][a] += acc[a];
+      }
+      wave_sync();   // the next step's tail lanes are others
+    }
+  };
+
   // t: thread inside its cell; LO / UP: which parts to sum; own(): loads of the
   // caller's, issued after the row ranges'. Ends in a barrier. E, F (colour-block
   // levels): taken with L and U.
@@ -615,53 +774,105 @@ struct CellSums {
                                              const Part<T>& L, const Part<T>& U, const Part<T>* E,
                                              const Part<T>* F, const T* __restrict__ cellM,
                                              const T* __restrict__ x, Own&& own) {
-    const int g = t / GR, gl = t % GR;
-    const bool has = g < m;
-    const int i = has ? v0 + g : v0;
-    int lb = 0, le = 0, ub = 0, ue = 0;
-    if constexpr (LO) { lb = L.ptr[i]; le = L.ptr[i + 1]; }
-    if constexpr (UP) { ub = U.ptr[i]; ue = U.ptr[i + 1]; }
-    StepVals<T> piece[PR];
-    const StepVals<T>* Mc = reinterpret_cast<const StepVals<T>*>(cellM + static_cast<int64_t>(c) * NU * NU);
+    Vec16 piece[PR];
+    const Vec16* Mc = reinterpret_cast<const Vec16*>(cellM + static_cast<int64_t>(c) * NU * NU);
+    if constexpr (CPW == 1) {
+      const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
+      T(*sum)[D] = sh.sum[0][w];
+      Flat<LO, UP> fl;
+      fl.load_ranges(L, U, v0, m);
+      static_for<PR>([&](auto ri) {
+        constexpr int r = decltype(ri)::value;
+        piece[r] = Mc[min(t + r * CT, PC - 1)];
+      });
+      own();
+      __builtin_amdgcn_sched_barrier(0);
+      fl.ranges();
+      if (lane < 2 * NV) {   // each wavefront its own sums
 #pragma unroll
-    for (int r = 0; r < PR; ++r) piece[r] = Mc[min(t + r * CT, PC - 1)];
-    own();
-    __builtin_amdgcn_sched_barrier(0);
-    T lo[D], up[D];
+        for (int a = 0; a < D; ++a) sum[lane][a] = T(0);
+      }
+      wave_sync();
+      fl.fetch(L, U, t);
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<PR>([&](auto ri) {
+        constexpr int r = decltype(ri)::value;
+        reinterpret_cast<Vec16*>(sh.M[0])[min(t + r * CT, PC - 1)] = piece[r];
+      });
+      fl.add(x, sum);
+      for (int f = CT; f + w * 64 < fl.total; f += CT) {   // uniform over the wavefront
+        fl.fetch(L, U, f + t);
+        __builtin_amdgcn_sched_barrier(0);
+        fl.add(x, sum);
+      }
+      if (E || F) {
+        // colour-block levels: a group of GR lanes per row
+        const int g = t / GR, gl = t % GR;
+        T lo[D], up[D];
 #pragma unroll
-    for (int a = 0; a < D; ++a) { lo[a] = T(0); up[a] = T(0); }
-    RowWalk<T, D, GR> wl, wu;
-    if constexpr (LO) wl.columns(L, lb, has ? le : lb, gl);
-    if constexpr (UP) wu.columns(U, ub, has ? ue : ub, gl);
-    if constexpr (LO) wl.values(L, wl.q0);
-    else wu.values(U, wu.q0);
-    __builtin_amdgcn_sched_barrier(0);
+        for (int a = 0; a < D; ++a) { lo[a] = T(0); up[a] = T(0); }
+        if (g < m) {
+          if (LO && E) part_quad_product<T, D, GR>(*E, v0 + g, gl, x, lo);
+          if (UP && F) part_quad_product<T, D, GR>(*F, v0 + g, gl, x, up);
+        }
 #pragma unroll
-    for (int r = 0; r < PR; ++r)
-      reinterpret_cast<StepVals<T>*>(sh.M[slot])[min(t + r * CT, PC - 1)] = piece[r];
-    if constexpr (LO) {
-      wl.product(L, x, lo);
-      wl.rest(L, x, lo);
-      if constexpr (UP) wu.values(U, wu.q0);
-    }
-    if constexpr (UP) {
-      wu.product(U, x, up);
-      wu.rest(U, x, up);
-    }
-    if (has) {
-      if (LO && E) part_quad_product<T, D, GR>(*E, i, gl, x, lo);
-      if (UP && F) part_quad_product<T, D, GR>(*F, i, gl, x, up);
-    }
+        for (int a = 0; a < D; ++a) {
+          lo[a] = group_sum<T, GR>(lo[a]);
+          up[a] = group_sum<T, GR>(up[a]);
+        }
+        if (gl == 0) {
 #pragma unroll
-    for (int a = 0; a < D; ++a) {
-      if (LO) lo[a] = group_sum<T, GR>(lo[a]);
-      if (UP) up[a] = group_sum<T, GR>(up[a]);
-    }
-    if (gl == 0) {
+          for (int a = 0; a < D; ++a) {
+            sum[g][a] += lo[a];
+            sum[NV + g][a] += up[a];
+          }
+        }
+      }
+    } else {
+      const int g = t / GR, gl = t % GR;
+      const bool has = g < m;
+      const int i = has ? v0 + g : v0;
+      int lb = 0, le = 0, ub = 0, ue = 0;
+      if constexpr (LO) { lb = L.ptr[i]; le = L.ptr[i + 1]; }
+      if constexpr (UP) { ub = U.ptr[i]; ue = U.ptr[i + 1]; }
+      static_for<PR>([&](auto ri) {
+        constexpr int r = decltype(ri)::value;
+        piece[r] = Mc[min(t + r * CT, PC - 1)];
+      });
+      own();
+      __builtin_amdgcn_sched_barrier(0);
+      T lo[D], up[D];
+#pragma unroll
+      for (int a = 0; a < D; ++a) { lo[a] = T(0); up[a] = T(0); }
+      RowWalk<T, D, GR> wl, wu;
+      if constexpr (LO) wl.columns(L, lb, has ? le : lb, gl);
+      if constexpr (UP) wu.columns(U, ub, has ? ue : ub, gl);
+      if constexpr (LO) wl.values(L, wl.q0);
+      else wu.values(U, wu.q0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < PR; ++r)
+        reinterpret_cast<Vec16*>(sh.M[slot])[min(t + r * CT, PC - 1)] = piece[r];
+      if constexpr (LO) {
+        wl.product(L, x, lo);
+        wl.rest(L, x, lo);
+        if constexpr (UP) wu.values(U, wu.q0);
+      }
+      if constexpr (UP) {
+        wu.product(U, x, up);
+        wu.rest(U, x, up);
+      }
 #pragma unroll
       for (int a = 0; a < D; ++a) {
-        if (LO) sh.lo[slot][g][a] = lo[a];
-        if (UP) sh.up[slot][g][a] = up[a];
+        if (LO) lo[a] = group_sum<T, GR>(lo[a]);
+        if (UP) up[a] = group_sum<T, GR>(up[a]);
+      }
+      if (gl == 0) {
+#pragma unroll
+        for (int a = 0; a < D; ++a) {
+          if (LO) sh.sum[slot][0][g][a] = lo[a];
+          if (UP) sh.sum[slot][0][NV + g][a] = up[a];
+        }
       }
     }
     __syncthreads();
@@ -697,13 +908,13 @@ __global__ __launch_bounds__((CellPack<D, GR>::threads)) void k_gs_cell(
 #pragma unroll
   for (int u = 0; u < NU; ++u) Mrow[u] = sh.M[slot][u * NU + tc];
   const T rdg = own ? T(1) / sh.M[slot][tc * NU + tc] : T(1);
-  const T s_t = own ? bt - sh.lo[slot][k][a] : T(0);
+  const T s_t = own ? bt - sh.lo(slot, k, a) : T(0);
   if (MODE != 2 && s_save && own) s_save[xi] = s_t;
   // acc: the unknown's residual. Each unknown in turn moves by residual /
   // diagonal and the others' residuals follow: one multiply, one broadcast and
   // one multiply-add on the chain per step. Lanes without an unknown hold zeros
   // (the cell matrix is zero outside the cell's unknowns).
-  T acc = own && MODE != 0 ? s_t - sh.up[slot][k][a] : s_t;
+  T acc = own && MODE != 0 ? s_t - sh.up(slot, k, a) : s_t;
   if (MODE != 0) {
     T mx[2] = {T(0), T(0)};
     static_for<NV>([&](auto vi) {
@@ -989,7 +1200,7 @@ __global__ __launch_bounds__((CellPack<D, GR>::threads)) void k_cell_apply(
       });
   });
   if (!own) return;
-  const T off = (KIND != 0 ? sh.lo[slot][k][a] : T(0)) + sh.up[slot][k][a];
+  const T off = (KIND != 0 ? sh.lo(slot, k, a) : T(0)) + sh.up(slot, k, a);
   out[xi] = KIND == 2 ? off + (mx[0] + mx[1]) : bt - off - (mx[0] + mx[1]);
 }
 

@@ -524,13 +524,13 @@ void upload_level(vasmg_ctx& C, int l, bool need32, bool need64, const std::vect
 }
 
 // Lanes per block row from the mean off-cell blocks per row. Point levels: about
-// two blocks per lane. 3D cell levels: about a quad of 4 blocks per lane and part,
-// 16 or 32 (forward sweep + residual + backward sweep of a level, 8 / 16 / 32 / 64
-// lanes: 218,053 rows of 120 blocks 1.07 / 0.91 / 0.86 / 1.14 ms in FP32 and 1.85 /
-// 1.53 / 1.39 / 1.52 in FP64, 19,369 rows of 90 blocks 0.34 / 0.28 / 0.25 / 0.27, 4,624 rows of
-// 79 blocks 0.071 / 0.074 / 0.067 / 0.078). 2D cell levels (short rows): about two
-// quads per lane, 4..64, several cells sharing a wavefront below 16 (137,528 rows
-// of 22 blocks, 4 / 8 / 16 lanes: 0.169 / 0.197 / 0.268).
+// two blocks per lane. 3D cell levels (a cell's lanes share its rows' steps): about
+// a quad of 4 blocks per lane and part, 16 or 32 (forward sweep + residual +
+// backward sweep of a level at 8 / 16 / 32 / 64 lanes: 218,053 rows of 120 blocks
+// 0.86 / 0.83 / 0.78 / 1.01 ms in FP32 and 1.49 / 1.44 / 1.34 / 1.36 in FP64, 19,369 rows
+// of 90 blocks 0.34 / 0.27 / 0.24 / 0.41). 2D cell levels (short rows): about two
+// quads per lane, 4..64, several cells sharing a wavefront below 16 (137,528 rows of
+// 22 blocks, 4 / 8 / 16 lanes: 0.169 / 0.197 / 0.268).
 void set_lanes(DevLevel& dl) {
   const double avg = dl.n > 0 ? static_cast<double>(dl.nnz) / dl.n : 1.0;
   auto lanes = [&](double blocks, int lo, int hi) {
@@ -706,6 +706,15 @@ void upload_level_device(vasmg_ctx& C, int l, bool need32, bool need64, const st
     (dl.cells ? dl.cellM32 : dl.diag32) = C.dalloc<float>(m_len);
     dl.has32 = true;
   }
+  // the first step of an empty part (RowWalk, Flat): a zero block of row 0
+  auto clear_first = [&](int64_t nnz, int* col, float* v32, double* v64) {
+    if (nnz > 0) return;
+    C.clear(col, dev::kQuad * sizeof(int));
+    if (v32) C.clear(v32, dev::kQuad * sizeof(float));
+    if (v64) C.clear(v64, dev::kQuad * sizeof(double));
+  };
+  clear_first(nL, dl.Lcol, dl.Lval32, dl.Lval64);
+  clear_first(nU, dl.Ucol, dl.Uval32, dl.Uval64);
   a.part[kPartL] = {dl.Lptr, d_cnt[kPartL], nL, dl.Lcol, dl.Lval32, dl.Lval64};
   a.part[kPartU] = {dl.Uptr, d_cnt[kPartU], nU, dl.Ucol, dl.Uval32, dl.Uval64};
   if (dl.blocks) {

@@ -126,3 +126,31 @@ def test_budget_without_room_for_tables():
     xo, io = Oracle(m.coords, m.elems, m.E, m.nu, m.fixed).solve(m.rhs[0], 1e-8)
     assert abs(res["info"]["iterations"] - io["iterations"]) <= 1
     assert np.linalg.norm(x - xo) / np.linalg.norm(xo) <= 1e-8
+
+
+def _few_cell_meshes():
+    """Meshes whose first coarse levels hold one to eight cells."""
+    return [small2d(3, seed=1, fix="x0"), small2d(4, seed=2, fix="x0"), small3d(3, seed=3, fix="x0"),
+            small2d(4, seed=4, fix="symmetry"), small3d(3, seed=5, fix="symmetry")]
+
+
+@pytest.mark.parametrize("prec", [V.FP64, V.FP32_PRECOND])
+def test_cells_without_off_cell_blocks(prec):
+    """Cells at the ends of the sweep order have no lower or no upper blocks, and a
+    level of one cell has none at all: the first step of an empty range is read and
+    dropped. Sweeps, residual (through the cycle) and solve against the oracle."""
+    for m in _few_cell_meshes():
+        o = Oracle(m.coords, m.elems, m.E, m.nu, m.fixed)
+        s = V.Solver.from_mesh(m, precision=prec)
+        xo, io = o.solve(m.rhs[0], 1e-8)
+        x, info = s.solve(m.rhs[0], 1e-8)
+        assert info["converged"] == 1 and abs(info["iterations"] - io["iterations"]) <= 1
+        assert np.linalg.norm(x - xo) / np.linalg.norm(xo) <= (1e-8 if prec == V.FP64 else 1e-5)
+        for l in range(1, s.hierarchy_info()[0] - 1):
+            n = s.level_info(l)["n_vertices"]
+            b = torch.from_numpy(np.random.default_rng(l).normal(size=(n, m.dim))).cuda()
+            y = torch.zeros_like(b)
+            for back in (0, 1):
+                s.gs_sweep_device(l, prec, back, b, y)
+            assert torch.isfinite(y).all()
+        s.free()
