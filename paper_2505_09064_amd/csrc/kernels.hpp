@@ -325,11 +325,86 @@ __device__ __forceinline__ void part_quad_product(const Part<T>& p, int i, int l
     row_product<T, D, G>(p.ptr[i], p.ptr[i + 1], lane, p.col, p.val, p.nnz, x, acc);
 }
 
-template <typename T, int D, int G>
-__device__ __forceinline__ void part_product(const Part<T>& p, int i, int lane,
-                                             const T* __restrict__ x, T* acc) {
-  row_product<T, D, G>(p.ptr[i], p.ptr[i + 1], lane, p.col, p.val, p.nnz, x, acc);
+// A row's diagonal block and (x != NULL, else zero) its own entry.
+template <typename T, int D>
+__device__ __forceinline__ void load_own(const T* __restrict__ diag, const T* __restrict__ x, int i, T* dg,
+                                         T* xi) {
+#pragma unroll
+  for (int e = 0; e < D * D; ++e) dg[e] = diag[static_cast<int64_t>(i) * D * D + e];
+  if (x) {
+    VecIO<T, D>::load(x + static_cast<int64_t>(i) * Pad<D>::value, xi);
+  } else {
+#pragma unroll
+    for (int a = 0; a < D; ++a) xi[a] = T(0);
+  }
 }
+
+// Off-diagonal products of a point-level row (LO / UP: which parts), a lane group
+// of G taking the blocks of the parts in order. Rows hold about 7 blocks per part,
+// so a row is one round, a chain of three dependent loads (row ranges -> columns ->
+// neighbours): the ranges of both parts come together, and columns and values of
+// UN blocks per lane go out before the first neighbour is waited for; only longer
+// rows loop. A lane without a block reads its row's last one (or, in an empty row,
+// the block before; an empty part has one zero block) times zero.
+template <typename T, int D, int G, bool LO, bool UP>
+struct PointRow {
+  static constexpr int DP = Pad<D>::value, UN = LO && UP ? 2 : 1;
+  int l0 = 0, u0 = 0, nl = 0, total = 0;
+  __device__ __forceinline__ void ranges(const Part<T>& L, const Part<T>& U, int i) {
+    int le = 0, ue = 0;
+    if (LO) { l0 = L.ptr[i]; le = L.ptr[i + 1]; }
+    if (UP) { u0 = U.ptr[i]; ue = U.ptr[i + 1]; }
+    nl = le - l0;
+    total = nl + ue - u0;
+  }
+  __device__ __forceinline__ void round(const Part<T>& L, const Part<T>& U, int f0,
+                                        const T* __restrict__ x, T* acc) const {
+    T m[UN][D * D], xv[UN][D];
+    int j[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int f = max(min(f0 + u * G, total - 1), 0);
+      const bool up = !LO || (UP && f >= nl);
+      int k = up ? u0 + f - nl : l0 + f;
+      if (total == 0) k = max(k - 1, 0);
+      const int* col = up ? U.col : L.col;
+      const T* val = up ? U.val : L.val;
+      const int64_t nnz = up ? U.nnz : L.nnz;
+      j[u] = col[k];
+#pragma unroll
+      for (int e = 0; e < D * D; ++e) m[u][e] = val[e * nnz + k];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < UN; ++u) VecIO<T, D>::load(x + static_cast<int64_t>(j[u]) * DP, xv[u]);
+    // (pinned here: the compiler would sink a load whose value is only selected)
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+#pragma unroll
+      for (int b = 0; b < D; ++b) asm volatile("" : "+v"(xv[u][b]));
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const bool in = f0 + u * G < total;
+#pragma unroll
+      for (int b = 0; b < D; ++b) {
+        const T xb = in ? xv[u][b] : T(0);
+#pragma unroll
+        for (int a = 0; a < D; ++a) acc[a] += m[u][a * D + b] * xb;
+      }
+    }
+  }
+  // acc = the row's sums, in every lane of the group
+  __device__ __forceinline__ void sum(const Part<T>& L, const Part<T>& U, int lane,
+                                      const T* __restrict__ x, T* acc) const {
+#pragma unroll
+    for (int a = 0; a < D; ++a) acc[a] = T(0);
+    round(L, U, lane, x, acc);
+    for (int f = lane + UN * G; f < total; f += UN * G) round(L, U, f, x, acc);
+#pragma unroll
+    for (int a = 0; a < D; ++a) acc[a] = group_sum<T, G>(acc[a]);
+  }
+};
 
 // ---------------------------------------------------------------------------
 // K1: y = A x (diag + off-diagonal), optional partial dot x.y per workgroup.
@@ -338,25 +413,19 @@ template <typename T, int D, int G, bool DOT>
 __global__ __launch_bounds__(kBlock) void k_spmv(int n, Part<T> L, Part<T> U,
                                                  const T* __restrict__ diag,
                                                  const T* __restrict__ x, T* __restrict__ y,
-                                                 double* __restrict__ partial,
-                                                 const int* __restrict__ done) {
-  if (done && *done) return;
+                                                 double* __restrict__ partial) {
   constexpr int DP = Pad<D>::value;
   const int lane = threadIdx.x % G;
   const int i = xcd_block() * (kBlock / G) + threadIdx.x / G;
   double dot = 0.0;
   if (i < n) {
-    T acc[D];
-#pragma unroll
-    for (int a = 0; a < D; ++a) acc[a] = T(0);
-    part_product<T, D, G>(L, i, lane, x, acc);
-    part_product<T, D, G>(U, i, lane, x, acc);
-#pragma unroll
-    for (int a = 0; a < D; ++a) acc[a] = group_sum<T, G>(acc[a]);
+    PointRow<T, D, G, true, true> row;
+    row.ranges(L, U, i);
+    T acc[D], xi[D], dg[D * D];
+    load_own<T, D>(diag, x, i, dg, xi);
+    row.sum(L, U, lane, x, acc);
     if (lane == 0) {
-      T xi[D], yi[D];
-      VecIO<T, D>::load(x + static_cast<int64_t>(i) * DP, xi);
-      const T* dg = diag + static_cast<int64_t>(i) * D * D;
+      T yi[D];
 #pragma unroll
       for (int a = 0; a < D; ++a) {
         T s = acc[a];
@@ -379,24 +448,19 @@ __global__ __launch_bounds__(kBlock) void k_spmv(int n, Part<T> L, Part<T> U,
 template <typename T, int D, int G>
 __global__ __launch_bounds__(kBlock) void k_residual_full(
     int n, Part<T> L, Part<T> U, const T* __restrict__ diag, const T* __restrict__ b,
-    const T* __restrict__ x, T* __restrict__ r, const int* __restrict__ done) {
-  if (done && *done) return;
+    const T* __restrict__ x, T* __restrict__ r) {
   constexpr int DP = Pad<D>::value;
   const int lane = threadIdx.x % G;
   const int i = xcd_block() * (kBlock / G) + threadIdx.x / G;
   if (i >= n) return;
-  T acc[D];
-#pragma unroll
-  for (int a = 0; a < D; ++a) acc[a] = T(0);
-  part_product<T, D, G>(L, i, lane, x, acc);
-  part_product<T, D, G>(U, i, lane, x, acc);
-#pragma unroll
-  for (int a = 0; a < D; ++a) acc[a] = group_sum<T, G>(acc[a]);
+  PointRow<T, D, G, true, true> row;
+  row.ranges(L, U, i);
+  T acc[D], xi[D], bi[D], dg[D * D];
+  load_own<T, D>(diag, x, i, dg, xi);
+  VecIO<T, D>::load(b + static_cast<int64_t>(i) * DP, bi);
+  row.sum(L, U, lane, x, acc);
   if (lane == 0) {
-    T xi[D], bi[D], ri[D];
-    VecIO<T, D>::load(x + static_cast<int64_t>(i) * DP, xi);
-    VecIO<T, D>::load(b + static_cast<int64_t>(i) * DP, bi);
-    const T* dg = diag + static_cast<int64_t>(i) * D * D;
+    T ri[D];
 #pragma unroll
     for (int a = 0; a < D; ++a) {
       T s = bi[a] - acc[a];
@@ -418,37 +482,27 @@ __global__ __launch_bounds__(kBlock) void k_residual_full(
 template <typename T, int D, int G, int MODE>
 __global__ __launch_bounds__(kBlock) void k_gs_color(
     int row0, int nrows, Part<T> L, Part<T> U, const T* __restrict__ diag,
-    const T* __restrict__ b, T* x, T* __restrict__ s_save, const int* __restrict__ done) {
-  if (done && *done) return;
+    const T* __restrict__ b, T* x, T* __restrict__ s_save) {
   constexpr int DP = Pad<D>::value;
   const int lane = threadIdx.x % G;
   const int g = xcd_block() * (kBlock / G) + threadIdx.x / G;
   if (g >= nrows) return;
   const int i = row0 + g;
-  // lane 0 fetches what it needs to finish the row before the row product
+  // s = b - L x is only wanted on its own by the forward sweeps; the backward
+  // sweep takes both parts in one walk
+  PointRow<T, D, G, true, MODE == 2> low;
+  PointRow<T, D, G, false, true> upp;
+  low.ranges(L, U, i);
+  if (MODE == 1) upp.ranges(L, U, i);
+  // what finishes the row, before the products
   T dg[D * D], xi[D], bi[D];
-  if (lane == 0) {
-    const T* dp = diag + static_cast<int64_t>(i) * D * D;
-#pragma unroll
-    for (int e = 0; e < D * D; ++e) dg[e] = dp[e];
-    VecIO<T, D>::load(b + static_cast<int64_t>(i) * DP, bi);
-    if (MODE == 0) {
-#pragma unroll
-      for (int a = 0; a < D; ++a) xi[a] = T(0);
-    } else {
-      VecIO<T, D>::load(x + static_cast<int64_t>(i) * DP, xi);
-    }
-  }
+  load_own<T, D>(diag, MODE == 0 ? nullptr : x, i, dg, xi);
+  VecIO<T, D>::load(b + static_cast<int64_t>(i) * DP, bi);
   T lo[D], up[D];
 #pragma unroll
-  for (int a = 0; a < D; ++a) { lo[a] = T(0); up[a] = T(0); }
-  part_product<T, D, G>(L, i, lane, x, lo);
-  if (MODE != 0) part_product<T, D, G>(U, i, lane, x, up);
-#pragma unroll
-  for (int a = 0; a < D; ++a) {
-    lo[a] = group_sum<T, G>(lo[a]);
-    if (MODE != 0) up[a] = group_sum<T, G>(up[a]);
-  }
+  for (int a = 0; a < D; ++a) up[a] = T(0);
+  low.sum(L, U, lane, x, lo);
+  if (MODE == 1) upp.sum(L, U, lane, x, up);
   if (lane != 0) return;
   T s[D], rhs[D];
 #pragma unroll
@@ -483,23 +537,19 @@ __global__ __launch_bounds__(kBlock) void k_gs_color(
 template <typename T, int D, int G>
 __global__ __launch_bounds__(kBlock) void k_residual_upper(
     int n, Part<T> U, const T* __restrict__ diag, const T* __restrict__ s_save,
-    const T* __restrict__ x, T* __restrict__ r, const int* __restrict__ done) {
-  if (done && *done) return;
+    const T* __restrict__ x, T* __restrict__ r) {
   constexpr int DP = Pad<D>::value;
   const int lane = threadIdx.x % G;
   const int i = xcd_block() * (kBlock / G) + threadIdx.x / G;
   if (i >= n) return;
-  T acc[D];
-#pragma unroll
-  for (int a = 0; a < D; ++a) acc[a] = T(0);
-  part_product<T, D, G>(U, i, lane, x, acc);
-#pragma unroll
-  for (int a = 0; a < D; ++a) acc[a] = group_sum<T, G>(acc[a]);
+  PointRow<T, D, G, false, true> row;
+  row.ranges(U, U, i);
+  T acc[D], xi[D], si[D], dg[D * D];
+  load_own<T, D>(diag, x, i, dg, xi);
+  VecIO<T, D>::load(s_save + static_cast<int64_t>(i) * DP, si);
+  row.sum(U, U, lane, x, acc);
   if (lane == 0) {
-    T xi[D], si[D], ri[D];
-    VecIO<T, D>::load(x + static_cast<int64_t>(i) * DP, xi);
-    VecIO<T, D>::load(s_save + static_cast<int64_t>(i) * DP, si);
-    const T* dg = diag + static_cast<int64_t>(i) * D * D;
+    T ri[D];
 #pragma unroll
     for (int a = 0; a < D; ++a) {
       T s = si[a] - acc[a];
@@ -1255,9 +1305,7 @@ template <typename T, int D, int GT>
 __global__ __launch_bounds__(kBlock) void k_restrict(int nc, const int* __restrict__ ptr,
                                                      const int* __restrict__ idx,
                                                      const T* __restrict__ w,
-                                                     const T* __restrict__ r, T* __restrict__ bc,
-                                                     const int* __restrict__ done) {
-  if (done && *done) return;
+                                                     const T* __restrict__ r, T* __restrict__ bc) {
   constexpr int DP = Pad<D>::value;
   const int lane = threadIdx.x % GT;
   const int I = xcd_block() * (kBlock / GT) + threadIdx.x / GT;
@@ -1276,9 +1324,7 @@ __global__ __launch_bounds__(kBlock) void k_prolong_add(int nf, const int* __res
                                                         const int* __restrict__ idx,
                                                         const T* __restrict__ w,
                                                         const T* __restrict__ e, T* x,
-                                                        const uint8_t* __restrict__ fixed,
-                                                        const int* __restrict__ done) {
-  if (done && *done) return;
+                                                        const uint8_t* __restrict__ fixed) {
   constexpr int DP = Pad<D>::value;
   const int lane = threadIdx.x % GT;
   const int i = xcd_block() * (kBlock / GT) + threadIdx.x / GT;

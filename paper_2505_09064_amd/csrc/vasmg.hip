@@ -973,11 +973,11 @@ int launch_spmv(const DevLevel& lv, const T* x, T* y, double* partial, int n_par
     if (partial)
       hipLaunchKernelGGL((dev::k_spmv<T, D, GG, true>), dim3(grid), dim3(dev::kBlock), 0, st, lv.n,
                          LevelMats<T>::L(lv), LevelMats<T>::U(lv), LevelMats<T>::diag(lv),
-                         x, y, partial, done);
+                         x, y, partial);
     else
       hipLaunchKernelGGL((dev::k_spmv<T, D, GG, false>), dim3(grid), dim3(dev::kBlock), 0, st,
                          lv.n, LevelMats<T>::L(lv), LevelMats<T>::U(lv), LevelMats<T>::diag(lv),
-                         x, y, partial, done);
+                         x, y, partial);
   });
   return used;
 }
@@ -993,15 +993,15 @@ void launch_gs_color(const DevLevel& lv, int c, int mode, const T* b, T* x, T* s
     if (mode == 0)
       hipLaunchKernelGGL((dev::k_gs_color<T, D, GG, 0>), dim3(grid), dim3(dev::kBlock), 0, st, r0,
                          nr, LevelMats<T>::L(lv), LevelMats<T>::U(lv), LevelMats<T>::diag(lv), b, x,
-                         s_save, done);
+                         s_save);
     else if (mode == 1)
       hipLaunchKernelGGL((dev::k_gs_color<T, D, GG, 1>), dim3(grid), dim3(dev::kBlock), 0, st, r0,
                          nr, LevelMats<T>::L(lv), LevelMats<T>::U(lv), LevelMats<T>::diag(lv), b, x,
-                         s_save, done);
+                         s_save);
     else
       hipLaunchKernelGGL((dev::k_gs_color<T, D, GG, 2>), dim3(grid), dim3(dev::kBlock), 0, st, r0,
                          nr, LevelMats<T>::L(lv), LevelMats<T>::U(lv), LevelMats<T>::diag(lv), b, x,
-                         s_save, done);
+                         s_save);
   });
 }
 
@@ -1114,7 +1114,7 @@ void launch_residual_upper(const DevLevel& lv, const T* s, const T* x, T* r, con
   DISPATCH_G(lv.G, {
     hipLaunchKernelGGL((dev::k_residual_upper<T, D, GG>), dim3(grid_for(lv.n, dev::kBlock / GG)),
                        dim3(dev::kBlock), 0, st, lv.n, LevelMats<T>::U(lv), LevelMats<T>::diag(lv),
-                       s, x, r, done);
+                       s, x, r);
   });
 }
 
@@ -1128,7 +1128,7 @@ void launch_residual_full(const DevLevel& lv, const T* b, const T* x, T* r, cons
   DISPATCH_G(lv.G, {
     hipLaunchKernelGGL((dev::k_residual_full<T, D, GG>), dim3(grid_for(lv.n, dev::kBlock / GG)),
                        dim3(dev::kBlock), 0, st, lv.n, LevelMats<T>::L(lv), LevelMats<T>::U(lv),
-                       LevelMats<T>::diag(lv), b, x, r, done);
+                       LevelMats<T>::diag(lv), b, x, r);
   });
 }
 
@@ -1152,14 +1152,14 @@ template <typename T, int D>
 void launch_restrict(const DevLevel& lv, const T* r, T* bc, const int* done, hipStream_t st) {
   hipLaunchKernelGGL((dev::k_restrict<T, D, kRestrictLanes>),
                      dim3(grid_for(lv.nnext, dev::kBlock / kRestrictLanes)), dim3(dev::kBlock), 0,
-                     st, lv.nnext, lv.pt_ptr, lv.pt_idx, LevelMats<T>::ptw(lv), r, bc, done);
+                     st, lv.nnext, lv.pt_ptr, lv.pt_idx, LevelMats<T>::ptw(lv), r, bc);
 }
 
 template <typename T, int D>
 void launch_prolong(const DevLevel& lv, const T* e, T* x, const int* done, hipStream_t st) {
   hipLaunchKernelGGL((dev::k_prolong_add<T, D, kProlongLanes>),
                      dim3(grid_for(lv.n, dev::kBlock / kProlongLanes)), dim3(dev::kBlock), 0, st,
-                     lv.n, lv.p_ptr, lv.p_idx, LevelMats<T>::pw(lv), e, x, lv.fixed, done);
+                     lv.n, lv.p_ptr, lv.p_idx, LevelMats<T>::pw(lv), e, x, lv.fixed);
 }
 
 template <typename T>
