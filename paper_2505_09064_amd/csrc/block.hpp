@@ -71,15 +71,12 @@ __device__ __forceinline__ T slot_sum(T v) {
 
 // acc += sum over blocks [kb, ke) of A_blk x_col(blk)[column k]; lane (slot, k)
 // of the row group takes blocks kb + slot, kb + slot + S, ... in ascending order.
-// The blocks go in chunks of CH (kStage on the cell levels, 4 per slot on the
-// point levels): the row group's GL lanes copy a chunk's D*D planes and columns
+// The blocks go in chunks of CH (4 per slot): the row group's GL lanes copy a chunk's D*D planes and columns
 // into LDS with coalesced loads (each value read once), and then every lane
 // reads its blocks from there. Read directly, each matrix value would be loaded
 // by each of the K column lanes, which multiplies what the load path returns
 // per block by K. The next chunk's values are loaded while the current one is
 // used.
-constexpr int kStage = 16;
-
 template <typename T, int D, int CH>
 struct StageShape {
   static constexpr int DD = D * D;
@@ -88,13 +85,13 @@ struct StageShape {
   static constexpr int NE = (DD + 1) * CH;                // planes and columns per chunk
 };
 
-template <typename T, int D, int CH = kStage>
+template <typename T, int D, int CH>
 struct alignas(16) RowStage {
   T val[CH * StageShape<T, D, CH>::BS];
   int col[CH];
 };
 
-template <typename T, int D, int K, int S, int VS, int GL, int CH = kStage, int CPL = 1>
+template <typename T, int D, int K, int S, int VS, int GL, int CH, int CPL = 1>
 __device__ __forceinline__ void mc_row_product_staged(int kb, int ke, int self, int lane, int slot,
                                                       int k, const int* __restrict__ col,
                                                       const T* __restrict__ val, int64_t nnz,
@@ -338,24 +335,31 @@ __global__ __launch_bounds__(kBlock) void k_residual_upper_mc(
 // blockIdx.y selects a batch of K columns, `batch` elements apart (the tables of
 // dense.hpp are built from many batches at once; a block solve has one).
 // ---------------------------------------------------------------------------
-template <typename T, int D, int K>
+// Columns per lane in the off-cell products (two, k and k + K / 2, from 8 columns
+// up: a staged block is read from LDS once for both), block slots per row and
+// blocks per chunk: four in flight per lane whatever the group (65^3, 4 and 8
+// columns, chunks of 16 / 32 / 64 blocks with 32 lanes: 36.1 / 31.3 / 33.8 and 41.7 /
+// 40.9 / 42.0 ms; 23x30x26 FP64: 52.0 / 43.6 / 44.1 and 28.4 / 24.0 / 24.6).
+template <int K, int GL>
+struct CellWalk {
+  static constexpr int CPL = K >= 8 ? 2 : 1, KL = K / CPL, S = GL / KL, CH = 4 * S;
+};
+
+template <typename T, int D, int K, int GL>
 struct CellLds {
   static constexpr int NV = CellShape<D>::NV, NU = CellShape<D>::NU;
   T M[NU * NU];
   T lo[NV][K][D];
   T up[NV][K][D];
-  RowStage<T, D> stage[NV];   // one per row group
+  RowStage<T, D, CellWalk<K, GL>::CH> stage[NV];   // one per row group
 };
 
 template <typename T, int D, int K, int GL>
 __device__ __forceinline__ void mc_cell_offcell(int v0, int m, const Part<T>& L, const Part<T>& U,
                                                 const T* __restrict__ x, bool want_lo,
-                                                bool want_up, CellLds<T, D, K>& sh) {
-  // two columns per lane (k and k + K/2) from 8 columns up: a staged block is
-  // read from LDS once for both
-  constexpr int CPL = K >= 8 ? 2 : 1, KL = K / CPL;
-  constexpr int S = GL / KL;
-  static_assert(S <= kStage, "slots fit a chunk");
+                                                bool want_up, CellLds<T, D, K, GL>& sh) {
+  using Walk = CellWalk<K, GL>;
+  constexpr int CPL = Walk::CPL, KL = Walk::KL, S = Walk::S, CH = Walk::CH;
   const int g = threadIdx.x / GL, lane = threadIdx.x % GL, slot = lane / KL, k = lane % KL;
   T lo[CPL * D], up[CPL * D];
 #pragma unroll
@@ -363,10 +367,10 @@ __device__ __forceinline__ void mc_cell_offcell(int v0, int m, const Part<T>& L,
   if (g < m) {
     const int i = v0 + g;
     if (want_lo)
-      mc_row_product_staged<T, D, K, S, D, GL, kStage, CPL>(L.ptr[i], L.ptr[i + 1], i, lane, slot, k,
+      mc_row_product_staged<T, D, K, S, D, GL, CH, CPL>(L.ptr[i], L.ptr[i + 1], i, lane, slot, k,
                                                             L.col, L.val, L.nnz, x, lo, sh.stage[g]);
     if (want_up)
-      mc_row_product_staged<T, D, K, S, D, GL, kStage, CPL>(U.ptr[i], U.ptr[i + 1], i, lane, slot, k,
+      mc_row_product_staged<T, D, K, S, D, GL, CH, CPL>(U.ptr[i], U.ptr[i + 1], i, lane, slot, k,
                                                             U.col, U.val, U.nnz, x, up, sh.stage[g]);
   }
 #pragma unroll
@@ -389,9 +393,9 @@ __device__ __forceinline__ void mc_cell_offcell(int v0, int m, const Part<T>& L,
 // In-cell sweep of two columns by one wavefront: lane 32h + t owns unknown t of
 // column k0 + h; each new value is broadcast to the column's lanes with lane
 // reads (the per-column analogue of k_gs_cell's sweep).
-template <typename T, int D, int K, int MODE>
+template <typename T, int D, int K, int GL, int MODE>
 __device__ __forceinline__ void mc_cell_sweep_pair(int k0, int v0, int n, const T* __restrict__ Msh,
-                                                   const CellLds<T, D, K>& sh,
+                                                   const CellLds<T, D, K, GL>& sh,
                                                    const T* __restrict__ b, T* x,
                                                    T* __restrict__ s_save) {
   constexpr int DP = D;   // coarse-level vectors: packed
@@ -412,28 +416,27 @@ __device__ __forceinline__ void mc_cell_sweep_pair(int k0, int v0, int n, const 
     acc = su - (MODE != 0 ? sh.up[row][k][a] : T(0));
     if (MODE != 0) xc = x[o];
   }
-  const T rdg = own_reciprocal<T, NU>(Mrow, t, own);
+  const T rdg = own ? T(1) / Msh[t * NU + t] : T(1);
+  // acc: the unknown's residual (as in k_gs_cell)
   if (MODE != 0) {
+    T mx[2] = {T(0), T(0)};
 #pragma unroll
     for (int u = 0; u < NU; ++u) {
       if (u < n) {
         const T x0 = bcast(xc, u), x1 = bcast(xc, 32 + u);
-        if (u != t) acc -= Mrow[u] * (h ? x1 : x0);
+        mx[u % 2] += Mrow[u] * (h ? x1 : x0);
       }
     }
+    acc -= mx[0] + mx[1];
   }
 #pragma unroll
   for (int uu = 0; uu < NU; ++uu) {
     const int u = (MODE == 2) ? NU - 1 - uu : uu;
     if (u < n) {
-      T delta = T(0);
-      if (t == u && own) {
-        const T xn = acc * rdg;
-        delta = xn - xc;
-        xc = xn;
-      }
-      const T d0 = bcast(delta, u), d1 = bcast(delta, 32 + u);
-      if (t != u) acc -= Mrow[u] * (h ? d1 : d0);
+      const T step = acc * rdg;
+      if (t == u) xc += step;
+      const T d0 = bcast(step, u), d1 = bcast(step, 32 + u);
+      acc -= Mrow[u] * (h ? d1 : d0);
     }
   }
   if (own) x[o] = xc;
@@ -445,7 +448,7 @@ __global__ __launch_bounds__(CellShape<D>::NV * GL) void k_gs_cell_mc(
     const T* __restrict__ cellM, const T* __restrict__ b, T* x, T* __restrict__ s_save,
     int64_t batch) {
   constexpr int NU = CellShape<D>::NU;
-  __shared__ CellLds<T, D, K> sh;
+  __shared__ CellLds<T, D, K, GL> sh;
   b += blockIdx.y * batch;
   x += blockIdx.y * batch;
   if (s_save) s_save += blockIdx.y * batch;
@@ -458,7 +461,7 @@ __global__ __launch_bounds__(CellShape<D>::NV * GL) void k_gs_cell_mc(
   // wavefront w sweeps column pairs w, w + waves, ... (all lanes of a wave active)
   const int w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   for (int k0 = 2 * w; k0 < K; k0 += 2 * nw)
-    mc_cell_sweep_pair<T, D, K, MODE>(k0, v0, n, sh.M, sh, b, x, s_save);
+    mc_cell_sweep_pair<T, D, K, GL, MODE>(k0, v0, n, sh.M, sh, b, x, s_save);
 }
 
 // r = s - U x - M x on a cell (after a forward sweep that saved s).
@@ -468,7 +471,7 @@ __global__ __launch_bounds__(CellShape<D>::NV * GL) void k_cell_residual_mc(
     const T* __restrict__ s_save, const T* __restrict__ x, T* __restrict__ r, int64_t batch) {
   constexpr int DP = D;   // coarse-level vectors: packed
   constexpr int NU = CellShape<D>::NU;
-  __shared__ CellLds<T, D, K> sh;
+  __shared__ CellLds<T, D, K, GL> sh;
   s_save += blockIdx.y * batch;
   x += blockIdx.y * batch;
   r += blockIdx.y * batch;
