@@ -182,18 +182,27 @@ __device__ __forceinline__ void mc_part_staged(const Part<T>& p, int i, int lane
                                                               k, p.col, p.val, p.nnz, x, acc, st);
 }
 
-// Per-column block sums: thread t contributes v to column col_of(t); on return
-// thread t < K holds column t's sum (fixed order: ascending thread index).
-template <int K, class ColOf>
-__device__ __forceinline__ double block_sum_cols(double v, double* sh, ColOf col_of) {
+// Per-column block sums: thread t contributes v to column (t / W) % K; on return
+// thread k < K holds column k's sum. A tree over the threads of equal t % (K * W)
+// (fixed order), then the W values of a column; one thread per column adding all
+// of the workgroup's values took 10 us of each reduction kernel.
+template <int K, int W>
+__device__ __forceinline__ double block_sum_cols(double v, double* sh) {
+  static_assert(kBlock % (K * W) == 0, "whole periods");
   sh[threadIdx.x] = v;
   __syncthreads();
-  double s = 0.0;
-  if (threadIdx.x < K)
-    for (int j = 0; j < static_cast<int>(blockDim.x); ++j)
-      if (col_of(j) == static_cast<int>(threadIdx.x)) s += sh[j];
+#pragma unroll
+  for (int s = kBlock / 2; s >= K * W; s >>= 1) {
+    if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
+    __syncthreads();
+  }
+  double r = 0.0;
+  if (threadIdx.x < K) {
+#pragma unroll
+    for (int a = 0; a < W; ++a) r += sh[threadIdx.x * W + a];
+  }
   __syncthreads();
-  return s;
+  return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -236,7 +245,7 @@ __global__ __launch_bounds__(kBlock) void k_spmv_mc(int n, Part<double> L, Part<
   }
   if (DOT) {
     __shared__ double sh[kBlock];
-    const double s = block_sum_cols<K>(dot, sh, [](int t) { return t % K; });
+    const double s = block_sum_cols<K, 1>(dot, sh);
     if (threadIdx.x < K) partial[static_cast<int64_t>(blockIdx.x) * K + threadIdx.x] = s;
   }
 }
@@ -497,8 +506,12 @@ __global__ __launch_bounds__(CellShape<D>::NV * GL) void k_cell_residual_mc(
 }
 
 // ---------------------------------------------------------------------------
-// Transfers: b_c = P^T r and x += P e, lane k of a K-lane group = column k.
+// Transfers: b_c = P^T r, 32 lanes per row (K columns x 32 / K slots over its
+// 9 to 60 entries: with one slot a row was one chain of dependent gathers, 37 us at
+// 4,374 rows and 4 columns), and x += P e, lane k of a K-lane group = column k.
 // ---------------------------------------------------------------------------
+constexpr int kRestrictMcLanes = 32;
+
 // VF: stride of the fine level's vectors; the coarse level's are packed (D).
 template <typename T, int D, int K, int VF>
 __global__ __launch_bounds__(kBlock) void k_restrict_mc(int nc, const int* __restrict__ ptr,
@@ -508,20 +521,23 @@ __global__ __launch_bounds__(kBlock) void k_restrict_mc(int nc, const int* __res
                                                         T* __restrict__ bc, int64_t batch_f) {
   r += blockIdx.y * batch_f;
   bc += blockIdx.y * (static_cast<int64_t>(nc) * K * D);
-  const int k = threadIdx.x % K;
-  const int I = xcd_block() * (kBlock / K) + threadIdx.x / K;
+  const int lane = threadIdx.x % kRestrictMcLanes, slot = lane / K, k = lane % K;
+  const int I = xcd_block() * (kBlock / kRestrictMcLanes) + threadIdx.x / kRestrictMcLanes;
   if (I >= nc) return;
   T acc[D];
 #pragma unroll
   for (int a = 0; a < D; ++a) acc[a] = T(0);
-  for (int p = ptr[I]; p < ptr[I + 1]; ++p) {
+#pragma unroll 2
+  for (int p = ptr[I] + slot; p < ptr[I + 1]; p += kRestrictMcLanes / K) {
     T e[D];
     BlockVecIO<T, D, VF>::load(r + (static_cast<int64_t>(idx[p]) * K + k) * VF, e);
     const T wp = w[p];
 #pragma unroll
     for (int a = 0; a < D; ++a) acc[a] += wp * e[a];
   }
-  BlockVecIO<T, D, D>::store(bc + (static_cast<int64_t>(I) * K + k) * D, acc);
+#pragma unroll
+  for (int a = 0; a < D; ++a) acc[a] = slot_sum<T, K, kRestrictMcLanes>(acc[a]);
+  if (slot == 0) BlockVecIO<T, D, D>::store(bc + (static_cast<int64_t>(I) * K + k) * D, acc);
 }
 
 template <typename T, int D, int K, int VF>
@@ -643,7 +659,7 @@ __global__ __launch_bounds__(kBlock) void k_dot_mc(int64_t n, const double* __re
   for (int64_t i = blockIdx.x * int64_t(kBlock) + threadIdx.x; i < n;
        i += int64_t(gridDim.x) * kBlock)
     v += a[i] * static_cast<double>(b[i]);
-  const double s = block_sum_cols<K>(v, sh, [](int t) { return flat_col<K, DP>(t); });
+  const double s = block_sum_cols<K, DP>(v, sh);
   if (threadIdx.x < K) partial[static_cast<int64_t>(blockIdx.x) * K + threadIdx.x] = s;
 }
 
@@ -661,7 +677,7 @@ __global__ __launch_bounds__(kBlock) void k_sub_norm_mc(int64_t n, const double*
     if (r) r[i] = t;
     v += t * t;
   }
-  const double s = block_sum_cols<K>(v, sh, [](int t) { return flat_col<K, DP>(t); });
+  const double s = block_sum_cols<K, DP>(v, sh);
   if (threadIdx.x < K) partial[static_cast<int64_t>(blockIdx.x) * K + threadIdx.x] = s;
 }
 
@@ -689,7 +705,7 @@ __global__ __launch_bounds__(kBlock) void k_update_xr_mc(int64_t n, const Scalar
       v += ri * ri;
     }
   }
-  const double s = block_sum_cols<K>(v, sh, [](int t) { return flat_col<K, DP>(t); });
+  const double s = block_sum_cols<K, DP>(v, sh);
   if (threadIdx.x < K) partial[static_cast<int64_t>(blockIdx.x) * K + threadIdx.x] = s;
 }
 

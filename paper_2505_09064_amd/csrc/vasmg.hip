@@ -2069,7 +2069,7 @@ void enqueue_vcycle_mc(vasmg_ctx& C, hipStream_t st) {
     for (int k = 0; k < C.opt.n_pre; ++k)
       launch_gs_sweep_mc<T, D, K>(lv, lv.mcGL, 1, false, k == 0, b, x, s, st);
     launch_residual_mc<T, D, K>(lv, lv.mcGL, 1, s, x, r, st);
-    const dim3 rgrid(grid_for(lv.nnext, dev::kBlock / K));
+    const dim3 rgrid(grid_for(lv.nnext, dev::kBlock / dev::kRestrictMcLanes));
     if (l == 0)
       hipLaunchKernelGGL((dev::k_restrict_mc<T, D, K, dev::Pad<D>::value>), rgrid, dim3(dev::kBlock),
                          0, st, lv.nnext, lv.pt_ptr, lv.pt_idx, LevelMats<T>::ptw(lv), r,
@@ -2343,7 +2343,7 @@ void dense_down(vasmg_ctx& C, std::vector<DenseWork>& w, int l0, int l1, int nb,
     for (int k = 0; k < C.opt.n_pre; ++k)
       launch_gs_sweep_mc<T, D, K>(lv, dev::kCellLanesNarrow, nb, false, k == 0, b, x, s, st);
     launch_residual_mc<T, D, K>(lv, dev::kCellLanesNarrow, nb, s, x, r, st);
-    hipLaunchKernelGGL((dev::k_restrict_mc<T, D, K, D>), dim3(grid_for(lv.nnext, dev::kBlock / K), nb),
+    hipLaunchKernelGGL((dev::k_restrict_mc<T, D, K, D>), dim3(grid_for(lv.nnext, dev::kBlock / dev::kRestrictMcLanes), nb),
                        dim3(dev::kBlock), 0, st, lv.nnext, lv.pt_ptr, lv.pt_idx, LevelMats<T>::ptw(lv), r,
                        static_cast<T*>(w[l + 1].v[0]), static_cast<int64_t>(lv.n) * K * D);
   }
