@@ -639,15 +639,21 @@ __device__ __forceinline__ int flat_col(int t) {
 // per-column scalar updates, one workgroup per column
 template <int MODE, int K>
 __global__ __launch_bounds__(kBlock) void k_finalize_mc(const double* __restrict__ partial, int np,
-                                                        Scalars* sc) {
+                                                        Scalars* sc, int* mail) {
   __shared__ double sh[kBlock];
   const int k = blockIdx.x;
   Scalars* s = sc + k;
-  if (MODE != FIN_NORMF && MODE != FIN_TRUE && s->done) return;
+  if (MODE != FIN_NORMF && MODE != FIN_TRUE && s->done) {
+    if (MODE == FIN_RES && threadIdx.x == 0) report(mail + k, s);
+    return;
+  }
   double v = 0.0;
   for (int i = threadIdx.x; i < np; i += blockDim.x) v += partial[static_cast<int64_t>(i) * K + k];
   const double tot = block_sum(v, sh);
-  if (threadIdx.x == 0) finalize_scalar<MODE>(tot, s);
+  if (threadIdx.x == 0) {
+    finalize_scalar<MODE>(tot, s);
+    if (MODE == FIN_RES) report(mail + k, s);
+  }
 }
 
 template <int K, int DP, typename TB>

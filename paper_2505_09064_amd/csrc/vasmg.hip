@@ -7,7 +7,8 @@
 //   graph A: q = A p with p.q partials, alpha, x += alpha p, r -= alpha q with
 //            ||r||^2 partials (and the FP32 copy of r), convergence flag;
 //   graph B: z = B r (the V-cycle), r.z partials, beta, p = z + beta p.
-// The host reads the device flag after graph A (the only per-iteration sync).
+// Graph A ends in a report to pinned host memory that the host polls (the only
+// per-iteration wait).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -136,7 +137,7 @@ class PinnedPool {
     }
     // one allocation per 64 blocks: pinned allocations are rare and early
     char* p = nullptr;
-    if (hipHostMalloc(reinterpret_cast<void**>(&p), kBytes * kBatch) != hipSuccess)
+    if (hipHostMalloc(reinterpret_cast<void**>(&p), kBytes * kBatch, hipHostMallocCoherent) != hipSuccess)
       throw vasmg::Error{VASMG_ENOMEM, "pinned host allocation failed"};
     for (int i = kBatch - 1; i > 0; --i) free_.push_back(p + static_cast<size_t>(i) * kBytes);
     return p;
@@ -156,6 +157,8 @@ PinnedPool& pinned_pool() {
   static PinnedPool* pool = new PinnedPool;   // lives until the process ends
   return *pool;
 }
+
+constexpr int kMailWords = 512;   // reports in a pinned block
 
 struct vasmg_ctx {
   Hierarchy H;
@@ -204,6 +207,8 @@ struct vasmg_ctx {
   Scalars* sc = nullptr;
   Scalars* h_sc = nullptr;          // pinned host copy
   double* h_rtol = nullptr;         // pinned
+  int* mail = nullptr;              // pinned: reports of the iteration (one per column or part)
+  int* big_mail = nullptr;          // own allocation, more than kMailWords parts
   int* zero_flag = nullptr;         // device int 0 (debug entry points)
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t gA = nullptr, gB = nullptr;
@@ -225,9 +230,8 @@ struct vasmg_ctx {
   std::vector<int64_t> seg_vertex_off;   // [nseg + 1] mesh-vertex offsets of the parts
   std::vector<int64_t> seg_free_off;     // [nseg + 1] fine canonical vertex offsets
   std::vector<std::vector<int64_t>> seg_level_off;   // the same on every level
-  int *seg_ptr = nullptr, *seg_rows = nullptr, *seg_of_row = nullptr;
+  int *seg_ptr = nullptr, *seg_rows = nullptr;
   Scalars* ssc = nullptr;                // [nseg]
-  int* seg_running = nullptr;            // segments still iterating
   hipGraphExec_t sgA = nullptr, sgB = nullptr;
   mutable std::vector<std::vector<int>> order_cache;   // device numbering per level (setup)
 
@@ -301,6 +305,7 @@ struct vasmg_ctx {
         (void)hipFree(p);
     }
     pinned_pool().put(pinned);
+    if (big_mail) (void)hipHostFree(big_mail);
   }
 };
 
@@ -820,11 +825,18 @@ void upload_all(vasmg_ctx& C) {
   C.clear(C.sc, sizeof(Scalars));
   C.zero_flag = C.dalloc<int>(1);
   C.clear(C.zero_flag, sizeof(int));
-  // pinned scalars: Scalars at 0, rtol at 256, block scalars [16] at 512
-  static_assert(512 + 16 * sizeof(Scalars) <= PinnedPool::kBytes, "pinned block too small");
+  // pinned: Scalars at 0, rtol at 256, block scalars [16] at 512, reports [kMailWords] at 2048
+  static_assert(512 + 16 * sizeof(Scalars) <= 2048 && 2048 + kMailWords * sizeof(int) <= PinnedPool::kBytes,
+                "pinned block too small");
   C.pinned = pinned_pool().get();
   C.h_sc = static_cast<Scalars*>(C.pinned);
   C.h_rtol = reinterpret_cast<double*>(static_cast<char*>(C.pinned) + 256);
+  C.mail = reinterpret_cast<int*>(static_cast<char*>(C.pinned) + 2048);
+  if (C.nseg > kMailWords) {
+    HIP_CHECK(hipHostMalloc(reinterpret_cast<void**>(&C.big_mail), sizeof(int) * C.nseg,
+                            hipHostMallocCoherent));
+    C.mail = C.big_mail;
+  }
   for (auto& e : C.ev) HIP_CHECK(hipEventCreate(&e));
   HIP_CHECK(hipStreamCreateWithFlags(&C.cap_stream, hipStreamNonBlocking));
   if (C.nseg > 0) {
@@ -840,13 +852,10 @@ void upload_all(vasmg_ctx& C) {
     for (int k = 0; k < C.nseg; ++k) cnt[k + 1] += cnt[k];
     std::vector<int> rows(C.n0), fill(cnt.begin(), cnt.end() - 1);
     for (int i = 0; i < C.n0; ++i) rows[fill[of[i]]++] = i;
-    C.seg_of_row = C.upload(of);
     C.seg_ptr = C.upload(cnt);
     C.seg_rows = C.upload(rows);
     C.ssc = C.dalloc<Scalars>(C.nseg);
     C.clear(C.ssc, sizeof(Scalars) * C.nseg);
-    C.seg_running = C.dalloc<int>(1);
-    C.clear(C.seg_running, sizeof(int));
   }
   std::vector<std::vector<int>>().swap(C.order_cache);   // numbering no longer needed
 }
@@ -1457,8 +1466,18 @@ void enqueue_iter_A(vasmg_ctx& C, hipStream_t st) {
   const DevLevel& l0 = C.lev[0];
   const int* done = &C.sc->done;
   const int np = launch_spmv<double, D>(l0, C.P, C.Q, C.partial, C.n_partial, done, st);
+  if (C.n0p <= dev::kSmallFlat) {
+    const int n = static_cast<int>(C.n0p);
+    if (C.vc32)
+      hipLaunchKernelGGL((dev::k_small_xr<float>), dim3(1), dim3(1024), 0, st, n, C.sc, C.partial, np,
+                         C.P, C.Q, C.X, C.R, static_cast<float*>(C.lev[0].b), C.mail);
+    else
+      hipLaunchKernelGGL((dev::k_small_xr<double>), dim3(1), dim3(1024), 0, st, n, C.sc, C.partial, np,
+                         C.P, C.Q, C.X, C.R, static_cast<double*>(nullptr), C.mail);
+    return;
+  }
   hipLaunchKernelGGL((dev::k_finalize<dev::FIN_ALPHA>), dim3(1), dim3(1024), 0, st, C.partial, np,
-                     C.sc);
+                     C.sc, static_cast<int*>(nullptr));
   if (C.vc32)
     hipLaunchKernelGGL((dev::k_update_xr<float>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, C.n0p,
                        C.sc, C.P, C.Q, C.X, C.R, static_cast<float*>(C.lev[0].b), C.partial);
@@ -1466,46 +1485,43 @@ void enqueue_iter_A(vasmg_ctx& C, hipStream_t st) {
     hipLaunchKernelGGL((dev::k_update_xr<double>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st,
                        C.n0p, C.sc, C.P, C.Q, C.X, C.R, static_cast<double*>(nullptr), C.partial);
   hipLaunchKernelGGL((dev::k_finalize<dev::FIN_RES>), dim3(1), dim3(1024), 0, st, C.partial,
-                     kFlatGrid, C.sc);
+                     kFlatGrid, C.sc, C.mail);
+}
+
+// rho = r.z; beta; p = z + beta p
+template <typename T>
+void enqueue_direction(vasmg_ctx& C, const T* z, hipStream_t st) {
+  if (C.n0p <= dev::kSmallFlat) {
+    hipLaunchKernelGGL((dev::k_small_p<T>), dim3(1), dim3(1024), 0, st, static_cast<int>(C.n0p), C.sc, C.R,
+                       z, C.P);
+    return;
+  }
+  hipLaunchKernelGGL((dev::k_dot<T>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, C.n0p, C.R, z,
+                     C.partial, static_cast<const int*>(&C.sc->done));
+  hipLaunchKernelGGL((dev::k_finalize<dev::FIN_BETA>), dim3(1), dim3(1024), 0, st, C.partial, kFlatGrid,
+                     C.sc, static_cast<int*>(nullptr));
+  hipLaunchKernelGGL((dev::k_update_p<T>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, C.n0p, C.sc, z,
+                     C.P);
 }
 
 // z = B r; rho = r.z; beta; p = z + beta p
 template <int D>
 void enqueue_iter_B(vasmg_ctx& C, hipStream_t st) {
-  const int* done = &C.sc->done;
   const int pc = C.opt.preconditioner;
   if (pc == VASMG_PRECOND_VASMG) {
     // the host launches this graph only while the iteration has not stopped, so
     // the V-cycle kernels do not read the flag (it would head their load chains)
     enqueue_precond<D>(C, nullptr, st);
-    if (C.vc32) {
-      hipLaunchKernelGGL((dev::k_dot<float>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, C.n0p, C.R,
-                         static_cast<const float*>(C.lev[0].x), C.partial, done);
-      hipLaunchKernelGGL((dev::k_finalize<dev::FIN_BETA>), dim3(1), dim3(1024), 0, st, C.partial,
-                         kFlatGrid, C.sc);
-      hipLaunchKernelGGL((dev::k_update_p<float>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, C.n0p,
-                         C.sc, static_cast<const float*>(C.lev[0].x), C.P);
-    } else {
-      hipLaunchKernelGGL((dev::k_dot<double>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, C.n0p,
-                         C.R, static_cast<const double*>(C.lev[0].x), C.partial, done);
-      hipLaunchKernelGGL((dev::k_finalize<dev::FIN_BETA>), dim3(1), dim3(1024), 0, st, C.partial,
-                         kFlatGrid, C.sc);
-      hipLaunchKernelGGL((dev::k_update_p<double>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st,
-                         C.n0p, C.sc, static_cast<const double*>(C.lev[0].x), C.P);
-    }
+    if (C.vc32)
+      enqueue_direction(C, static_cast<const float*>(C.lev[0].x), st);
+    else
+      enqueue_direction(C, static_cast<const double*>(C.lev[0].x), st);
+  } else if (pc == VASMG_PRECOND_JACOBI) {
+    hipLaunchKernelGGL((dev::k_jacobi<D>), dim3(grid_for(C.n0, dev::kBlock)), dim3(dev::kBlock), 0, st,
+                       C.n0, C.lev[0].diag64, C.R, C.Z, static_cast<const int*>(&C.sc->done));
+    enqueue_direction(C, static_cast<const double*>(C.Z), st);
   } else {
-    const double* z = C.R;
-    if (pc == VASMG_PRECOND_JACOBI) {
-      hipLaunchKernelGGL((dev::k_jacobi<D>), dim3(grid_for(C.n0, dev::kBlock)), dim3(dev::kBlock), 0,
-                         st, C.n0, C.lev[0].diag64, C.R, C.Z, done);
-      z = C.Z;
-    }
-    hipLaunchKernelGGL((dev::k_dot<double>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, C.n0p, C.R,
-                       z, C.partial, done);
-    hipLaunchKernelGGL((dev::k_finalize<dev::FIN_BETA>), dim3(1), dim3(1024), 0, st, C.partial,
-                       kFlatGrid, C.sc);
-    hipLaunchKernelGGL((dev::k_update_p<double>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, C.n0p,
-                       C.sc, z, C.P);
+    enqueue_direction(C, static_cast<const double*>(C.R), st);
   }
 }
 
@@ -1637,43 +1653,64 @@ void ensure_graphs(vasmg_ctx& C) {
 }
 
 // -------------------------------------------------------------------------
+// Reports of the iteration (dev::report): pinned words that the host polls, so the
+// next graph is launched as soon as the stopping test is known. The stream's work
+// up to here has otherwise no effect that the host reads.
+// -------------------------------------------------------------------------
+void clear_reports(int* mail, int n) {
+  for (int k = 0; k < n; ++k) __atomic_store_n(mail + k, -1, __ATOMIC_RELAXED);
+}
+
+// Waits until the n words report iteration `it` or a stop; true if all have
+// stopped. Polls for up to 2 ms, then waits for the stream (which also returns a
+// launch's error).
+bool wait_reports(const int* mail, int n, int it, hipStream_t st) {
+  auto reported = [&](int v) { return v >= 0 && ((v & 1) || v >= 2 * it); };
+  const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+  bool polling = true, all = true;
+  for (int k = 0; k < n; ++k) {
+    int v = __atomic_load_n(mail + k, __ATOMIC_RELAXED);
+    while (!reported(v) && polling) {
+      __builtin_ia32_pause();
+      v = __atomic_load_n(mail + k, __ATOMIC_RELAXED);
+      if (!reported(v) && std::chrono::steady_clock::now() > end) {
+        HIP_CHECK(hipStreamSynchronize(st));
+        polling = false;
+        v = __atomic_load_n(mail + k, __ATOMIC_RELAXED);
+      }
+    }
+    all = all && v >= 0 && (v & 1);
+  }
+  return all;
+}
+
+// -------------------------------------------------------------------------
 // Packed problems: the shared SpMV and V-cycle, per-segment scalars
 // -------------------------------------------------------------------------
-// q = A p; alpha_s; x, r updates; ||r||_s and the stopping test; running count
+// q = A p; alpha_s; x, r updates; ||r||_s, the stopping test and the report
 template <int D>
 void enqueue_packed_A(vasmg_ctx& C, hipStream_t st) {
+  constexpr int DP = dev::Pad<D>::value;
   launch_spmv<double, D>(C.lev[0], C.P, C.Q, nullptr, 0, nullptr, st);
-  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_ALPHA, false, double>), dim3(C.nseg), dim3(dev::kBlock), 0,
-                     st, C.seg_ptr, C.seg_rows, C.DP, C.P, C.Q, C.ssc);
   if (C.vc32)
-    hipLaunchKernelGGL((dev::k_seg_update_xr<float>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, C.n0p,
-                       C.DP, C.seg_of_row, C.ssc, C.P, C.Q, C.X, C.R, static_cast<float*>(C.lev[0].b));
+    hipLaunchKernelGGL((dev::k_seg_xr<float, DP>), dim3(C.nseg), dim3(dev::kSegBlock), 0, st, C.seg_ptr,
+                       C.seg_rows, C.ssc, C.P, C.Q, C.X, C.R, static_cast<float*>(C.lev[0].b), C.mail);
   else
-    hipLaunchKernelGGL((dev::k_seg_update_xr<double>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, C.n0p,
-                       C.DP, C.seg_of_row, C.ssc, C.P, C.Q, C.X, C.R, static_cast<double*>(nullptr));
-  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_RES, false, double>), dim3(C.nseg), dim3(dev::kBlock), 0,
-                     st, C.seg_ptr, C.seg_rows, C.DP, C.R, C.R, C.ssc);
-  hipLaunchKernelGGL(dev::k_seg_running, dim3(1), dim3(dev::kBlock), 0, st, C.nseg, C.ssc,
-                     C.seg_running);
+    hipLaunchKernelGGL((dev::k_seg_xr<double, DP>), dim3(C.nseg), dim3(dev::kSegBlock), 0, st, C.seg_ptr,
+                       C.seg_rows, C.ssc, C.P, C.Q, C.X, C.R, static_cast<double*>(nullptr), C.mail);
 }
 
 // z = B r (the whole packed V-cycle); rho_s, beta_s; p = z + beta_s p
 template <int D>
 void enqueue_packed_B(vasmg_ctx& C, hipStream_t st) {
+  constexpr int DP = dev::Pad<D>::value;
   enqueue_precond<D>(C, nullptr, st);
-  if (C.vc32) {
-    const float* z = static_cast<const float*>(C.lev[0].x);
-    hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_BETA, false, float>), dim3(C.nseg), dim3(dev::kBlock), 0,
-                       st, C.seg_ptr, C.seg_rows, C.DP, C.R, z, C.ssc);
-    hipLaunchKernelGGL((dev::k_seg_update_p<float>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, C.n0p,
-                       C.DP, C.seg_of_row, C.ssc, z, C.P);
-  } else {
-    const double* z = static_cast<const double*>(C.lev[0].x);
-    hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_BETA, false, double>), dim3(C.nseg), dim3(dev::kBlock),
-                       0, st, C.seg_ptr, C.seg_rows, C.DP, C.R, z, C.ssc);
-    hipLaunchKernelGGL((dev::k_seg_update_p<double>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, C.n0p,
-                       C.DP, C.seg_of_row, C.ssc, z, C.P);
-  }
+  if (C.vc32)
+    hipLaunchKernelGGL((dev::k_seg_p<float, DP>), dim3(C.nseg), dim3(dev::kSegBlock), 0, st, C.seg_ptr,
+                       C.seg_rows, C.ssc, C.R, static_cast<const float*>(C.lev[0].x), C.P);
+  else
+    hipLaunchKernelGGL((dev::k_seg_p<double, DP>), dim3(C.nseg), dim3(dev::kSegBlock), 0, st, C.seg_ptr,
+                       C.seg_rows, C.ssc, C.R, static_cast<const double*>(C.lev[0].x), C.P);
 }
 
 template <int D>
@@ -1695,10 +1732,11 @@ int solve_packed(vasmg_ctx& C, const double* d_rhs, double* d_x, double rtol, hi
   hipLaunchKernelGGL((dev::k_gather_user<double, double, D>), dim3(grid_for(n0, dev::kBlock)),
                      dim3(dev::kBlock), 0, st, n0, C.user_map, d_rhs, C.F,
                      static_cast<const uint8_t*>(C.lev[0].fixed));
-  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_NORMF, false, double>), dim3(nseg), dim3(dev::kBlock), 0, st,
+  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_NORMF, false>), dim3(nseg), dim3(dev::kSegBlock), 0, st,
                      C.seg_ptr, C.seg_rows, C.DP, C.F, C.F, C.ssc);
+  clear_reports(C.mail, nseg);
   hipLaunchKernelGGL(dev::k_seg_start, dim3(grid_for(nseg, dev::kBlock)), dim3(dev::kBlock), 0, st, nseg,
-                     C.ssc, rtol);
+                     C.ssc, rtol, C.mail);
   launch_fill<double>(C.X, n0p, 0.0, st);
   launch_fill<double>(C.P, n0p, 0.0, st);
   hipLaunchKernelGGL((dev::k_convert<double, double>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, n0p, C.F,
@@ -1706,24 +1744,19 @@ int solve_packed(vasmg_ctx& C, const double* d_rhs, double* d_x, double rtol, hi
   if (C.vc32)
     hipLaunchKernelGGL((dev::k_convert<double, float>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st, n0p,
                        C.R, static_cast<float*>(C.lev[0].b));
-  hipLaunchKernelGGL(dev::k_seg_running, dim3(1), dim3(dev::kBlock), 0, st, nseg, C.ssc, C.seg_running);
-  int running = 0;
-  HIP_CHECK(hipMemcpyAsync(&running, C.seg_running, sizeof(int), hipMemcpyDeviceToHost, st));
-  HIP_CHECK(hipStreamSynchronize(st));
-  if (running > 0) {
+  HIP_CHECK(hipGetLastError());
+  if (!wait_reports(C.mail, nseg, 0, st)) {
     // Algorithm 2 initialisation for every segment: z = B r, p = z, rho = r^T z
     HIP_CHECK(hipGraphLaunch(C.sgB, st));
     for (int k = 0; k < C.opt.max_iters; ++k) {
       HIP_CHECK(hipGraphLaunch(C.sgA, st));
-      HIP_CHECK(hipMemcpyAsync(&running, C.seg_running, sizeof(int), hipMemcpyDeviceToHost, st));
-      HIP_CHECK(hipStreamSynchronize(st));
-      if (running == 0) break;
+      if (wait_reports(C.mail, nseg, k + 1, st)) break;
       HIP_CHECK(hipGraphLaunch(C.sgB, st));
     }
   }
   // true residuals, scatter
   launch_spmv<double, D>(C.lev[0], C.X, C.Q, nullptr, 0, nullptr, st);
-  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_TRUE, true, double>), dim3(nseg), dim3(dev::kBlock), 0, st,
+  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_TRUE, true>), dim3(nseg), dim3(dev::kSegBlock), 0, st,
                      C.seg_ptr, C.seg_rows, C.DP, C.F, C.Q, C.ssc);
   launch_fill<double>(d_x, C.H.n_mesh_vertices * D, 0.0, st);
   hipLaunchKernelGGL((dev::k_scatter_user<double, double, D>), dim3(grid_for(n0, dev::kBlock)),
@@ -1773,7 +1806,7 @@ int solve_one(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d_x
   hipLaunchKernelGGL((dev::k_dot<double>), dim3(gflat), dim3(dev::kBlock), 0, st, n0p, C.F, C.F,
                      C.partial, static_cast<const int*>(nullptr));
   hipLaunchKernelGGL((dev::k_finalize<dev::FIN_NORMF>), dim3(1), dim3(1024), 0, st, C.partial, gflat,
-                     C.sc);
+                     C.sc, static_cast<int*>(nullptr));
   *C.h_rtol = rtol;
   HIP_CHECK(hipMemcpyAsync(&C.sc->rtol, C.h_rtol, sizeof(double), hipMemcpyHostToDevice, st));
   if (d_x0) {
@@ -1784,7 +1817,7 @@ int solve_one(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d_x
     hipLaunchKernelGGL(dev::k_sub_norm, dim3(gflat), dim3(dev::kBlock), 0, st, n0p, C.F, C.Q, C.R,
                        C.partial);
     hipLaunchKernelGGL((dev::k_finalize<dev::FIN_TRUE>), dim3(1), dim3(1024), 0, st, C.partial, gflat,
-                       C.sc);
+                       C.sc, static_cast<int*>(nullptr));
   } else {
     launch_fill<double>(C.X, n0p, 0.0, st);
     hipLaunchKernelGGL((dev::k_convert<double, double>), dim3(gflat), dim3(dev::kBlock), 0, st, n0p,
@@ -1817,6 +1850,7 @@ int solve_one(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d_x
     HIP_CHECK(hipGraphLaunch(C.gB, st));
     if (prof) HIP_CHECK(hipEventRecord(C.ev[3], st));
     int k = 0;
+    clear_reports(C.mail, 1);
     while (k < C.opt.max_iters) {
       if (prof) {
         HIP_CHECK(hipEventSynchronize(C.ev[3]));
@@ -1826,16 +1860,16 @@ int solve_one(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d_x
         HIP_CHECK(hipEventRecord(C.ev[2], st));
       }
       HIP_CHECK(hipGraphLaunch(C.gA, st));
-      HIP_CHECK(hipMemcpyAsync(C.h_sc, C.sc, sizeof(Scalars), hipMemcpyDeviceToHost, st));
       if (prof) HIP_CHECK(hipEventRecord(C.ev[3], st));
-      HIP_CHECK(hipStreamSynchronize(st));
+      const bool stopped = wait_reports(C.mail, 1, k + 1, st);
       if (prof) {
+        HIP_CHECK(hipEventSynchronize(C.ev[3]));
         float ms = 0.f;
         HIP_CHECK(hipEventElapsedTime(&ms, C.ev[2], C.ev[3]));
         t_a += ms;
       }
       ++k;
-      if (C.h_sc->done) break;
+      if (stopped) break;
       if (prof) HIP_CHECK(hipEventRecord(C.ev[2], st));
       HIP_CHECK(hipGraphLaunch(C.gB, st));
       if (prof) HIP_CHECK(hipEventRecord(C.ev[3], st));
@@ -1846,7 +1880,7 @@ int solve_one(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d_x
   hipLaunchKernelGGL(dev::k_sub_norm, dim3(gflat), dim3(dev::kBlock), 0, st, n0p, C.F, C.Q,
                      static_cast<double*>(nullptr), C.partial);
   hipLaunchKernelGGL((dev::k_finalize<dev::FIN_TRUE>), dim3(1), dim3(1024), 0, st, C.partial, gflat,
-                     C.sc);
+                     C.sc, static_cast<int*>(nullptr));
   launch_fill<double>(d_x, C.H.n_mesh_vertices * D, 0.0, st);
   hipLaunchKernelGGL((dev::k_scatter_user<double, double, D>), dim3(grid_for(n0, dev::kBlock)),
                      dim3(dev::kBlock), 0, st, n0, C.user_map, C.X, d_x);
@@ -2125,7 +2159,7 @@ void enqueue_iter_A_mc(vasmg_ctx& C, hipStream_t st) {
   const int64_t n = C.n0p * K;
   const int np = launch_spmv_mc<D, K>(C, C.kP, C.kQ, C.kpartial, st);
   hipLaunchKernelGGL((dev::k_finalize_mc<dev::FIN_ALPHA, K>), dim3(K), dim3(dev::kBlock), 0, st,
-                     C.kpartial, np, C.ksc);
+                     C.kpartial, np, C.ksc, static_cast<int*>(nullptr));
   if (C.vc32)
     hipLaunchKernelGGL((dev::k_update_xr_mc<float, K, DP>), dim3(kFlatGrid), dim3(dev::kBlock), 0,
                        st, n, C.ksc, C.kP, C.kQ, C.kX, C.kR, static_cast<float*>(C.kb[0]),
@@ -2135,7 +2169,7 @@ void enqueue_iter_A_mc(vasmg_ctx& C, hipStream_t st) {
                        st, n, C.ksc, C.kP, C.kQ, C.kX, C.kR, static_cast<double*>(nullptr),
                        C.kpartial);
   hipLaunchKernelGGL((dev::k_finalize_mc<dev::FIN_RES, K>), dim3(K), dim3(dev::kBlock), 0, st,
-                     C.kpartial, kFlatGrid, C.ksc);
+                     C.kpartial, kFlatGrid, C.ksc, C.mail);
 }
 
 // z = B r, rho = r.z, beta, p = z + beta p (per column)
@@ -2153,7 +2187,7 @@ void enqueue_iter_B_mc(vasmg_ctx& C, hipStream_t st) {
                        n, C.kR, static_cast<const double*>(C.kx[0]), C.kpartial);
   }
   hipLaunchKernelGGL((dev::k_finalize_mc<dev::FIN_BETA, K>), dim3(K), dim3(dev::kBlock), 0, st,
-                     C.kpartial, kFlatGrid, C.ksc);
+                     C.kpartial, kFlatGrid, C.ksc, static_cast<int*>(nullptr));
   if (C.vc32)
     hipLaunchKernelGGL((dev::k_update_p_mc<float, K, DP>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st,
                        n, C.ksc, static_cast<const float*>(C.kx[0]), C.kP);
@@ -2186,7 +2220,7 @@ int solve_block(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d
   hipLaunchKernelGGL((dev::k_dot_mc<K, DP, double>), dim3(gflat), dim3(dev::kBlock), 0, st, n, C.kF,
                      C.kF, C.kpartial);
   hipLaunchKernelGGL((dev::k_finalize_mc<dev::FIN_NORMF, K>), dim3(K), dim3(dev::kBlock), 0, st,
-                     C.kpartial, gflat, C.ksc);
+                     C.kpartial, gflat, C.ksc, static_cast<int*>(nullptr));
   if (d_x0) {
     hipLaunchKernelGGL((dev::k_gather_user_mc<D, K>), gk, dim3(dev::kBlock), 0, st, n0, C.user_map,
                        d_x0, nv, c0, nc, C.kX, static_cast<const uint8_t*>(C.lev[0].fixed));
@@ -2196,7 +2230,7 @@ int solve_block(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d
     hipLaunchKernelGGL((dev::k_sub_norm_mc<K, DP>), dim3(gflat), dim3(dev::kBlock), 0, st, n, C.kF,
                        C.kQ, C.kR, C.kpartial);
     hipLaunchKernelGGL((dev::k_finalize_mc<dev::FIN_TRUE, K>), dim3(K), dim3(dev::kBlock), 0, st,
-                       C.kpartial, gflat, C.ksc);
+                       C.kpartial, gflat, C.ksc, static_cast<int*>(nullptr));
   } else {
     launch_fill<double>(C.kX, n, 0.0, st);
     hipLaunchKernelGGL((dev::k_convert<double, double>), dim3(gflat), dim3(dev::kBlock), 0, st, n,
@@ -2218,13 +2252,10 @@ int solve_block(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d
   }
   if (!all_done) {
     HIP_CHECK(hipGraphLaunch(C.kgB, st));
+    clear_reports(C.mail, K);
     for (int it = 0; it < C.opt.max_iters; ++it) {
       HIP_CHECK(hipGraphLaunch(C.kgA, st));
-      HIP_CHECK(hipMemcpyAsync(C.kh_sc, C.ksc, sizeof(Scalars) * K, hipMemcpyDeviceToHost, st));
-      HIP_CHECK(hipStreamSynchronize(st));
-      all_done = true;
-      for (int k = 0; k < K; ++k) all_done = all_done && C.kh_sc[k].done;
-      if (all_done) break;
+      if (wait_reports(C.mail, K, it + 1, st)) break;
       HIP_CHECK(hipGraphLaunch(C.kgB, st));
     }
   }
@@ -2233,7 +2264,7 @@ int solve_block(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d
   hipLaunchKernelGGL((dev::k_sub_norm_mc<K, DP>), dim3(gflat), dim3(dev::kBlock), 0, st, n, C.kF,
                      C.kQ, static_cast<double*>(nullptr), C.kpartial);
   hipLaunchKernelGGL((dev::k_finalize_mc<dev::FIN_TRUE, K>), dim3(K), dim3(dev::kBlock), 0, st,
-                     C.kpartial, gflat, C.ksc);
+                     C.kpartial, gflat, C.ksc, static_cast<int*>(nullptr));
   launch_fill<double>(d_x + static_cast<int64_t>(c0) * nv * D, static_cast<int64_t>(nc) * nv * D, 0.0,
                       st);                                       // fixed DOFs
   hipLaunchKernelGGL((dev::k_scatter_user_mc<D, K>), gk, dim3(dev::kBlock), 0, st, n0, C.user_map,

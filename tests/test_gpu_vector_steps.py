@@ -1,0 +1,90 @@
+"""The vector steps of an iteration on both sides of the size up to which one
+workgroup takes them (8,192 entries of a solve's padded vectors), in packs of
+unequal parts, and a pack of more parts than a handle's report words."""
+import numpy as np
+import pytest
+
+from oracle import Oracle
+from workloads import small2d, small3d
+
+torch = pytest.importorskip("torch")
+from paper_2505_09064_amd import vasmg as V  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+SMALL_ENTRIES = 8192
+
+SIZES = {
+    "2d, last small": (lambda: small2d(66, seed=1), True),
+    "2d, first general": (lambda: small2d(67, seed=1), False),
+    "3d, small": (lambda: small3d(13, seed=2), True),
+    "3d, general": (lambda: small3d(14, seed=2), False),
+}
+
+
+def _rel(x, y):
+    return np.linalg.norm(x - y) / np.linalg.norm(y)
+
+
+@pytest.mark.parametrize("name", list(SIZES))
+def test_solve_around_the_small_size(name):
+    """FP64 within 1e-8 of the oracle and +-1 iteration; the FP32 cycle, a warm
+    start and point Jacobi are solved to 1e-10, which at a condition number below
+    1e5 (about h^-2 times the material's) is 1e-5 of the solution."""
+    make, small = SIZES[name]
+    m = make()
+    f = m.rhs[0]
+    xo, io = Oracle(m.coords, m.elems, m.E, m.nu, m.fixed).solve(f, 1e-6)
+    xt, _ = Oracle(m.coords, m.elems, m.E, m.nu, m.fixed).solve(f, 1e-11)
+    with V.Solver.from_mesh(m, autotune=0) as s:
+        rows = s.hierarchy_info()[1] // m.dim
+        assert (rows * (2 if m.dim == 2 else 4) <= SMALL_ENTRIES) == small
+        x, info = s.solve(f, 1e-6)
+        assert abs(info["iterations"] - io["iterations"]) <= 1 and _rel(x, xo) <= 1e-8
+        xz, iz = s.solve(np.zeros_like(f), 1e-6)
+        assert iz["iterations"] == 0 and np.all(xz == 0.0)
+        xw, iw = s.solve(f, 1e-10, x0=0.5 * x)
+        assert iw["converged"] == 1 and iw["rel_res_true"] < 1e-9 and _rel(xw, xt) <= 1e-5
+        x2, i2 = s.solve(f, 1e-6)
+        assert np.array_equal(x2, x) and i2["iterations"] == info["iterations"]
+    for kw in (dict(precision=V.FP32_PRECOND), dict(preconditioner=V.PRECOND_JACOBI)):
+        with V.Solver.from_mesh(m, autotune=0, max_iters=3000, **kw) as s:
+            x, info = s.solve(f, 1e-10)
+            assert info["converged"] == 1 and info["rel_res_true"] < 1e-9 and _rel(x, xt) <= 1e-5, kw
+
+
+@pytest.mark.parametrize("prec", [V.FP64, V.FP32_PRECOND])
+def test_pack_of_unequal_parts(prec):
+    """Each part as alone: +-1 iteration, FP64 1e-10, FP32 cycle 1e-5."""
+    meshes = [small2d(2, seed=1, fix="x0"), small2d(67, seed=2), small2d(17, seed=3, fix="symmetry")]
+    fs = [m.rhs[0] for m in meshes]
+    pk = V.PackedSolver([V.Solver.from_mesh(m, host_only=1, precision=prec) for m in meshes])
+    X, infos = pk.solve_packed(fs, 1e-6)
+    for m, f, x, info in zip(meshes, fs, X, infos):
+        with V.Solver.from_mesh(m, precision=prec, autotune=0) as s:
+            xa, ia = s.solve(f, 1e-6)
+        assert info["converged"] == 1 and abs(info["iterations"] - ia["iterations"]) <= 1
+        assert _rel(x, xa) <= (1e-10 if prec == V.FP64 else 1e-5)
+    pk.free()
+
+
+def test_pack_of_many_parts():
+    """520 parts of three meshes, scaled loads, every seventh without a load."""
+    # (the smallest meshes: a pack's coarsest levels hold 4,096 DOFs together)
+    kinds = [small2d(2, seed=1, fix="x0"), small2d(2, seed=5, fix="x0", nu=0.4), small2d(2, seed=1, fix="symmetry")]
+    alone = []
+    for m in kinds:
+        with V.Solver.from_mesh(m, autotune=0) as s:
+            alone.append(s.solve(m.rhs[0], 1e-6))
+    n = 520
+    pk = V.PackedSolver([V.Solver.from_mesh(kinds[i % 3], host_only=1) for i in range(n)])
+    scale = [0.0 if i % 7 == 0 else 2.0 ** (i % 5) for i in range(n)]
+    X, infos = pk.solve_packed([c * kinds[i % 3].rhs[0] for i, c in enumerate(scale)], 1e-6)
+    for i, c in enumerate(scale):
+        xa, ia = alone[i % 3]
+        if c == 0.0:
+            assert infos[i]["iterations"] == 0 and np.all(X[i] == 0.0)
+        else:
+            assert abs(infos[i]["iterations"] - ia["iterations"]) <= 1
+            assert _rel(X[i], c * xa) <= 1e-10
+    pk.free()
