@@ -578,6 +578,18 @@ struct CellShape {
   static constexpr int NU = NV * D;
 };
 
+// A cell's record: first device row, rows, then the NV + 1 row ranges' ends in L and
+// in U (in blocks; rows beyond the cell's last are empty). One cache line and one
+// load, where cell -> rows -> row ranges were two dependent ones: a launch is a
+// chain of dependent loads of about 6 us on most levels. Solve of a graded 401 x 401
+// mesh, FP32 cycle, 193.1 -> 184.0 ms; of a 65^3 mesh 16.2 -> 15.8 ms.
+template <int D>
+struct CellRec {
+  static constexpr int NV = CellShape<D>::NV;
+  static constexpr int L = 2, U = L + NV + 1, ints = D == 2 ? 16 : 32;
+  static_assert(U + NV + 1 <= ints, "record too small");
+};
+
 // Cells per workgroup: one per workgroup when a cell's NV * GR lanes fill a
 // wavefront or more (its wavefront 0 runs the in-cell sweep); otherwise as many
 // as share one wavefront (2D cells with 4 or 8 lanes per row), each with its own
@@ -692,9 +704,9 @@ struct RowWalk {
 // What the sweeps and the residual of a cell have in common: the off-cell products
 // of its rows (their sums end in LDS) and the cell matrix (staged in LDS);
 // wavefront 0 then owns the cell's unknowns, one per lane. A launch of a small
-// level is one pass through a chain of dependent loads (cell -> row ranges ->
+// level is one pass through a chain of dependent loads (the cell's record ->
 // columns -> neighbours), so nothing waits that need not: both parts' ranges are
-// fetched first and together, then columns and matrix values; the cell matrix goes
+// in the record, then come columns and matrix values; the cell matrix goes
 // to LDS in 16-byte pieces by all threads.
 //
 // One cell per workgroup (3D): the rows of a cell are one contiguous run of steps
@@ -714,6 +726,7 @@ template <typename T, int D, int GR>
 struct CellSums {
   static constexpr int NV = CellShape<D>::NV, NU = CellShape<D>::NU;
   static constexpr int CPW = CellPack<D, GR>::CPW, CT = CellPack<D, GR>::CT;
+  using Rec = CellRec<D>;
   static constexpr int PC = NU * NU * static_cast<int>(sizeof(T)) / 16;   // 16-byte pieces of M
   static constexpr int PR = (PC + CT - 1) / CT;
   static constexpr int NW = CPW == 1 ? CT / 64 : 1;   // partial sums of a row
@@ -730,6 +743,22 @@ struct CellSums {
     __device__ __forceinline__ T up(int slot, int k, int a) const { return total(slot, NV + k, a); }
   };
 
+  // The cell's record: an int per lane where the workgroup has one cell, else only
+  // its first two.
+  struct Head {
+    int rec, v0, m;
+  };
+  static __device__ __forceinline__ Head head(const int* __restrict__ rec, int c, bool live) {
+    const int* r = rec + static_cast<int64_t>(c) * Rec::ints;
+    if constexpr (CPW == 1) {
+      const int v = r[threadIdx.x & (Rec::ints - 1)];
+      return {v, __builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 1)};
+    } else {
+      const int2 h = *reinterpret_cast<const int2*>(r);
+      return {0, h.x, live ? h.y : 0};
+    }
+  }
+
   // One step of the flat walk over both parts of a cell.
   template <bool LO, bool UP>
   struct Flat {
@@ -740,20 +769,14 @@ struct CellSums {
     bool in;
     typename CellStep<T>::Cols j;
     StepVals<T> m[D * D];
-    // one vector load for both parts' row ranges, read into scalars lane by lane
-    // (as 18 scalar loads per wavefront they missed the scalar cache: the backward
-    // launch of 1,331 cells took 56 us instead of 15)
-    int pv;
-    __device__ __forceinline__ void load_ranges(const Part<T>& L, const Part<T>& U, int v0, int m_) {
-      const int lane = threadIdx.x & 63;
-      const int* ptr = !LO || (UP && lane >= 16) ? U.ptr : L.ptr;
-      pv = ptr[v0 + min(lane & 15, m_)];
-    }
-    __device__ __forceinline__ void ranges() {
+    // rec: the cell's record, an int per lane, read into scalars lane by lane (as
+    // 18 scalar loads per wavefront the ranges missed the scalar cache: the
+    // backward launch of 1,331 cells took 56 us instead of 15)
+    __device__ __forceinline__ void ranges(int rec) {
       static_for<NV + 1>([&](auto ri) {
         constexpr int r = decltype(ri)::value;
-        pl[r] = LO ? __builtin_amdgcn_readlane(pv, r) / B : 0;
-        pu[r] = UP ? __builtin_amdgcn_readlane(pv, LO ? 16 + r : r) / B : 0;
+        pl[r] = LO ? __builtin_amdgcn_readlane(rec, Rec::L + r) / B : 0;
+        pu[r] = UP ? __builtin_amdgcn_readlane(rec, Rec::U + r) / B : 0;
       });
       nl = pl[NV] - pl[0];
       total = nl + pu[NV] - pu[0];
@@ -820,24 +843,24 @@ struct CellSums {
   // caller's, issued after the row ranges'. Ends in a barrier. E, F (colour-block
   // levels): taken with L and U.
   template <bool LO, bool UP, class Own>
-  static __device__ __forceinline__ void run(Lds& sh, int slot, int t, int c, int v0, int m,
-                                             const Part<T>& L, const Part<T>& U, const Part<T>* E,
+  static __device__ __forceinline__ void run(Lds& sh, int slot, int t, int c, const Head& hd,
+                                             const int* __restrict__ rec, const Part<T>& L, const Part<T>& U, const Part<T>* E,
                                              const Part<T>* F, const T* __restrict__ cellM,
                                              const T* __restrict__ x, Own&& own) {
+    const int v0 = hd.v0, m = hd.m;
     Vec16 piece[PR];
     const Vec16* Mc = reinterpret_cast<const Vec16*>(cellM + static_cast<int64_t>(c) * NU * NU);
     if constexpr (CPW == 1) {
       const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
       T(*sum)[D] = sh.sum[0][w];
       Flat<LO, UP> fl;
-      fl.load_ranges(L, U, v0, m);
       static_for<PR>([&](auto ri) {
         constexpr int r = decltype(ri)::value;
         piece[r] = Mc[min(t + r * CT, PC - 1)];
       });
       own();
       __builtin_amdgcn_sched_barrier(0);
-      fl.ranges();
+      fl.ranges(hd.rec);
       if (lane < 2 * NV) {   // each wavefront its own sums
 #pragma unroll
         for (int a = 0; a < D; ++a) sum[lane][a] = T(0);
@@ -881,10 +904,10 @@ struct CellSums {
     } else {
       const int g = t / GR, gl = t % GR;
       const bool has = g < m;
-      const int i = has ? v0 + g : v0;
+      const int* rg = rec + static_cast<int64_t>(c) * Rec::ints + g;
       int lb = 0, le = 0, ub = 0, ue = 0;
-      if constexpr (LO) { lb = L.ptr[i]; le = L.ptr[i + 1]; }
-      if constexpr (UP) { ub = U.ptr[i]; ue = U.ptr[i + 1]; }
+      if constexpr (LO) { lb = rg[Rec::L]; le = rg[Rec::L + 1]; }
+      if constexpr (UP) { ub = rg[Rec::U]; ue = rg[Rec::U + 1]; }
       static_for<PR>([&](auto ri) {
         constexpr int r = decltype(ri)::value;
         piece[r] = Mc[min(t + r * CT, PC - 1)];
@@ -931,7 +954,7 @@ struct CellSums {
 
 template <typename T, int D, int GR, int MODE>
 __global__ __launch_bounds__((CellPack<D, GR>::threads)) void k_gs_cell(
-    int cell0, int ncell, const int* __restrict__ cell_ptr, Part<T> L, Part<T> U,
+    int cell0, int ncell, const int* __restrict__ rec, Part<T> L, Part<T> U,
     const T* __restrict__ cellM, const T* __restrict__ b, T* x, T* __restrict__ s_save) {
   constexpr int DP = Pad<D>::value;
   using Sums = CellSums<T, D, GR>;
@@ -942,12 +965,13 @@ __global__ __launch_bounds__((CellPack<D, GR>::threads)) void k_gs_cell(
   const int ci = xcd_block() * CPW + slot;
   const bool live = CPW == 1 || ci < ncell;   // the last workgroup may hold fewer cells
   const int c = cell0 + (live ? ci : 0);
-  const int v0 = cell_ptr[c], m = live ? cell_ptr[c + 1] - v0 : 0, n = m * D;
+  const typename Sums::Head hd = Sums::head(rec, c, live);
+  const int v0 = hd.v0, m = hd.m, n = m * D;
   const bool own = t < n;
   const int k = own ? t / D : 0, a = own ? t % D : 0;
   const int64_t xi = static_cast<int64_t>(v0 + k) * DP + a;
   T bt = T(0), xc = T(0);
-  Sums::template run<true, MODE != 0>(sh, slot, t, c, v0, m, L, U, nullptr, nullptr, cellM, x, [&] {
+  Sums::template run<true, MODE != 0>(sh, slot, t, c, hd, rec, L, U, nullptr, nullptr, cellM, x, [&] {
     bt = b[xi];
     if (MODE != 0) xc = x[xi];
   });
@@ -1215,7 +1239,7 @@ __global__ __launch_bounds__(BlockShape<D>::threads, 4) void k_gs_block(
 //   BLK: a colour-block level, E (with L) and F (with U) taken as well.
 template <typename T, int D, int GR, int KIND, bool BLK>
 __global__ __launch_bounds__((CellPack<D, GR>::threads)) void k_cell_apply(
-    int ncell, const int* __restrict__ cell_ptr, Part<T> L, Part<T> U, Part<T> E, Part<T> F,
+    int ncell, const int* __restrict__ rec, Part<T> L, Part<T> U, Part<T> E, Part<T> F,
     const T* __restrict__ cellM, const T* __restrict__ base, const T* __restrict__ x,
     T* __restrict__ out) {
   constexpr int DP = Pad<D>::value;
@@ -1227,12 +1251,13 @@ __global__ __launch_bounds__((CellPack<D, GR>::threads)) void k_cell_apply(
   const int ci = xcd_block() * CPW + slot;
   const bool live = CPW == 1 || ci < ncell;
   const int c = live ? ci : 0;
-  const int v0 = cell_ptr[c], m = live ? cell_ptr[c + 1] - v0 : 0, n = m * D;
+  const typename Sums::Head hd = Sums::head(rec, c, live);
+  const int v0 = hd.v0, m = hd.m, n = m * D;
   const bool own = t < n;
   const int k = own ? t / D : 0, a = own ? t % D : 0;
   const int64_t xi = static_cast<int64_t>(v0 + k) * DP + a;
   T xt = T(0), bt = T(0);
-  Sums::template run<KIND != 0, true>(sh, slot, t, c, v0, m, L, U, BLK ? &E : nullptr,
+  Sums::template run<KIND != 0, true>(sh, slot, t, c, hd, rec, L, U, BLK ? &E : nullptr,
                                       BLK ? &F : nullptr, cellM, x, [&] {
                                         xt = x[xi];
                                         if (KIND != 2) bt = base[xi];

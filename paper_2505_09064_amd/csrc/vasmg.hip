@@ -75,6 +75,7 @@ struct DevLevel {
   bool cells = false;              // coarse lattice level: Gauss-Seidel over cells
   int ncells = 0;
   int* cell_ptr = nullptr;         // cell levels: first device row of each cell
+  int* cell_rec = nullptr;         // cell levels: each cell's record (CellRec)
   // colour-block levels (cells grouped into blocks of several cells, a colour
   // per block): color_ptr then counts blocks, block_ptr gives each block's
   // first cell, and the off-cell blocks inside a row's colour block form the
@@ -558,6 +559,8 @@ std::vector<int> padded_ptr(const std::vector<int>& cnt, bool cells) {
   return ptr;
 }
 
+int cell_rec_ints(int d) { return d == 2 ? dev::CellRec<2>::ints : dev::CellRec<3>::ints; }
+
 // Device memory that lives for one level's layout: stream-ordered on the upload
 // stream when there is one (a server slot's), else plain allocations.
 struct TempDev {
@@ -689,7 +692,22 @@ void upload_level_device(vasmg_ctx& C, int l, bool need32, bool need64, const st
     dl.Ecol = C.dalloc<int>(nE);
     dl.Fcol = C.dalloc<int>(nF);
   }
-  if (dl.cells) dl.cell_ptr = C.upload(cell_ptr);
+  if (dl.cells) {
+    dl.cell_ptr = C.upload(cell_ptr);
+    const int NV = 1 << d, ints = cell_rec_ints(d);
+    std::vector<int> rec(static_cast<size_t>(dl.ncells) * ints, 0);
+    for (int c = 0; c < dl.ncells; ++c) {
+      const int v0 = cell_ptr[c], m = cell_ptr[c + 1] - v0;
+      int* r = rec.data() + static_cast<size_t>(c) * ints;
+      r[0] = v0;
+      r[1] = m;
+      for (int k = 0; k <= NV; ++k) {
+        r[2 + k] = Lptr[v0 + std::min(k, m)];
+        r[3 + NV + k] = Uptr[v0 + std::min(k, m)];
+      }
+    }
+    dl.cell_rec = C.upload(rec);
+  }
   const int64_t m_len = dl.cells ? static_cast<int64_t>(dl.ncells) * NU * NU : static_cast<int64_t>(n) * dd;
   if (need64) {
     dl.Lval64 = C.dalloc<double>(std::max<int64_t>(nL * dd, dev::kQuad));
@@ -1064,13 +1082,13 @@ void launch_gs_cells(const DevLevel& lv, int c, int mode, const T* b, T* x, T* s
     using Pack = dev::CellPack<D, GR>;
     const dim3 blk(Pack::threads), grid((nc + Pack::CPW - 1) / Pack::CPW);
     if (mode == 0)
-      hipLaunchKernelGGL((dev::k_gs_cell<T, D, GR, 0>), grid, blk, 0, st, c0, nc, lv.cell_ptr,
+      hipLaunchKernelGGL((dev::k_gs_cell<T, D, GR, 0>), grid, blk, 0, st, c0, nc, lv.cell_rec,
                          Lp, Up, M, b, x, s_save);
     else if (mode == 1)
-      hipLaunchKernelGGL((dev::k_gs_cell<T, D, GR, 1>), grid, blk, 0, st, c0, nc, lv.cell_ptr,
+      hipLaunchKernelGGL((dev::k_gs_cell<T, D, GR, 1>), grid, blk, 0, st, c0, nc, lv.cell_rec,
                          Lp, Up, M, b, x, s_save);
     else
-      hipLaunchKernelGGL((dev::k_gs_cell<T, D, GR, 2>), grid, blk, 0, st, c0, nc, lv.cell_ptr,
+      hipLaunchKernelGGL((dev::k_gs_cell<T, D, GR, 2>), grid, blk, 0, st, c0, nc, lv.cell_rec,
                          Lp, Up, M, b, x, s_save);
   });
 }
@@ -1084,11 +1102,11 @@ void launch_cell_apply(const DevLevel& lv, const T* base, const T* x, T* out, co
     const dim3 grid((lv.ncells + Pack::CPW - 1) / Pack::CPW), blk(Pack::threads);
     if (lv.blocks)
       hipLaunchKernelGGL((dev::k_cell_apply<T, D, GR, KIND, true>), grid, blk, 0, st, lv.ncells,
-                         lv.cell_ptr, LevelMats<T>::L(lv), LevelMats<T>::U(lv), Ep, Fp,
+                         lv.cell_rec, LevelMats<T>::L(lv), LevelMats<T>::U(lv), Ep, Fp,
                          LevelMats<T>::cellM(lv), base, x, out);
     else
       hipLaunchKernelGGL((dev::k_cell_apply<T, D, GR, KIND, false>), grid, blk, 0, st, lv.ncells,
-                         lv.cell_ptr, LevelMats<T>::L(lv), LevelMats<T>::U(lv), Ep, Fp,
+                         lv.cell_rec, LevelMats<T>::L(lv), LevelMats<T>::U(lv), Ep, Fp,
                          LevelMats<T>::cellM(lv), base, x, out);
   });
 }
@@ -2698,7 +2716,7 @@ int64_t estimate_device_bytes(const vasmg_ctx& C) {
     const int64_t vb = (need64 ? 8 : 0) + (need32 ? 4 : 0);
     b += n * 4 + 2 * (n + 1) * 4 + nb * (4 + dd * vb);
     if (l > 0 && l < L)
-      b += lv.ncells * (NU * NU * vb + 4) + 4 * (lv.ncolors + 2);
+      b += lv.ncells * (NU * NU * vb + 4 + 4 * cell_rec_ints(d)) + 4 * (lv.ncolors + 2);
     else
       b += n * dd * vb;
     if (l < L) {
