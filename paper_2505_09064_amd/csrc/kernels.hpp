@@ -14,8 +14,9 @@
 //     neighbour's components come in one 8/16-byte (FP32) or 16/32-byte (FP64)
 //     load; pad entries are kept at zero.
 // A block row is handled by a group of G lanes (G divides 64) that stride over
-// its blocks; partial sums are combined with cross-lane shuffles inside the
-// group and lane 0 of the group (or wavefront 0 of a cell) finishes the row.
+// its blocks (3D cell levels: a cell's threads walk all its rows together);
+// partial sums are combined across the group's lanes and lane 0 of the group (or
+// wavefront 0 of a cell) finishes the row.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -581,7 +582,7 @@ struct CellShape {
 // A cell's record: first device row, rows, then the NV + 1 row ranges' ends in L and
 // in U (in blocks; rows beyond the cell's last are empty). One cache line and one
 // load, where cell -> rows -> row ranges were two dependent ones: a launch is a
-// chain of dependent loads of about 6 us on most levels. Solve of a graded 401 x 401
+// chain of dependent loads of about 6 us on most levels. Solve of a graded 513 x 513
 // mesh, FP32 cycle, 193.1 -> 184.0 ms; of a 65^3 mesh 16.2 -> 15.8 ms.
 template <int D>
 struct CellRec {

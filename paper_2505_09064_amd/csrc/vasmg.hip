@@ -21,6 +21,7 @@
 #include <mutex>
 #include <numeric>
 #include <string>
+#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -1680,22 +1681,25 @@ void clear_reports(int* mail, int n) {
 }
 
 // Waits until the n words report iteration `it` or a stop; true if all have
-// stopped. Polls for up to 2 ms, then waits for the stream (which also returns a
-// launch's error).
+// stopped. Polls for up to 2 ms (giving way to other threads after 50 us), then
+// waits for the stream (which also returns a launch's error).
 bool wait_reports(const int* mail, int n, int it, hipStream_t st) {
   auto reported = [&](int v) { return v >= 0 && ((v & 1) || v >= 2 * it); };
-  const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+  const auto start = std::chrono::steady_clock::now();
   bool polling = true, all = true;
   for (int k = 0; k < n; ++k) {
     int v = __atomic_load_n(mail + k, __ATOMIC_RELAXED);
     while (!reported(v) && polling) {
-      __builtin_ia32_pause();
-      v = __atomic_load_n(mail + k, __ATOMIC_RELAXED);
-      if (!reported(v) && std::chrono::steady_clock::now() > end) {
+      const auto waited = std::chrono::steady_clock::now() - start;
+      if (waited > std::chrono::milliseconds(2)) {
         HIP_CHECK(hipStreamSynchronize(st));
         polling = false;
-        v = __atomic_load_n(mail + k, __ATOMIC_RELAXED);
+      } else if (waited > std::chrono::microseconds(50)) {
+        std::this_thread::yield();
+      } else {
+        __builtin_ia32_pause();
       }
+      v = __atomic_load_n(mail + k, __ATOMIC_RELAXED);
     }
     all = all && v >= 0 && (v & 1);
   }
