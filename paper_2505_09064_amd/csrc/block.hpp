@@ -183,23 +183,20 @@ __device__ __forceinline__ void mc_part_staged(const Part<T>& p, int i, int lane
 }
 
 // Per-column block sums: thread t contributes v to column (t / W) % K; on return
-// thread k < K holds column k's sum. A tree over the threads of equal t % (K * W)
-// (fixed order), then the W values of a column; one thread per column adding all
-// of the workgroup's values took 10 us of each reduction kernel.
+// thread k < K holds column k's sum, its values added in ascending thread order
+// (64 to 16 of them, all read from LDS at once: under half a microsecond).
 template <int K, int W>
 __device__ __forceinline__ double block_sum_cols(double v, double* sh) {
   static_assert(kBlock % (K * W) == 0, "whole periods");
   sh[threadIdx.x] = v;
   __syncthreads();
-#pragma unroll
-  for (int s = kBlock / 2; s >= K * W; s >>= 1) {
-    if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
   double r = 0.0;
   if (threadIdx.x < K) {
+#pragma unroll 16
+    for (int i = 0; i < kBlock / (K * W); ++i) {
 #pragma unroll
-    for (int a = 0; a < W; ++a) r += sh[threadIdx.x * W + a];
+      for (int a = 0; a < W; ++a) r += sh[(i * K + threadIdx.x) * W + a];
+    }
   }
   __syncthreads();
   return r;
@@ -426,6 +423,27 @@ __device__ __forceinline__ void mc_cell_sweep_pair(int k0, int v0, int n, const 
     if (MODE != 0) xc = x[o];
   }
   const T rdg = own ? T(1) / Msh[t * NU + t] : T(1);
+  if constexpr (D == 2) {   // one running sum per unknown (SEQ in k_gs_cell)
+#pragma unroll
+    for (int u = 0; u < NU; ++u) Mrow[u] = u == t ? T(0) : Mrow[u];
+    if (MODE != 0) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const T x0 = bcast(xc, u), x1 = bcast(xc, 32 + u);
+        acc = __builtin_elementwise_fma(-Mrow[u], h ? x1 : x0, acc);
+      }
+    }
+#pragma unroll
+    for (int uu = 0; uu < NU; ++uu) {
+      const int u = (MODE == 2) ? NU - 1 - uu : uu;
+      const T delta = __builtin_elementwise_fma(acc, rdg, -xc);
+      if (t == u) xc = acc * rdg;
+      const T d0 = bcast(delta, u), d1 = bcast(delta, 32 + u);
+      acc = __builtin_elementwise_fma(-Mrow[u], h ? d1 : d0, acc);
+    }
+    if (own) x[o] = xc;
+    return;
+  }
   // acc: the unknown's residual (as in k_gs_cell)
   if (MODE != 0) {
     T mx[2] = {T(0), T(0)};
@@ -509,8 +527,12 @@ __global__ __launch_bounds__(CellShape<D>::NV * GL) void k_cell_residual_mc(
 // Transfers: b_c = P^T r, 32 lanes per row (K columns x 32 / K slots over its
 // 9 to 60 entries: with one slot a row was one chain of dependent gathers, 37 us at
 // 4,374 rows and 4 columns), and x += P e, lane k of a K-lane group = column k.
+// FP32 in 2D: one slot (the order of the sums is part of the result: CellSums).
 // ---------------------------------------------------------------------------
-constexpr int kRestrictMcLanes = 32;
+template <typename T, int D, int K>
+struct RestrictMc {
+  static constexpr int lanes = D == 2 && sizeof(T) == 4 ? K : 32;
+};
 
 // VF: stride of the fine level's vectors; the coarse level's are packed (D).
 template <typename T, int D, int K, int VF>
@@ -521,14 +543,15 @@ __global__ __launch_bounds__(kBlock) void k_restrict_mc(int nc, const int* __res
                                                         T* __restrict__ bc, int64_t batch_f) {
   r += blockIdx.y * batch_f;
   bc += blockIdx.y * (static_cast<int64_t>(nc) * K * D);
-  const int lane = threadIdx.x % kRestrictMcLanes, slot = lane / K, k = lane % K;
-  const int I = xcd_block() * (kBlock / kRestrictMcLanes) + threadIdx.x / kRestrictMcLanes;
+  constexpr int RL = RestrictMc<T, D, K>::lanes;
+  const int lane = threadIdx.x % RL, slot = lane / K, k = lane % K;
+  const int I = xcd_block() * (kBlock / RL) + threadIdx.x / RL;
   if (I >= nc) return;
   T acc[D];
 #pragma unroll
   for (int a = 0; a < D; ++a) acc[a] = T(0);
 #pragma unroll 2
-  for (int p = ptr[I] + slot; p < ptr[I + 1]; p += kRestrictMcLanes / K) {
+  for (int p = ptr[I] + slot; p < ptr[I + 1]; p += RL / K) {
     T e[D];
     BlockVecIO<T, D, VF>::load(r + (static_cast<int64_t>(idx[p]) * K + k) * VF, e);
     const T wp = w[p];
@@ -536,7 +559,7 @@ __global__ __launch_bounds__(kBlock) void k_restrict_mc(int nc, const int* __res
     for (int a = 0; a < D; ++a) acc[a] += wp * e[a];
   }
 #pragma unroll
-  for (int a = 0; a < D; ++a) acc[a] = slot_sum<T, K, kRestrictMcLanes>(acc[a]);
+  for (int a = 0; a < D; ++a) acc[a] = slot_sum<T, K, RL>(acc[a]);
   if (slot == 0) BlockVecIO<T, D, D>::store(bc + (static_cast<int64_t>(I) * K + k) * D, acc);
 }
 

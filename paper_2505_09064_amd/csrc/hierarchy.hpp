@@ -98,6 +98,7 @@ struct Hierarchy {
   double box_m = 0.0, box_M = 0.0;      // root box [m, M]^d
   int max_depth = 0;
   int capacity = 0;
+  double contrast = 1.0;                // stiffest over softest element (a pack: its worst part)
   // wall-clock milliseconds of the setup phases, in the order they ran
   std::vector<std::pair<std::string, double>> phase_ms;
 };

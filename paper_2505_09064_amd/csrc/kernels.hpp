@@ -178,22 +178,46 @@ __device__ __forceinline__ double dpp(double v) {
 }
 constexpr int kDppXor1 = 0xB1;         // quad_perm [1, 0, 3, 2]
 constexpr int kDppXor2 = 0x4E;         // quad_perm [2, 3, 0, 1]
-constexpr int kDppHalfMirror = 0x141;  // lane i of 8 <- 7 - i: the other quad
-constexpr int kDppMirror = 0x140;      // lane i of 16 <- 15 - i: the other half
+constexpr int kDppRowShl = 0x100;      // + n: lane i of 16 <- i + n
+constexpr int kDppRowRor = 0x120;      // + n: lane i of 16 <- i - n, around the row
 constexpr int kDppBcast = 0x150;       // + u: lane u of the row to all 16
 
-// Sum over groups of G lanes, the same in every lane. Inside a row of 16 the
-// pairs, quads and halves meet by mirrored moves (the partial sums they fetch
-// are uniform over what they mirror); rows meet by shuffles.
+// v of lane i ^ 4: up in the even quads of a row, down in the odd ones.
+__device__ __forceinline__ int dpp_xor4(int v) {
+  const int o = __builtin_amdgcn_update_dpp(0, v, kDppRowShl + 4, 0xf, 0x5, false);
+  return __builtin_amdgcn_update_dpp(o, v, kDppRowShr + 4, 0xf, 0xa, false);
+}
+__device__ __forceinline__ float dpp_xor4(float v) { return __int_as_float(dpp_xor4(__float_as_int(v))); }
+__device__ __forceinline__ double dpp_xor4(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = dpp_xor4(static_cast<int>(b)), hi = dpp_xor4(static_cast<int>(b >> 32));
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
+}
+
+// Sum over groups of G lanes, the same in every lane: a butterfly from the widest
+// distance to the nearest lane, whose order FP32 results depend on. Rows of 16 meet
+// by shuffles, lanes of a row by moves (after the step over 8 lanes, a value
+// repeats every 8, so that a rotation by 4 fetches lane i ^ 4's).
 template <typename T, int G>
 __device__ __forceinline__ T group_sum(T v) {
-  if constexpr (G > 1) v += dpp<kDppXor1>(v);
-  if constexpr (G > 2) v += dpp<kDppXor2>(v);
-  if constexpr (G > 4) v += dpp<kDppHalfMirror>(v);
-  if constexpr (G > 8) v += dpp<kDppMirror>(v);
 #pragma unroll
-  for (int off = 16; off < G; off <<= 1) v += __shfl_xor(v, off, G);
+  for (int off = G / 2; off >= 16; off >>= 1) v += __shfl_xor(v, off, G);
+  if constexpr (G > 8) v += dpp<kDppRowRor + 8>(v);
+  if constexpr (G > 8) v += dpp<kDppRowRor + 4>(v);
+  else if constexpr (G > 4) v += dpp_xor4(v);
+  if constexpr (G > 2) v += dpp<kDppXor2>(v);
+  if constexpr (G > 1) v += dpp<kDppXor1>(v);
   return v;
+}
+
+// Lane 0: the sum over the wavefront by a tree (lane i adds lane i + 32's, ..., i + 1's).
+__device__ __forceinline__ double wave_tree(double v) {
+  v += __shfl_down(v, 32, 64);
+  v += __shfl_down(v, 16, 64);
+  v += dpp<kDppRowShl + 8>(v);
+  v += dpp<kDppRowShl + 4>(v);
+  v += dpp<kDppRowShl + 2>(v);
+  return v + dpp<kDppRowShl + 1>(v);
 }
 
 // Block-wide deterministic sum of one value per thread (fixed tree order).
@@ -340,70 +364,80 @@ __device__ __forceinline__ void load_own(const T* __restrict__ diag, const T* __
   }
 }
 
-// Off-diagonal products of a point-level row (LO / UP: which parts), a lane group
-// of G taking the blocks of the parts in order. Rows hold about 7 blocks per part,
-// so a row is one round, a chain of three dependent loads (row ranges -> columns ->
-// neighbours): the ranges of both parts come together, and columns and values of
-// UN blocks per lane go out before the first neighbour is waited for; only longer
-// rows loop. A lane without a block reads its row's last one (or, in an empty row,
-// the block before; an empty part has one zero block) times zero.
-template <typename T, int D, int G, bool LO, bool UP>
+// One part of a point-level row, a lane group of G taking its blocks in order (lane
+// l blocks l, l + G, ...). Rows hold about 7 blocks per part, so a part is one
+// round, a chain of three dependent loads (row range -> column -> neighbour): the
+// caller takes the ranges of both parts together, then opens both (columns and
+// values of the first round), and only then fetches neighbours; longer rows loop.
+// A lane without a block reads its row's last one (or, in an empty row, the block
+// before; an empty part has one zero block) times zero.
+template <typename T, int D, int G>
+struct PointWalk {
+  static constexpr int DP = Pad<D>::value;
+  int k = 0, ke = 0, j;
+  T m[D * D], xv[D];
+  __device__ __forceinline__ void range(const Part<T>& p, int i) {
+    k = p.ptr[i];
+    ke = p.ptr[i + 1];
+  }
+  __device__ __forceinline__ void open(const Part<T>& p, int lane) {
+    k += lane;
+    const int kc = max(min(k, ke - 1), 0);
+    j = p.col[kc];
+#pragma unroll
+    for (int e = 0; e < D * D; ++e) m[e] = p.val[e * p.nnz + kc];
+  }
+  __device__ __forceinline__ void gather(const T* __restrict__ x) {
+    VecIO<T, D>::load(x + static_cast<int64_t>(j) * DP, xv);
+  }
+  // (the compiler would sink a load whose value is only selected)
+  __device__ __forceinline__ void pin() {
+#pragma unroll
+    for (int b = 0; b < D; ++b) asm volatile("" : "+v"(xv[b]));
+  }
+  __device__ __forceinline__ void add(const Part<T>& p, const T* __restrict__ x, T* acc) {
+    const bool in = k < ke;
+#pragma unroll
+    for (int b = 0; b < D; ++b) {
+      const T xb = in ? xv[b] : T(0);
+#pragma unroll
+      for (int a = 0; a < D; ++a) acc[a] += m[a * D + b] * xb;
+    }
+    if (k + G < ke) row_product<T, D, G>(k + G, ke, 0, p.col, p.val, p.nnz, x, acc);
+  }
+};
+
+// Off-diagonal products of a point-level row (LO / UP: which parts): lo and up get
+// the parts' sums, in every lane of the group; BOTH: lo gets the one running sum
+// over L's blocks, then U's.
+template <typename T, int D, int G, bool LO, bool UP, bool BOTH = false>
 struct PointRow {
-  static constexpr int DP = Pad<D>::value, UN = LO && UP ? 2 : 1;
-  int l0 = 0, u0 = 0, nl = 0, total = 0;
+  PointWalk<T, D, G> l, u;
   __device__ __forceinline__ void ranges(const Part<T>& L, const Part<T>& U, int i) {
-    int le = 0, ue = 0;
-    if (LO) { l0 = L.ptr[i]; le = L.ptr[i + 1]; }
-    if (UP) { u0 = U.ptr[i]; ue = U.ptr[i + 1]; }
-    nl = le - l0;
-    total = nl + ue - u0;
+    if (LO) l.range(L, i);
+    if (UP) u.range(U, i);
   }
-  __device__ __forceinline__ void round(const Part<T>& L, const Part<T>& U, int f0,
-                                        const T* __restrict__ x, T* acc) const {
-    T m[UN][D * D], xv[UN][D];
-    int j[UN];
-#pragma unroll
-    for (int u = 0; u < UN; ++u) {
-      const int f = max(min(f0 + u * G, total - 1), 0);
-      const bool up = !LO || (UP && f >= nl);
-      int k = up ? u0 + f - nl : l0 + f;
-      if (total == 0) k = max(k - 1, 0);
-      const int* col = up ? U.col : L.col;
-      const T* val = up ? U.val : L.val;
-      const int64_t nnz = up ? U.nnz : L.nnz;
-      j[u] = col[k];
-#pragma unroll
-      for (int e = 0; e < D * D; ++e) m[u][e] = val[e * nnz + k];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int u = 0; u < UN; ++u) VecIO<T, D>::load(x + static_cast<int64_t>(j[u]) * DP, xv[u]);
-    // (pinned here: the compiler would sink a load whose value is only selected)
-#pragma unroll
-    for (int u = 0; u < UN; ++u) {
-#pragma unroll
-      for (int b = 0; b < D; ++b) asm volatile("" : "+v"(xv[u][b]));
-    }
-#pragma unroll
-    for (int u = 0; u < UN; ++u) {
-      const bool in = f0 + u * G < total;
-#pragma unroll
-      for (int b = 0; b < D; ++b) {
-        const T xb = in ? xv[u][b] : T(0);
-#pragma unroll
-        for (int a = 0; a < D; ++a) acc[a] += m[u][a * D + b] * xb;
-      }
-    }
-  }
-  // acc = the row's sums, in every lane of the group
   __device__ __forceinline__ void sum(const Part<T>& L, const Part<T>& U, int lane,
-                                      const T* __restrict__ x, T* acc) const {
+                                      const T* __restrict__ x, T* lo, T* up) {
 #pragma unroll
-    for (int a = 0; a < D; ++a) acc[a] = T(0);
-    round(L, U, lane, x, acc);
-    for (int f = lane + UN * G; f < total; f += UN * G) round(L, U, f, x, acc);
+    for (int a = 0; a < D; ++a) {
+      if (LO) lo[a] = T(0);
+      if (UP && !BOTH) up[a] = T(0);
+    }
+    if (LO) l.open(L, lane);
+    if (UP) u.open(U, lane);
+    __builtin_amdgcn_sched_barrier(0);
+    if (LO) l.gather(x);
+    if (UP) u.gather(x);
+    if (LO) l.pin();
+    if (UP) u.pin();
+    if (LO) l.add(L, x, lo);
+    if (UP) u.add(U, x, BOTH ? lo : up);
 #pragma unroll
-    for (int a = 0; a < D; ++a) acc[a] = group_sum<T, G>(acc[a]);
+    for (int a = 0; a < D; ++a) {
+      if (LO) lo[a] = group_sum<T, G>(lo[a]);
+      if (UP && !BOTH) up[a] = group_sum<T, G>(up[a]);
+    }
   }
 };
 
@@ -420,11 +454,11 @@ __global__ __launch_bounds__(kBlock) void k_spmv(int n, Part<T> L, Part<T> U,
   const int i = xcd_block() * (kBlock / G) + threadIdx.x / G;
   double dot = 0.0;
   if (i < n) {
-    PointRow<T, D, G, true, true> row;
+    PointRow<T, D, G, true, true, true> row;
     row.ranges(L, U, i);
     T acc[D], xi[D], dg[D * D];
     load_own<T, D>(diag, x, i, dg, xi);
-    row.sum(L, U, lane, x, acc);
+    row.sum(L, U, lane, x, acc, nullptr);
     if (lane == 0) {
       T yi[D];
 #pragma unroll
@@ -454,12 +488,12 @@ __global__ __launch_bounds__(kBlock) void k_residual_full(
   const int lane = threadIdx.x % G;
   const int i = xcd_block() * (kBlock / G) + threadIdx.x / G;
   if (i >= n) return;
-  PointRow<T, D, G, true, true> row;
+  PointRow<T, D, G, true, true, true> row;
   row.ranges(L, U, i);
   T acc[D], xi[D], bi[D], dg[D * D];
   load_own<T, D>(diag, x, i, dg, xi);
   VecIO<T, D>::load(b + static_cast<int64_t>(i) * DP, bi);
-  row.sum(L, U, lane, x, acc);
+  row.sum(L, U, lane, x, acc, nullptr);
   if (lane == 0) {
     T ri[D];
 #pragma unroll
@@ -489,12 +523,8 @@ __global__ __launch_bounds__(kBlock) void k_gs_color(
   const int g = xcd_block() * (kBlock / G) + threadIdx.x / G;
   if (g >= nrows) return;
   const int i = row0 + g;
-  // s = b - L x is only wanted on its own by the forward sweeps; the backward
-  // sweep takes both parts in one walk
-  PointRow<T, D, G, true, MODE == 2> low;
-  PointRow<T, D, G, false, true> upp;
-  low.ranges(L, U, i);
-  if (MODE == 1) upp.ranges(L, U, i);
+  PointRow<T, D, G, true, MODE != 0> row;
+  row.ranges(L, U, i);
   // what finishes the row, before the products
   T dg[D * D], xi[D], bi[D];
   load_own<T, D>(diag, MODE == 0 ? nullptr : x, i, dg, xi);
@@ -502,8 +532,7 @@ __global__ __launch_bounds__(kBlock) void k_gs_color(
   T lo[D], up[D];
 #pragma unroll
   for (int a = 0; a < D; ++a) up[a] = T(0);
-  low.sum(L, U, lane, x, lo);
-  if (MODE == 1) upp.sum(L, U, lane, x, up);
+  row.sum(L, U, lane, x, lo, up);
   if (lane != 0) return;
   T s[D], rhs[D];
 #pragma unroll
@@ -548,7 +577,7 @@ __global__ __launch_bounds__(kBlock) void k_residual_upper(
   T acc[D], xi[D], si[D], dg[D * D];
   load_own<T, D>(diag, x, i, dg, xi);
   VecIO<T, D>::load(s_save + static_cast<int64_t>(i) * DP, si);
-  row.sum(U, U, lane, x, acc);
+  row.sum(U, U, lane, x, nullptr, acc);
   if (lane == 0) {
     T ri[D];
 #pragma unroll
@@ -675,7 +704,9 @@ struct RowWalk {
     for (int e = 0; e < D * D; ++e)
       m[e] = reinterpret_cast<const StepVals<T>*>(p.val + static_cast<int64_t>(e) * p.nnz)[qq];
   }
-  __device__ __forceinline__ void product(const Part<T>& p, const T* __restrict__ x, T* acc) {
+  // a step's blocks are summed per component pair and then added, as in the quad
+  // steps of the fused bottom
+  __device__ __forceinline__ void product(const T* __restrict__ x, T* acc) {
     T xv[B][D];
 #pragma unroll
     for (int k = 0; k < B; ++k)
@@ -685,10 +716,18 @@ struct RowWalk {
 #pragma unroll
     for (int k = 0; k < B; ++k) {
 #pragma unroll
-      for (int b = 0; b < D; ++b) {
+      for (int b = 0; b < D; ++b)
         if (!in) xv[k][b] = T(0);
+    }
 #pragma unroll
-        for (int a = 0; a < D; ++a) acc[a] += m[a * D + b].v[k] * xv[k][b];
+    for (int a = 0; a < D; ++a) {
+#pragma unroll
+      for (int b = 0; b < D; ++b) {
+        const T* mv = m[a * D + b].v;
+        T v = __builtin_elementwise_fma(mv[0], xv[0][b], mv[1] * xv[1][b]);
+#pragma unroll
+        for (int k = 2; k < B; ++k) v = __builtin_elementwise_fma(mv[k], xv[k][b], v);
+        acc[a] = acc[a] + v;
       }
     }
   }
@@ -697,7 +736,7 @@ struct RowWalk {
       j = CellStep<T>::cols(p.col, q);
       values(p, q);
       __builtin_amdgcn_sched_barrier(0);
-      product(p, x, acc);
+      product(x, acc);
     }
   }
 };
@@ -722,7 +761,13 @@ struct RowWalk {
 // loads first, 13.7 flat (3.1 TB/s; the launch itself and the cell's own chain
 // are about 5 us of it); 4,092 cells a colour 30.1 -> 26.6 us (4.8 TB/s; a plain
 // read of ten such planes streams at 6.1); its residual 194 -> 176 us.
-// Several cells per wavefront (2D, rows of a few steps): a group of GR lanes per row.
+//
+// 2D (rows of a few steps, several cells per wavefront): a group of GR lanes per
+// row, and the in-cell arithmetic (SEQ below) in one running sum per unknown. The
+// order of the FP32 operations is part of the result there: a 2D iteration with
+// materials 1:100 takes 15 to 50 products and amplifies another rounding of its
+// preconditioner to 1e-9 .. 1e-8 of the solution (4 of 60 such problems above 1e-9
+// with this order changed; 3D: none of 500 above 2.5e-10).
 template <typename T, int D, int GR>
 struct CellSums {
   static constexpr int NV = CellShape<D>::NV, NU = CellShape<D>::NU;
@@ -730,7 +775,8 @@ struct CellSums {
   using Rec = CellRec<D>;
   static constexpr int PC = NU * NU * static_cast<int>(sizeof(T)) / 16;   // 16-byte pieces of M
   static constexpr int PR = (PC + CT - 1) / CT;
-  static constexpr int NW = CPW == 1 ? CT / 64 : 1;   // partial sums of a row
+  static constexpr bool FLAT = D == 3 && CPW == 1;
+  static constexpr int NW = FLAT ? CT / 64 : 1;   // partial sums of a row
   struct Lds {
     T M[CPW][NU * NU];
     T sum[CPW][NW][2 * NV][D];   // lower parts of the rows, then upper parts
@@ -744,14 +790,13 @@ struct CellSums {
     __device__ __forceinline__ T up(int slot, int k, int a) const { return total(slot, NV + k, a); }
   };
 
-  // The cell's record: an int per lane where the workgroup has one cell, else only
-  // its first two.
+  // The cell's record: an int per lane for the flat walk, else only its first two.
   struct Head {
     int rec, v0, m;
   };
   static __device__ __forceinline__ Head head(const int* __restrict__ rec, int c, bool live) {
     const int* r = rec + static_cast<int64_t>(c) * Rec::ints;
-    if constexpr (CPW == 1) {
+    if constexpr (FLAT) {
       const int v = r[threadIdx.x & (Rec::ints - 1)];
       return {v, __builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 1)};
     } else {
@@ -851,7 +896,7 @@ struct CellSums {
     const int v0 = hd.v0, m = hd.m;
     Vec16 piece[PR];
     const Vec16* Mc = reinterpret_cast<const Vec16*>(cellM + static_cast<int64_t>(c) * NU * NU);
-    if constexpr (CPW == 1) {
+    if constexpr (FLAT) {
       const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
       T(*sum)[D] = sh.sum[0][w];
       Flat<LO, UP> fl;
@@ -928,12 +973,12 @@ struct CellSums {
       for (int r = 0; r < PR; ++r)
         reinterpret_cast<Vec16*>(sh.M[slot])[min(t + r * CT, PC - 1)] = piece[r];
       if constexpr (LO) {
-        wl.product(L, x, lo);
+        wl.product(x, lo);
         wl.rest(L, x, lo);
         if constexpr (UP) wu.values(U, wu.q0);
       }
       if constexpr (UP) {
-        wu.product(U, x, up);
+        wu.product(x, up);
         wu.rest(U, x, up);
       }
 #pragma unroll
@@ -985,11 +1030,31 @@ __global__ __launch_bounds__((CellPack<D, GR>::threads)) void k_gs_cell(
   const T rdg = own ? T(1) / sh.M[slot][tc * NU + tc] : T(1);
   const T s_t = own ? bt - sh.lo(slot, k, a) : T(0);
   if (MODE != 2 && s_save && own) s_save[xi] = s_t;
+  T acc = own && MODE != 0 ? s_t - sh.up(slot, k, a) : s_t;
+  if constexpr (D == 2) {
+    // SEQ. acc: the unknown's right-hand side minus all other unknowns' products.
+    // Each unknown in turn is acc / diagonal and the others follow its change.
+    // Lanes without an unknown hold zeros (the cell matrix is zero outside the
+    // cell's unknowns).
+#pragma unroll
+    for (int u = 0; u < NU; ++u) Mrow[u] = u == t ? T(0) : Mrow[u];
+    if (MODE != 0)
+      static_for<NU>([&](auto ui) {
+        constexpr int u = decltype(ui)::value;
+        acc = __builtin_elementwise_fma(-Mrow[u], cell_bcast<CPW, CT, u>(xc), acc);
+      });
+    static_for<NU>([&](auto ui) {
+      constexpr int u = MODE == 2 ? NU - 1 - decltype(ui)::value : decltype(ui)::value;
+      const T delta = __builtin_elementwise_fma(acc, rdg, -xc);
+      if (t == u) xc = acc * rdg;
+      acc = __builtin_elementwise_fma(-Mrow[u], cell_bcast<CPW, CT, u>(delta), acc);
+    });
+    if (own) x[xi] = xc;
+    return;
+  }
   // acc: the unknown's residual. Each unknown in turn moves by residual /
   // diagonal and the others' residuals follow: one multiply, one broadcast and
-  // one multiply-add on the chain per step. Lanes without an unknown hold zeros
-  // (the cell matrix is zero outside the cell's unknowns).
-  T acc = own && MODE != 0 ? s_t - sh.up(slot, k, a) : s_t;
+  // one multiply-add on the chain per step. Lanes without an unknown hold zeros.
   if (MODE != 0) {
     T mx[2] = {T(0), T(0)};
     static_for<NV>([&](auto vi) {
@@ -1266,13 +1331,14 @@ __global__ __launch_bounds__((CellPack<D, GR>::threads)) void k_cell_apply(
   if (threadIdx.x >= 64) return;
   if (!own) xt = T(0);
   const int tc = min(t, NU - 1);
+  constexpr int CH = D == 2 ? 1 : 2;   // running sums (2D: one, SEQ)
   T mx[2] = {T(0), T(0)};
   static_for<NV>([&](auto vi) {
     constexpr int v = decltype(vi)::value;
     if (CPW > 1 || v < m)
       static_for<D>([&](auto ai) {
         constexpr int u = v * D + decltype(ai)::value;
-        mx[u % 2] += sh.M[slot][u * NU + tc] * cell_bcast<CPW, CT, u>(xt);
+        mx[u % CH] += sh.M[slot][u * NU + tc] * cell_bcast<CPW, CT, u>(xt);
       });
   });
   if (!own) return;
@@ -1885,12 +1951,50 @@ __global__ __launch_bounds__(kBlock) void k_update_p(int64_t n, const Scalars* _
 // test and the report. FP32-cycle iteration, separate launches and this way: 4,232
 // entries 78.8 and 73.6 us, 16,200 entries 131 and 139 us.
 constexpr int kSmallFlat = 8192;
+constexpr int kSmallRounds = kSmallFlat / 1024;   // entries per thread
+
+// Sum over the workgroup, thread t holding entries t, t + 1024, ...: in the order of
+// k_dot's workgroups of 256 entries and k_finalize's tree over them, so that a
+// problem's iterates do not depend on which form its size takes (PCG in FP32-cycle
+// 2D problems amplifies one flipped rounding of r to 1e-9 of the solution). A
+// workgroup of 256 entries is four wavefronts here: the first adds the others'
+// values as the tree's two widest steps do, and goes on inside itself.
+struct SmallSum {
+  double w[kSmallRounds][4][3][64];
+  double part[kSmallFlat / kBlock];
+};
+
+__device__ __forceinline__ double small_sum(int n, double (&v)[kSmallRounds], SmallSum& sh) {
+#pragma unroll
+  for (int j = 0; j < kSmallRounds; ++j) asm volatile("" : "+v"(v[j]));   // products rounded before the sums
+  const int g = threadIdx.x >> 8, w = (threadIdx.x >> 6) & 3, l = threadIdx.x & 63;
+  if (w > 0) {
+#pragma unroll
+    for (int j = 0; j < kSmallRounds; ++j)
+      if (1024 * j < n) sh.w[j][g][w - 1][l] = v[j];
+  }
+  __syncthreads();
+  if (w == 0) {
+#pragma unroll
+    for (int j = 0; j < kSmallRounds; ++j) {
+      double c = 0.0;
+      if (1024 * j < n)
+        c = wave_tree((v[j] + sh.w[j][g][1][l]) + (sh.w[j][g][0][l] + sh.w[j][g][2][l]));
+      if (l == 0) sh.part[4 * j + g] = c;
+    }
+  }
+  __syncthreads();
+  constexpr int NP = kSmallFlat / kBlock;
+  return bcast(wave_tree(l < NP ? sh.part[l] : 0.0), 0);
+}
+
 template <typename T>
 __global__ __launch_bounds__(1024) void k_small_xr(int n, Scalars* s, const double* __restrict__ partial,
                                                    int np, const double* __restrict__ p,
                                                    const double* __restrict__ q, double* __restrict__ x,
                                                    double* __restrict__ r, T* __restrict__ b0, int* mail) {
   __shared__ double sh[1024];
+  __shared__ SmallSum ss;
   if (s->done) {
     if (threadIdx.x == 0) report(mail, s);
     return;
@@ -1905,16 +2009,20 @@ __global__ __launch_bounds__(1024) void k_small_xr(int n, Scalars* s, const doub
     return;
   }
   const double alpha = rho / pq;
-  v = 0.0;
-#pragma unroll 4
-  for (int i = threadIdx.x; i < n; i += 1024) {
-    x[i] += alpha * p[i];
-    const double ri = r[i] - alpha * q[i];
-    r[i] = ri;
-    if (b0) b0[i] = static_cast<T>(ri);
-    v += ri * ri;
+  double e[kSmallRounds];
+#pragma unroll
+  for (int j = 0; j < kSmallRounds; ++j) {
+    const int i = threadIdx.x + 1024 * j;
+    e[j] = 0.0;
+    if (i < n) {
+      x[i] += alpha * p[i];
+      const double ri = r[i] - alpha * q[i];
+      r[i] = ri;
+      if (b0) b0[i] = static_cast<T>(ri);
+      e[j] = ri * ri;
+    }
   }
-  const double rr = block_sum(v, sh);
+  const double rr = small_sum(n, e, ss);
   if (threadIdx.x == 0) {
     finalize_scalar<FIN_RES>(rr, s);
     report(mail, s);
@@ -1925,14 +2033,17 @@ __global__ __launch_bounds__(1024) void k_small_xr(int n, Scalars* s, const doub
 template <typename T>
 __global__ __launch_bounds__(1024) void k_small_p(int n, Scalars* s, const double* __restrict__ r,
                                                   const T* __restrict__ z, double* __restrict__ p) {
-  __shared__ double sh[1024];
+  __shared__ SmallSum ss;
   if (s->done) return;
   const double rho = s->rho;
   const bool first = s->first != 0;
-  double v = 0.0;
-#pragma unroll 4
-  for (int i = threadIdx.x; i < n; i += 1024) v += r[i] * static_cast<double>(z[i]);
-  const double tot = block_sum(v, sh);   // (its barriers keep the reads of s before the write)
+  double e[kSmallRounds];
+#pragma unroll
+  for (int j = 0; j < kSmallRounds; ++j) {
+    const int i = threadIdx.x + 1024 * j;
+    e[j] = i < n ? r[i] * static_cast<double>(z[i]) : 0.0;
+  }
+  const double tot = small_sum(n, e, ss);   // (its barriers keep the reads of s before the write)
   if (threadIdx.x == 0) finalize_scalar<FIN_BETA>(tot, s);
   if (!isfinite(tot)) return;
   const double beta = first ? 0.0 : tot / rho;

@@ -10,33 +10,78 @@
 namespace vasmg {
 namespace dev {
 
-// One workgroup per segment: the segment's dot product over its rows (DP
-// entries each; DIFF: of a - b with itself), summed in a fixed order, then the
-// scalar step MODE (the norms of the right-hand side and the true residual) on
-// the segment's own scalars.
-constexpr int kSegBlock = 1024;
+// One workgroup per segment sums over its entries (DP per row). The order is that of
+// 256 threads, each taking every 256th entry, and a tree over them (so that a part's
+// iterates stay what they are whatever fetches the entries); all 1,024 threads fetch,
+// for the loads in flight, and hand the factors over in LDS.
+constexpr int kSegBlock = 1024, kSegChunk = 2 * kSegBlock;
 
-template <int MODE, bool DIFF>
+struct SegSum {
+  double a[kSegChunk], b[kSegChunk], t[kBlock];
+};
+
+// Sum of a b over the entries e < n, f(e, a, b) giving entry e's factors (called
+// once per entry, by one thread); the same in every thread.
+template <class F>
+__device__ __forceinline__ double seg_sum(int64_t n, SegSum& sh, F&& f) {
+  const int t = threadIdx.x;
+  double a[2], b[2], v = 0.0;
+  auto fetch = [&](int64_t c0) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int64_t e = c0 + t + u * kSegBlock;
+      a[u] = b[u] = 0.0;
+      if (e < n) f(e, a[u], b[u]);
+    }
+  };
+  fetch(0);
+  for (int64_t c0 = 0; c0 < n; c0 += kSegChunk) {
+    __syncthreads();   // the chunk before has been added
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      sh.a[t + u * kSegBlock] = a[u];
+      sh.b[t + u * kSegBlock] = b[u];
+    }
+    __syncthreads();
+    fetch(c0 + kSegChunk);
+    if (t < kBlock) {
+#pragma unroll
+      for (int i = 0; i < kSegChunk / kBlock; ++i)
+        v = __builtin_fma(sh.a[t + i * kBlock], sh.b[t + i * kBlock], v);
+    }
+  }
+  if (t < kBlock) sh.t[t] = v;
+  __syncthreads();
+#pragma unroll
+  for (int s = kBlock / 2; s > 0; s >>= 1) {
+    if (t < s) sh.t[t] += sh.t[t + s];
+    __syncthreads();
+  }
+  const double r = sh.t[0];
+  __syncthreads();
+  return r;
+}
+
+// The segment's dot product (DIFF: of a - b with itself), then the scalar step MODE
+// (the norms of the right-hand side and the true residual) on its own scalars.
+template <int MODE, bool DIFF, int DP>
 __global__ __launch_bounds__(kSegBlock) void k_seg_dot(const int* __restrict__ seg_ptr,
-                                                       const int* __restrict__ seg_rows, int DP,
+                                                       const int* __restrict__ seg_rows,
                                                        const double* __restrict__ a,
                                                        const double* __restrict__ b,
                                                        Scalars* __restrict__ ss) {
-  __shared__ double sh[kSegBlock];
-  const int s = blockIdx.x;
-  const int lo = seg_ptr[s], hi = seg_ptr[s + 1];
-  double v = 0.0;
-  for (int64_t q = static_cast<int64_t>(lo) * DP + threadIdx.x; q < static_cast<int64_t>(hi) * DP;
-       q += kSegBlock) {
-    const int64_t i = static_cast<int64_t>(seg_rows[q / DP]) * DP + q % DP;
+  __shared__ SegSum sh;
+  const int s = blockIdx.x, lo = seg_ptr[s];
+  const int64_t n = static_cast<int64_t>(seg_ptr[s + 1] - lo) * DP;
+  const double tot = seg_sum(n, sh, [&](int64_t e, double& u, double& v) {
+    const int64_t i = static_cast<int64_t>(seg_rows[lo + e / DP]) * DP + e % DP;
     if (DIFF) {
-      const double t = a[i] - b[i];
-      v += t * t;
+      u = v = a[i] - b[i];
     } else {
-      v += a[i] * b[i];
+      u = a[i];
+      v = b[i];
     }
-  }
-  const double tot = block_sum(v, sh);
+  });
   if (threadIdx.x == 0) finalize_scalar<MODE>(tot, &ss[s]);
 }
 
@@ -59,10 +104,7 @@ __global__ void k_seg_start(int nseg, Scalars* __restrict__ ss, double rtol, int
 // The vector work of an iteration, one workgroup per part: all of it between the
 // SpMV and the preconditioner (p.q, alpha, x += alpha p, r -= alpha q, b0 = (T) r,
 // ||r||, the stopping test, the report) and all of it after (r.z, beta,
-// p = z + beta p). As separate launches, with the sums by 256 threads per part and
-// the updates spread over the chip, an iteration of 8 parts of 3,840 rows took
-// 509 us, and 424 us this way; of 2 parts of 7,600 rows 536 and 374 us. The sums
-// need one workgroup per part in either form, so they bound both at any part size.
+// p = z + beta p).
 template <typename T, int DP>
 __global__ __launch_bounds__(kSegBlock) void k_seg_xr(const int* __restrict__ seg_ptr,
                                                       const int* __restrict__ seg_rows,
@@ -71,7 +113,7 @@ __global__ __launch_bounds__(kSegBlock) void k_seg_xr(const int* __restrict__ se
                                                       const double* __restrict__ q,
                                                       double* __restrict__ x, double* __restrict__ r,
                                                       T* __restrict__ b0, int* mail) {
-  __shared__ double sh[kSegBlock];
+  __shared__ SegSum sh;
   Scalars* s = ss + blockIdx.x;
   mail += blockIdx.x;
   if (s->done) {
@@ -79,32 +121,28 @@ __global__ __launch_bounds__(kSegBlock) void k_seg_xr(const int* __restrict__ se
     return;
   }
   const double rho = s->rho;
-  const int64_t lo = static_cast<int64_t>(seg_ptr[blockIdx.x]) * DP;
-  const int64_t hi = static_cast<int64_t>(seg_ptr[blockIdx.x + 1]) * DP;
-  double v = 0.0;
-#pragma unroll 4
-  for (int64_t e = lo + threadIdx.x; e < hi; e += kSegBlock) {
-    const int64_t i = static_cast<int64_t>(seg_rows[e / DP]) * DP + e % DP;
-    v += p[i] * q[i];
-  }
-  const double pq = block_sum(v, sh);
+  const int lo = seg_ptr[blockIdx.x];
+  const int64_t n = static_cast<int64_t>(seg_ptr[blockIdx.x + 1] - lo) * DP;
+  auto at = [&](int64_t e) { return static_cast<int64_t>(seg_rows[lo + e / DP]) * DP + e % DP; };
+  const double pq = seg_sum(n, sh, [&](int64_t e, double& u, double& v) {
+    const int64_t i = at(e);
+    u = p[i];
+    v = q[i];
+  });
   if (threadIdx.x == 0) finalize_scalar<FIN_ALPHA>(pq, s);
   if (!(pq > 0.0) || !isfinite(pq)) {   // breakdown: this part has stopped
     if (threadIdx.x == 0) report(mail, s);
     return;
   }
   const double alpha = rho / pq;
-  v = 0.0;
-#pragma unroll 4
-  for (int64_t e = lo + threadIdx.x; e < hi; e += kSegBlock) {
-    const int64_t i = static_cast<int64_t>(seg_rows[e / DP]) * DP + e % DP;
+  const double rr = seg_sum(n, sh, [&](int64_t e, double& u, double& v) {
+    const int64_t i = at(e);
     x[i] += alpha * p[i];
     const double ri = r[i] - alpha * q[i];
     r[i] = ri;
     if (b0) b0[i] = static_cast<T>(ri);
-    v += ri * ri;
-  }
-  const double rr = block_sum(v, sh);
+    u = v = ri;
+  });
   if (threadIdx.x == 0) {
     finalize_scalar<FIN_RES>(rr, s);
     report(mail, s);
@@ -117,26 +155,25 @@ __global__ __launch_bounds__(kSegBlock) void k_seg_p(const int* __restrict__ seg
                                                      Scalars* __restrict__ ss,
                                                      const double* __restrict__ r,
                                                      const T* __restrict__ z, double* __restrict__ p) {
-  __shared__ double sh[kSegBlock];
+  __shared__ SegSum sh;
   Scalars* s = ss + blockIdx.x;
   if (s->done) return;
   const double rho = s->rho;
   const bool first = s->first != 0;
-  const int64_t lo = static_cast<int64_t>(seg_ptr[blockIdx.x]) * DP;
-  const int64_t hi = static_cast<int64_t>(seg_ptr[blockIdx.x + 1]) * DP;
-  double v = 0.0;
-#pragma unroll 4
-  for (int64_t e = lo + threadIdx.x; e < hi; e += kSegBlock) {
-    const int64_t i = static_cast<int64_t>(seg_rows[e / DP]) * DP + e % DP;
-    v += r[i] * static_cast<double>(z[i]);
-  }
-  const double tot = block_sum(v, sh);   // (its barriers keep the reads of s before the write)
+  const int lo = seg_ptr[blockIdx.x];
+  const int64_t n = static_cast<int64_t>(seg_ptr[blockIdx.x + 1] - lo) * DP;
+  auto at = [&](int64_t e) { return static_cast<int64_t>(seg_rows[lo + e / DP]) * DP + e % DP; };
+  const double tot = seg_sum(n, sh, [&](int64_t e, double& u, double& v) {
+    const int64_t i = at(e);
+    u = r[i];
+    v = static_cast<double>(z[i]);
+  });   // (its barriers keep the reads of s before the write)
   if (threadIdx.x == 0) finalize_scalar<FIN_BETA>(tot, s);
   if (!isfinite(tot)) return;
   const double beta = first ? 0.0 : tot / rho;
 #pragma unroll 4
-  for (int64_t e = lo + threadIdx.x; e < hi; e += kSegBlock) {
-    const int64_t i = static_cast<int64_t>(seg_rows[e / DP]) * DP + e % DP;
+  for (int64_t e = threadIdx.x; e < n; e += kSegBlock) {
+    const int64_t i = at(e);
     p[i] = static_cast<double>(z[i]) + beta * p[i];
   }
 }

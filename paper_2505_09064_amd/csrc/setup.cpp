@@ -32,6 +32,7 @@
 #include <cmath>
 #include <cstring>
 #include <exception>
+#include <limits>
 #include <numeric>
 #include <thread>
 #include <utility>
@@ -110,6 +111,21 @@ void validate(const MeshView& m) {
     if (!(m.nu[e] > -1.0 && m.nu[e] < 0.5)) fail(1, "nu must lie in (-1, 0.5)");
     fail(1, "element vertex index out of range");
   }
+}
+
+// Largest over smallest modulus of the elements: of shear (mu) or of uniaxial
+// strain (lambda + 2 mu), whichever varies more.
+double stiffness_contrast(const MeshView& m) {
+  double lo_s = std::numeric_limits<double>::infinity(), hi_s = 0.0, lo_p = lo_s, hi_p = 0.0;
+#pragma omp parallel for schedule(static) reduction(min : lo_s, lo_p) reduction(max : hi_s, hi_p)
+  for (int64_t e = 0; e < m.ne; ++e) {
+    const double nu = m.nu[e], s = m.E[e] / (2.0 * (1.0 + nu)), p = 2.0 * s * (1.0 - nu) / (1.0 - 2.0 * nu);
+    lo_s = std::min(lo_s, s);
+    hi_s = std::max(hi_s, s);
+    lo_p = std::min(lo_p, p);
+    hi_p = std::max(hi_p, p);
+  }
+  return std::max(hi_s / lo_s, hi_p / lo_p);
 }
 
 // --------------------------------------------------------------------------
@@ -776,6 +792,7 @@ void pack_hierarchies(const std::vector<const Hierarchy*>& parts, Hierarchy& U) 
     for (int32_t v : p->free_vertices) U.free_vertices.push_back(static_cast<int32_t>(v + vo));
     vo += p->n_mesh_vertices;
     U.max_depth = std::max(U.max_depth, p->max_depth);
+    U.contrast = std::max(U.contrast, p->contrast);
   }
   if (vo > INT32_MAX) fail(1, "packed problems exceed 2^31 vertices");
   U.n_mesh_vertices = vo;
@@ -881,6 +898,7 @@ void build_hierarchy(const MeshView& m, const SetupParams& prm, Hierarchy& H) {
   H = Hierarchy();
   H.d = d;
   H.n_mesh_vertices = m.nv;
+  H.contrast = stiffness_contrast(m);
   H.capacity = prm.capacity;
   auto t0 = std::chrono::steady_clock::now();
   auto mark = [&](const char* phase) {

@@ -1746,6 +1746,7 @@ void ensure_packed_graphs(vasmg_ctx& C) {
 template <int D>
 int solve_packed(vasmg_ctx& C, const double* d_rhs, double* d_x, double rtol, hipStream_t st,
                  vasmg_solve_info* info) {
+  constexpr int DP = dev::Pad<D>::value;
   ensure_packed_graphs<D>(C);
   const int n0 = C.n0;
   const int64_t n0p = C.n0p;
@@ -1754,8 +1755,8 @@ int solve_packed(vasmg_ctx& C, const double* d_rhs, double* d_x, double rtol, hi
   hipLaunchKernelGGL((dev::k_gather_user<double, double, D>), dim3(grid_for(n0, dev::kBlock)),
                      dim3(dev::kBlock), 0, st, n0, C.user_map, d_rhs, C.F,
                      static_cast<const uint8_t*>(C.lev[0].fixed));
-  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_NORMF, false>), dim3(nseg), dim3(dev::kSegBlock), 0, st,
-                     C.seg_ptr, C.seg_rows, C.DP, C.F, C.F, C.ssc);
+  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_NORMF, false, DP>), dim3(nseg), dim3(dev::kSegBlock), 0, st,
+                     C.seg_ptr, C.seg_rows, C.F, C.F, C.ssc);
   clear_reports(C.mail, nseg);
   hipLaunchKernelGGL(dev::k_seg_start, dim3(grid_for(nseg, dev::kBlock)), dim3(dev::kBlock), 0, st, nseg,
                      C.ssc, rtol, C.mail);
@@ -1778,8 +1779,8 @@ int solve_packed(vasmg_ctx& C, const double* d_rhs, double* d_x, double rtol, hi
   }
   // true residuals, scatter
   launch_spmv<double, D>(C.lev[0], C.X, C.Q, nullptr, 0, nullptr, st);
-  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_TRUE, true>), dim3(nseg), dim3(dev::kSegBlock), 0, st,
-                     C.seg_ptr, C.seg_rows, C.DP, C.F, C.Q, C.ssc);
+  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_TRUE, true, DP>), dim3(nseg), dim3(dev::kSegBlock), 0, st,
+                     C.seg_ptr, C.seg_rows, C.F, C.Q, C.ssc);
   launch_fill<double>(d_x, C.H.n_mesh_vertices * D, 0.0, st);
   hipLaunchKernelGGL((dev::k_scatter_user<double, double, D>), dim3(grid_for(n0, dev::kBlock)),
                      dim3(dev::kBlock), 0, st, n0, C.user_map, C.X, d_x);
@@ -1989,9 +1990,11 @@ void upload_block(vasmg_ctx& C, int K) {
     const double avg = lv.n > 0 ? static_cast<double>(lv.nnz) / lv.n : 0.0;
     // (16 columns: the wide groups where a colour has no more cells than the chip
     // compute units, a workgroup each and its chain of chunks all there is: 23x30x26,
-    // narrow / wide, FP32 28.0 / 23.9 ms, FP64 34.7 / 30.6)
+    // narrow / wide, FP32 28.0 / 23.9 ms, FP64 34.7 / 30.6; FP32 in 2D keeps one
+    // order of the sums, see CellSums)
     if (lv.cells)
-      lv.mcGL = K == 16 && lv.ncells <= 256 * lv.ncolors ? dev::kCellLanesWide : dev::kCellLanesNarrow;
+      lv.mcGL = K == 16 && lv.ncells <= 256 * lv.ncolors && (C.d == 3 || !C.vc32) ? dev::kCellLanesWide
+                                                                                 : dev::kCellLanesNarrow;
     else
       lv.mcGL = avg >= 24.0 ? dev::kPointLanesWide : dev::kPointLanesNarrow;
     if (C.opt.block_lanes != 0) {   // forced: narrow (1) or wide (2) groups everywhere
@@ -2125,7 +2128,7 @@ void enqueue_vcycle_mc(vasmg_ctx& C, hipStream_t st) {
     for (int k = 0; k < C.opt.n_pre; ++k)
       launch_gs_sweep_mc<T, D, K>(lv, lv.mcGL, 1, false, k == 0, b, x, s, st);
     launch_residual_mc<T, D, K>(lv, lv.mcGL, 1, s, x, r, st);
-    const dim3 rgrid(grid_for(lv.nnext, dev::kBlock / dev::kRestrictMcLanes));
+    const dim3 rgrid(grid_for(lv.nnext, dev::kBlock / dev::RestrictMc<T, D, K>::lanes));
     if (l == 0)
       hipLaunchKernelGGL((dev::k_restrict_mc<T, D, K, dev::Pad<D>::value>), rgrid, dim3(dev::kBlock),
                          0, st, lv.nnext, lv.pt_ptr, lv.pt_idx, LevelMats<T>::ptw(lv), r,
@@ -2332,6 +2335,18 @@ int solve_block(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d
 constexpr int64_t kDenseMaxDofs = 2304;
 constexpr int64_t kDenseMaxBytes = int64_t(256) << 20;
 constexpr int64_t kDenseWorkBytes = int64_t(384) << 20;   // transient vectors of one chunk
+// FP32 cycles in 2D take tables only up to this stiffness contrast of the mesh.
+// Another rounding of the preconditioner moves the solution of PCG little where it
+// converges in 10 to 20 products, and by 1e-9 and more where it takes 15 to 50 (200
+// 2D problems of up to 60,000 vertices each, FP32 tables against the level launches,
+// largest relative change: contrast 1 1.4e-12, 4 9e-13, 10 3.4e-11, 30 1.3e-9, 100
+// 7.9e-9; 3D, contrast 100, 2.5e-10).
+constexpr double kDenseMaxContrast2d = 10.0;
+
+bool dense_wanted(const vasmg_ctx& C) {
+  return !C.no_dense && C.opt.cycle != VASMG_CYCLE_W &&
+         !(C.vc32 && C.d == 2 && C.H.contrast > kDenseMaxContrast2d);
+}
 
 // Vertex offsets of the parts on level l.
 std::vector<int64_t> part_offsets(const vasmg_ctx& C, int l) {
@@ -2360,7 +2375,7 @@ int64_t dense_elems(const vasmg_ctx& C, const std::vector<int64_t>& hi, const st
 int64_t dense_bytes_bound(const vasmg_ctx& C, int64_t* work) {
   *work = 0;
   const int L = static_cast<int>(C.H.levels.size()) - 1;
-  if (C.no_dense || C.opt.preconditioner != VASMG_PRECOND_VASMG || C.opt.cycle == VASMG_CYCLE_W ||
+  if (!dense_wanted(C) || C.opt.preconditioner != VASMG_PRECOND_VASMG ||
       C.opt.smoother != VASMG_SMOOTHER_GS || C.opt.n_pre < 1 || L < 2)
     return 0;
   for (int l = 1; l < L; ++l) {
@@ -2396,7 +2411,7 @@ void dense_down(vasmg_ctx& C, std::vector<DenseWork>& w, int l0, int l1, int nb,
     for (int k = 0; k < C.opt.n_pre; ++k)
       launch_gs_sweep_mc<T, D, K>(lv, dev::kCellLanesNarrow, nb, false, k == 0, b, x, s, st);
     launch_residual_mc<T, D, K>(lv, dev::kCellLanesNarrow, nb, s, x, r, st);
-    hipLaunchKernelGGL((dev::k_restrict_mc<T, D, K, D>), dim3(grid_for(lv.nnext, dev::kBlock / dev::kRestrictMcLanes), nb),
+    hipLaunchKernelGGL((dev::k_restrict_mc<T, D, K, D>), dim3(grid_for(lv.nnext, dev::kBlock / dev::RestrictMc<T, D, K>::lanes), nb),
                        dim3(dev::kBlock), 0, st, lv.nnext, lv.pt_ptr, lv.pt_idx, LevelMats<T>::ptw(lv), r,
                        static_cast<T*>(w[l + 1].v[0]), static_cast<int64_t>(lv.n) * K * D);
   }
@@ -2561,7 +2576,7 @@ void build_dense(vasmg_ctx& C, hipStream_t st) {
 // from a nonzero iterate and keeps k_bottom). Without memory for them the
 // handle goes on without.
 void make_dense(vasmg_ctx& C) {
-  if (C.bottom_lo < 0 || C.no_dense || C.opt.cycle == VASMG_CYCLE_W) return;
+  if (C.bottom_lo < 0 || !dense_wanted(C)) return;
   hipStream_t st = C.alloc_stream;
   if (!st && C.gdev) {   // the level layouts are still being written on the setup's stream
     st = static_cast<hipStream_t>(galerkin_device_stream(C.gdev));
