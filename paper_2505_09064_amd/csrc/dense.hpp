@@ -3,13 +3,15 @@
 // Below some level the multiplicative cycle is a fixed linear map of a few
 // thousand unknowns whose evaluation level by level is a chain of hundreds of
 // dependent steps (colours, transfers), each a few microseconds whatever its
-// size. The map is tabulated once per handle by running the cycle itself, in the
-// cycle's precision, on the columns of the identity (block kernels, 16 columns
-// per batch, all batches of a chunk in one launch), and a visit is then one
-// matrix-vector product per table:
+// size. The map is tabulated once per handle by running the cycle itself on the
+// columns of the identity (block kernels, 16 columns per batch, all batches of a
+// chunk in one launch), and a visit is then one matrix-vector product per table:
 //   B  (level lo, where the fused bottom starts): x_lo = B b_lo;
 //   R, [S Q] (levels ld .. lo - 1 above it): b_lo = R b_ld and
 //      x_ld = S b_ld + Q x_lo.
+// B holds the coarsest solve, which is FP64 in every cycle: B is built from FP64
+// levels, kept and applied in FP64 also where the vectors and the other tables are
+// FP32 (375 unknowns at 65^3: 1.1 MB).
 // A product streams its table once: 2,187 unknowns in FP32 are 19 MB, a few
 // microseconds, where the level's 19 launches took 115. One wavefront per row;
 // the input vector is staged in LDS while the row's first 16-byte chunks are in
@@ -53,13 +55,13 @@ struct alignas(16) Chunk {
   T v[Q];
 };
 
-// out = M [v1; v2]; one wavefront per row, segment blockIdx.y (one: the only
-// segment, by value).
-template <typename T, int D>
+// out = M [v1; v2], table and sums in T, vectors in V; one wavefront per row, segment
+// blockIdx.y (one: the only segment, by value).
+template <typename V, typename T, int D>
 __global__ __launch_bounds__(64 * kDenseWaves) void k_dense(
     DenseSeg one, const DenseSeg* __restrict__ segs, const T* __restrict__ M,
-    const T* __restrict__ v1, const int* __restrict__ list1, const T* __restrict__ v2,
-    const int* __restrict__ list2, T* __restrict__ out, const int* __restrict__ list_out) {
+    const V* __restrict__ v1, const int* __restrict__ list1, const V* __restrict__ v2,
+    const int* __restrict__ list2, V* __restrict__ out, const int* __restrict__ list_out) {
   constexpr int DP = Pad<D>::value, Q = DenseShape<T>::Q, NP = 8;
   using C = Chunk<T, Q>;
   extern __shared__ __align__(16) unsigned char dense_smem[];
@@ -79,16 +81,16 @@ __global__ __launch_bounds__(64 * kDenseWaves) void k_dense(
   }
   const int c1 = DenseShape<T>::pad(s.na * D);
   for (int i = threadIdx.x; i < s.na; i += blockDim.x) {
-    T v[D];
-    VecIO<T, D>::load(v1 + static_cast<int64_t>(list1 ? list1[s.a0 + i] : s.a0 + i) * DP, v);
+    V v[D];
+    VecIO<V, D>::load(v1 + static_cast<int64_t>(list1 ? list1[s.a0 + i] : s.a0 + i) * DP, v);
 #pragma unroll
-    for (int a = 0; a < D; ++a) xs[i * D + a] = v[a];
+    for (int a = 0; a < D; ++a) xs[i * D + a] = static_cast<T>(v[a]);
   }
   for (int i = threadIdx.x; i < s.nc; i += blockDim.x) {
-    T v[D];
-    VecIO<T, D>::load(v2 + static_cast<int64_t>(list2 ? list2[s.c0 + i] : s.c0 + i) * DP, v);
+    V v[D];
+    VecIO<V, D>::load(v2 + static_cast<int64_t>(list2 ? list2[s.c0 + i] : s.c0 + i) * DP, v);
 #pragma unroll
-    for (int a = 0; a < D; ++a) xs[c1 + i * D + a] = v[a];
+    for (int a = 0; a < D; ++a) xs[c1 + i * D + a] = static_cast<T>(v[a]);
   }
   if (threadIdx.x < c1 - s.na * D) xs[s.na * D + threadIdx.x] = T(0);
   if (threadIdx.x < s.ld - c1 - s.nc * D) xs[c1 + s.nc * D + threadIdx.x] = T(0);
@@ -117,7 +119,7 @@ __global__ __launch_bounds__(64 * kDenseWaves) void k_dense(
   sum = group_sum<T, 64>(sum);
   if (lane == 0 && row < rows) {
     const int i = s.r0 + row / D;
-    out[static_cast<int64_t>(list_out ? list_out[i] : i) * DP + row % D] = sum;
+    out[static_cast<int64_t>(list_out ? list_out[i] : i) * DP + row % D] = static_cast<V>(sum);
   }
 }
 
@@ -155,8 +157,8 @@ struct Mfma16<double> {
 
 // acc += M[row][cols of one input] v: nv vertices, the first at index v0 of v,
 // matrix row m (this lane's). Groups of four vertices wave, wave + waves, ...
-template <typename T, int D, int K>
-__device__ __forceinline__ void dense_mc_input(const T* __restrict__ m, const T* __restrict__ v, int v0,
+template <typename V, typename T, int D, int K>
+__device__ __forceinline__ void dense_mc_input(const T* __restrict__ m, const V* __restrict__ v, int v0,
                                                int nv, int wave, int lane,
                                                typename Mfma16<T>::Acc& acc) {
   constexpr int UN = sizeof(T) == 4 ? 4 : 2;
@@ -164,15 +166,17 @@ __device__ __forceinline__ void dense_mc_input(const T* __restrict__ m, const T*
   const int groups = (nv + 3) / 4;
   for (int q0 = wave; q0 < groups; q0 += UN * kDenseMcWaves) {
     T a[UN][D], b[UN][D];
+    V vb[UN][D];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
       const int i = 4 * (q0 + u * kDenseMcWaves) + g;
       const bool in = i < nv;
       const int ic = in ? i : nv - 1;
       BlockVecIO<T, D, D>::load(m + ic * D, a[u]);
-      BlockVecIO<T, D, D>::load(v + (static_cast<int64_t>(v0 + ic) * K + n % K) * D, b[u]);
+      BlockVecIO<V, D, D>::load(v + (static_cast<int64_t>(v0 + ic) * K + n % K) * D, vb[u]);
 #pragma unroll
       for (int c = 0; c < D; ++c) {
+        b[u][c] = static_cast<T>(vb[u][c]);
         if (!in) a[u][c] = T(0);
         if (!in || n >= K) b[u][c] = T(0);
       }
@@ -186,20 +190,20 @@ __device__ __forceinline__ void dense_mc_input(const T* __restrict__ m, const T*
 }
 
 // out = M [v1; v2] for K columns of a single problem (segment s).
-template <typename T, int D, int K>
+template <typename V, typename T, int D, int K>
 __global__ __launch_bounds__(64 * kDenseMcWaves) void k_dense_mc(DenseSeg s, const T* __restrict__ M,
-                                                                 const T* __restrict__ v1,
-                                                                 const T* __restrict__ v2,
-                                                                 T* __restrict__ out) {
+                                                                 const V* __restrict__ v1,
+                                                                 const V* __restrict__ v2,
+                                                                 V* __restrict__ out) {
   static_assert(K <= 16, "one column per matrix column");
   __shared__ T part[kDenseMcWaves][16][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int rows = s.nr * D, row0 = blockIdx.x * 16;
   const T* m = M + s.m0 + static_cast<int64_t>(min(row0 + (lane & 15), rows - 1)) * s.ld;
   typename Mfma16<T>::Acc acc = {T(0), T(0), T(0), T(0)};
-  dense_mc_input<T, D, K>(m, v1, s.a0, s.na, wave, lane, acc);
+  dense_mc_input<V, T, D, K>(m, v1, s.a0, s.na, wave, lane, acc);
   if (s.nc > 0)
-    dense_mc_input<T, D, K>(m + DenseShape<T>::pad(s.na * D), v2, s.c0, s.nc, wave, lane, acc);
+    dense_mc_input<V, T, D, K>(m + DenseShape<T>::pad(s.na * D), v2, s.c0, s.nc, wave, lane, acc);
 #pragma unroll
   for (int q = 0; q < 4; ++q) part[wave][Mfma16<T>::row(lane, q)][lane & 15] = acc[q];
   __syncthreads();
@@ -208,7 +212,7 @@ __global__ __launch_bounds__(64 * kDenseMcWaves) void k_dense_mc(DenseSeg s, con
   T sum = part[0][r][n];
 #pragma unroll
   for (int w = 1; w < kDenseMcWaves; ++w) sum += part[w][r][n];
-  out[(static_cast<int64_t>(s.r0 + row / D) * K + n) * D + row % D] = sum;
+  out[(static_cast<int64_t>(s.r0 + row / D) * K + n) * D + row % D] = static_cast<V>(sum);
 }
 
 // ---- construction ---------------------------------------------------------

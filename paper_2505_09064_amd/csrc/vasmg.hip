@@ -187,7 +187,8 @@ struct vasmg_ctx {
   // bottom_lo.. (dense[0]) and, when dense_lo < bottom_lo, R (dense[1]) and
   // [S Q] (dense[2]) of levels dense_lo .. bottom_lo - 1; -1 when the cycle has none
   struct DenseTable {
-    void* M = nullptr;              // V-cycle precision
+    void* M = nullptr;              // dense[0]: FP64, the others: V-cycle precision
+    int bytes = 0;                  // per value
     dev::DenseSeg one;              // the only segment of a single problem
     dev::DenseSeg* segs = nullptr;  // packed: one per part
     int nseg = 1, max_rows = 0, max_ld = 0;
@@ -783,6 +784,7 @@ std::vector<double> coarse_inverse(const std::vector<double>& Lf, int64_t n) {
 }
 
 void select_bottom(vasmg_ctx& C);
+bool table64(const vasmg_ctx& C, int l);
 
 void upload_all(vasmg_ctx& C) {
   const int nl = static_cast<int>(C.H.levels.size());
@@ -796,7 +798,8 @@ void upload_all(vasmg_ctx& C) {
     const bool need32 = C.vc32 && vasmg;
     std::vector<int> inv_next;
     if (l < C.L) inv_next = device_inverse(C, l + 1);
-    upload_level(C, l, need32, need64, inv_next);
+    upload_level(C, l, need32, need64 || table64(C, l), inv_next);
+    if (!need64) C.lev[l].has64 = false;   // the FP64 values serve the construction of B only
   }
   const int T = C.vc32 ? 4 : 8;
   for (int l = 0; l <= last; ++l) {
@@ -959,7 +962,7 @@ void select_bottom(vasmg_ctx& C) {
   // the kernel restricts into (and prolongs from) the coarsest level's DOFs in LDS
   if (static_cast<int64_t>(C.lev[C.L - 1].nnext) * C.d != C.n_coarse || C.n_coarse > dev::kCoarseInvMax)
     return;
-  const int tb = C.lev[C.L - 1].has64 ? 8 : 4;
+  const int tb = C.vc32 ? 4 : 8;
   const int maxlev = C.opt.cycle == VASMG_CYCLE_W ? 1 : dev::kBottomLevels;
   auto fits = [&](const DevLevel& lv) {
     if (!lv.cells || lv.blocks) return false;
@@ -1299,9 +1302,12 @@ void launch_dense(const vasmg_ctx& C, int which, const T* v1, const T* v2, T* ou
   const int* lo = C.dense_map[0].list;
   const int* hi = C.dense_map[1].list;
   const dim3 grid(grid_for(t.max_rows, dev::kDenseWaves), t.nseg), blk(64 * dev::kDenseWaves);
-  hipLaunchKernelGGL((dev::k_dense<T, D>), grid, blk, t.max_ld * sizeof(T), st, t.one, t.segs,
-                     static_cast<const T*>(t.M), v1, which == 0 ? lo : hi, v2, lo, out,
-                     which == 2 ? hi : lo);
+  if (which == 0)
+    hipLaunchKernelGGL((dev::k_dense<T, double, D>), grid, blk, t.max_ld * sizeof(double), st, t.one,
+                       t.segs, static_cast<const double*>(t.M), v1, lo, v2, lo, out, lo);
+  else
+    hipLaunchKernelGGL((dev::k_dense<T, T, D>), grid, blk, t.max_ld * sizeof(T), st, t.one, t.segs,
+                       static_cast<const T*>(t.M), v1, hi, v2, lo, out, which == 2 ? hi : lo);
 }
 
 // One V-cycle: lev[0].b -> lev[0].x (Algorithm 3, recursive, zero initial guess).
@@ -1339,12 +1345,12 @@ void enqueue_level(vasmg_ctx& C, int l, bool zero_guess, const int* done, hipStr
     T* bl = static_cast<T*>(C.lev[lo].b);
     T* xl = static_cast<T*>(C.lev[lo].x);
     if (l < lo)
-      run_phase(prof, "dense_down", l, 1, C.dense[1].elems * static_cast<double>(tb),
+      run_phase(prof, "dense_down", l, 1, C.dense[1].elems * static_cast<double>(C.dense[1].bytes),
                 [&] { launch_dense<T, D>(C, 1, b, nullptr, bl, st); });
-    run_phase(prof, "bottom", lo, 1, C.dense[0].elems * static_cast<double>(tb),
+    run_phase(prof, "bottom", lo, 1, C.dense[0].elems * static_cast<double>(C.dense[0].bytes),
               [&] { launch_dense<T, D>(C, 0, bl, nullptr, xl, st); });
     if (l < lo)
-      run_phase(prof, "dense_up", l, 1, C.dense[2].elems * static_cast<double>(tb),
+      run_phase(prof, "dense_up", l, 1, C.dense[2].elems * static_cast<double>(C.dense[2].bytes),
                 [&] { launch_dense<T, D>(C, 2, b, xl, x, st); });
     return;
   }
@@ -2111,9 +2117,14 @@ template <typename T, int D, int K>
 void launch_dense_mc(const vasmg_ctx& C, int which, const void* v1, const void* v2, void* out,
                      hipStream_t st) {
   const vasmg_ctx::DenseTable& t = C.dense[which];
-  hipLaunchKernelGGL((dev::k_dense_mc<T, D, K>), dim3(grid_for(t.max_rows, 16)),
-                     dim3(64 * dev::kDenseMcWaves), 0, st, t.one, static_cast<const T*>(t.M),
-                     static_cast<const T*>(v1), static_cast<const T*>(v2), static_cast<T*>(out));
+  const dim3 grid(grid_for(t.max_rows, 16)), blk(64 * dev::kDenseMcWaves);
+  const T *a = static_cast<const T*>(v1), *b = static_cast<const T*>(v2);
+  if (which == 0)
+    hipLaunchKernelGGL((dev::k_dense_mc<T, double, D, K>), grid, blk, 0, st, t.one,
+                       static_cast<const double*>(t.M), a, b, static_cast<T*>(out));
+  else
+    hipLaunchKernelGGL((dev::k_dense_mc<T, T, D, K>), grid, blk, 0, st, t.one,
+                       static_cast<const T*>(t.M), a, b, static_cast<T*>(out));
 }
 
 template <typename T, int D, int K>
@@ -2354,19 +2365,48 @@ std::vector<int64_t> part_offsets(const vasmg_ctx& C, int l) {
   return {0, C.H.levels[l].n};
 }
 
-// Elements of the tables that start at level ld over a bottom of vertex
-// offsets `lo` (padding included); -1 if a part is too large.
-int64_t dense_elems(const vasmg_ctx& C, const std::vector<int64_t>& hi, const std::vector<int64_t>& lo,
-                    bool split) {
-  const int64_t Q = C.vc32 ? 4 : 2;
-  auto pad = [&](int64_t n) { return (n + Q - 1) / Q * Q; };
-  int64_t e = 0;
+// Bytes of the tables that start at level ld over a bottom of vertex offsets `lo`
+// (padding included); -1 if a part is too large.
+int64_t dense_table_bytes(const vasmg_ctx& C, const std::vector<int64_t>& hi,
+                          const std::vector<int64_t>& lo, bool split) {
+  const int64_t tb = C.vc32 ? 4 : 8;
+  auto row = [](int64_t n, int64_t bytes) { return (n * bytes + 15) / 16 * 16; };
+  int64_t b = 0;
   for (size_t p = 0; p + 1 < hi.size(); ++p) {
     const int64_t n = (hi[p + 1] - hi[p]) * C.d, m = (lo[p + 1] - lo[p]) * C.d;
     if (n > kDenseMaxDofs || m > kDenseMaxDofs) return -1;
-    e += m * pad(m) + (split ? m * pad(n) + n * (pad(n) + pad(m)) : 0);
+    b += m * row(m, 8) + (split ? m * row(n, tb) + n * (row(n, tb) + row(m, tb)) : 0);
   }
-  return e;
+  return b;
+}
+
+// Whether the handle's cycle and size admit tables at all.
+bool dense_possible(const vasmg_ctx& C) {
+  return dense_wanted(C) && C.opt.preconditioner == VASMG_PRECOND_VASMG &&
+         C.opt.smoother == VASMG_SMOOTHER_GS && C.opt.n_pre >= 1 && C.H.levels.size() >= 3 &&
+         C.H.n_coarse_dofs <= dev::kCoarseInvMax;
+}
+
+// FP32 cycle: whether level l may lie in the fused bottom, whose table is built from
+// FP64 values (select_bottom's limits, before the levels are laid out).
+bool table64(const vasmg_ctx& C, int l) {
+  const int L = static_cast<int>(C.H.levels.size()) - 1;
+  return C.vc32 && dense_possible(C) && l >= 1 && l < L && L - l <= dev::kBottomLevels &&
+         dev::bottom_vec_elems(static_cast<int>(C.H.levels[l].n), C.DP) * 4 <= dev::kBottomLds;
+}
+
+// Vectors of one column batch of levels l0 .. l1 (the last one: b and x only).
+int64_t dense_batch_bytes(const vasmg_ctx& C, int l0, int l1, int64_t value) {
+  int64_t b = 0;
+  for (int l = l0; l <= l1; ++l)
+    b += C.H.levels[l].n * dev::kDenseCols * C.d * value * (l == l1 ? 2 : 4);
+  return b;
+}
+
+// Column batches per chunk, within the transient vectors' bound.
+int dense_chunk(int64_t cols, int64_t batch_bytes) {
+  return static_cast<int>(std::min<int64_t>((cols + dev::kDenseCols - 1) / dev::kDenseCols,
+                                            std::max<int64_t>(1, kDenseWorkBytes / batch_bytes)));
 }
 
 // Upper bound of the tables' bytes before the levels are on the device (any
@@ -2374,22 +2414,18 @@ int64_t dense_elems(const vasmg_ctx& C, const std::vector<int64_t>& hi, const st
 // transient vectors; 0 when the cycle takes none.
 int64_t dense_bytes_bound(const vasmg_ctx& C, int64_t* work) {
   *work = 0;
+  if (!dense_possible(C)) return 0;
   const int L = static_cast<int>(C.H.levels.size()) - 1;
-  if (!dense_wanted(C) || C.opt.preconditioner != VASMG_PRECOND_VASMG ||
-      C.opt.smoother != VASMG_SMOOTHER_GS || C.opt.n_pre < 1 || L < 2)
-    return 0;
   for (int l = 1; l < L; ++l) {
-    const int64_t e = dense_elems(C, part_offsets(C, l), part_offsets(C, std::min(l + 1, L - 1)), true);
-    if (e < 0) continue;
-    int64_t per_batch = 0, part = 0;   // vectors of one column batch, the largest part
-    for (int q = l; q <= L; ++q)
-      per_batch += C.H.levels[q].n * dev::kDenseCols * C.d * (C.vc32 ? 4 : 8) * 4;
-    const std::vector<int64_t> off = part_offsets(C, l);
-    for (size_t p = 0; p + 1 < off.size(); ++p) part = std::max(part, off[p + 1] - off[p]);
-    *work = std::min(std::max(kDenseWorkBytes, per_batch),
-                     (2 * part * C.d / dev::kDenseCols + 1) * per_batch);
+    const std::vector<int64_t> off = part_offsets(C, l), next = part_offsets(C, std::min(l + 1, L - 1));
+    const int64_t one = dense_table_bytes(C, off, off, false), split = dense_table_bytes(C, off, next, true);
+    if (one < 0 || split < 0) continue;
+    int64_t part = 0;
+    for (size_t p = 0; p + 1 < off.size(); ++p) part = std::max(part, (off[p + 1] - off[p]) * C.d);
+    const int64_t batch = dense_batch_bytes(C, l, L, 8);
+    *work = dense_chunk(2 * part, batch) * batch;
     const int64_t rows = C.H.levels[l].n * 12;   // part order, packed only
-    return std::min(e * (C.vc32 ? 4 : 8), kDenseMaxBytes) + (C.nseg > 0 ? 2 * rows + 1024 * C.nseg : 0);
+    return std::min(std::max(one, split), kDenseMaxBytes) + (C.nseg > 0 ? 2 * rows + 1024 * C.nseg : 0);
   }
   return 0;
 }
@@ -2433,19 +2469,53 @@ void dense_up(vasmg_ctx& C, std::vector<DenseWork>& w, int l0, int l1, int nb, h
   }
 }
 
+// A chunk's vectors of levels l0 .. l1 in the slab.
+template <typename T, int D>
+std::vector<DenseWork> dense_vectors(const vasmg_ctx& C, int l0, int l1, int nb, char* slab, hipStream_t st) {
+  std::vector<DenseWork> w(C.L + 1);
+  T* p = reinterpret_cast<T*>(slab);
+  for (int l = l0; l <= l1; ++l) {
+    const int64_t len = static_cast<int64_t>(C.lev[l].n) * dev::kDenseCols * D * nb;
+    for (int q = 0; q < (l == l1 ? 2 : 4); ++q) {
+      w[l].v[q] = p;
+      p += len;
+    }
+    // the zero padding blocks of a row multiply the row's own entry of x before
+    // the first sweep has written it
+    launch_fill<T>(static_cast<T*>(w[l].v[1]), len, T(0), st);
+  }
+  return w;
+}
+
+// Unit vectors c0 - shift, ... in vector v of level l (q: its part order).
+template <typename T, int D>
+void dense_unit(const vasmg_ctx& C, const std::vector<DenseWork>& w, int l, int q, int v, int nb, int col0,
+                int shift, hipStream_t st) {
+  const int64_t e = static_cast<int64_t>(C.lev[l].n) * dev::kDenseCols * D;
+  hipLaunchKernelGGL((dev::k_dense_unit<T, D>), dim3(grid_for(e, dev::kBlock), nb), dim3(dev::kBlock), 0, st,
+                     C.lev[l].n, C.dense_map[q].loc, col0, shift, static_cast<T*>(w[l].v[v]));
+}
+
+template <typename T, int D>
+void dense_extract(const vasmg_ctx& C, const std::vector<DenseWork>& w, int which, int l, int q, int v, int nb,
+                   int col0, int shift, int second, hipStream_t st) {
+  const int64_t e = static_cast<int64_t>(C.lev[l].n) * dev::kDenseCols * D;
+  const vasmg_ctx::DenseTable& t = C.dense[which];
+  hipLaunchKernelGGL((dev::k_dense_extract<T, D>), dim3(grid_for(e, dev::kBlock), nb), dim3(dev::kBlock), 0, st,
+                     C.lev[l].n, C.dense_map[q], t.one, t.segs, col0, shift, second,
+                     static_cast<const T*>(w[l].v[v]), static_cast<T*>(t.M));
+}
+
 template <typename T, int D>
 void build_dense(vasmg_ctx& C, hipStream_t st) {
   constexpr int K = dev::kDenseCols;
-  using Shape = dev::DenseShape<T>;
   const int lo = C.bottom_lo, L = C.L;
   const std::vector<int64_t> off_lo = part_offsets(C, lo);
-  auto fits = [&](int64_t e) {
-    return e >= 0 && e * static_cast<int64_t>(sizeof(T)) <= kDenseMaxBytes;
-  };
-  if (!fits(dense_elems(C, off_lo, off_lo, false))) return;
+  auto fits = [&](int64_t bytes) { return bytes >= 0 && bytes <= kDenseMaxBytes; };
+  if (!fits(dense_table_bytes(C, off_lo, off_lo, false))) return;
   int ld = lo;
   while (ld - 1 >= 1 && C.lev[ld - 1].cells && !C.lev[ld - 1].blocks &&
-         fits(dense_elems(C, part_offsets(C, ld - 1), off_lo, true)))
+         fits(dense_table_bytes(C, part_offsets(C, ld - 1), off_lo, true)))
     --ld;
   const std::vector<int64_t> off_hi = part_offsets(C, ld);
   const int np = static_cast<int>(off_lo.size()) - 1;
@@ -2468,10 +2538,11 @@ void build_dense(vasmg_ctx& C, hipStream_t st) {
       C.dense_map[q].seg = C.upload(seg);
     }
   }
-  auto table = [&](int which, const std::vector<int64_t>& ro, const std::vector<int64_t>& ao,
+  auto table = [&](int which, int bytes, const std::vector<int64_t>& ro, const std::vector<int64_t>& ao,
                    const std::vector<int64_t>* co) {
     vasmg_ctx::DenseTable& t = C.dense[which];
     std::vector<dev::DenseSeg> segs(np);
+    auto pad = [&](int n) { return (n * bytes + 15) / 16 * 16 / bytes; };
     int64_t m = 0;
     for (int p = 0; p < np; ++p) {
       dev::DenseSeg& g = segs[p];
@@ -2482,7 +2553,7 @@ void build_dense(vasmg_ctx& C, hipStream_t st) {
       g.na = static_cast<int>(ao[p + 1] - ao[p]);
       g.c0 = co ? static_cast<int>((*co)[p]) : 0;
       g.nc = co ? static_cast<int>((*co)[p + 1] - (*co)[p]) : 0;
-      g.ld = Shape::pad(g.na * D) + Shape::pad(g.nc * D);
+      g.ld = pad(g.na * D) + pad(g.nc * D);
       m += static_cast<int64_t>(g.nr) * D * g.ld;
       t.max_rows = std::max(t.max_rows, g.nr * D);
       t.max_ld = std::max(t.max_ld, g.ld);
@@ -2490,80 +2561,55 @@ void build_dense(vasmg_ctx& C, hipStream_t st) {
     t.one = segs[0];
     t.nseg = np;
     t.elems = m;
+    t.bytes = bytes;
     if (C.nseg > 0) t.segs = C.upload(segs);
+    t.M = C.dalloc<char>(m * bytes);
+    if (bytes == 8)   // the row padding
+      launch_fill<double>(static_cast<double*>(t.M), m, 0.0, st);
+    else
+      launch_fill<float>(static_cast<float*>(t.M), m, 0.0f, st);
   };
-  table(0, off_lo, off_lo, nullptr);
+  table(0, 8, off_lo, off_lo, nullptr);
   if (ld < lo) {
-    table(1, off_lo, off_hi, nullptr);
-    table(2, off_hi, off_hi, &off_lo);
-  }
-  {
-    const int64_t m = C.dense[0].elems + C.dense[1].elems + C.dense[2].elems;
-    T* M = C.dalloc<T>(m);
-    launch_fill<T>(M, m, T(0), st);   // the row padding
-    for (auto& t : C.dense) {
-      t.M = M;
-      M += t.elems;
-    }
+    table(1, sizeof(T), off_lo, off_hi, nullptr);
+    table(2, sizeof(T), off_hi, off_hi, &off_lo);
   }
   auto max_part = [&](const std::vector<int64_t>& off) {
     int64_t m = 0;
     for (int p = 0; p < np; ++p) m = std::max(m, off[p + 1] - off[p]);
     return static_cast<int>(m) * D;
   };
-  const int n_lo = max_part(off_lo), n_hi = max_part(off_hi);
-  // column batches per chunk, within the transient vectors' bound
-  int64_t per_batch = 0;
-  for (int l = ld; l <= L; ++l)
-    per_batch += static_cast<int64_t>(C.lev[l].n) * K * D * sizeof(T) * (l == L ? 2 : 4);
-  const int cols = std::max(n_lo, ld < lo ? n_hi + n_lo : 0);
-  const int nbmax = static_cast<int>(
-      std::min<int64_t>((cols + K - 1) / K, std::max<int64_t>(1, kDenseWorkBytes / per_batch)));
+  const int n_lo = max_part(off_lo), n_hi = max_part(off_hi), n_up = ld < lo ? n_hi + n_lo : 0;
+  const int64_t batch_lo = dense_batch_bytes(C, lo, L, 8), batch_up = dense_batch_bytes(C, ld, lo, sizeof(T));
+  const int nb_lo = dense_chunk(n_lo, batch_lo), nb_up = n_up ? dense_chunk(n_up, batch_up) : 0;
   TempDev tmp(st, C.alloc_stream != nullptr);
-  std::vector<DenseWork> w(L + 1);
-  T* slab = tmp.get<T>(per_batch / sizeof(T) * nbmax);   // one: freeing each on its own takes longer
-  for (int l = ld; l <= L; ++l) {
-    const int64_t len = static_cast<int64_t>(C.lev[l].n) * K * D * nbmax;
-    for (int q = 0; q < (l == L ? 2 : 4); ++q) {
-      w[l].v[q] = slab;
-      slab += len;
+  // one slab: freeing the vectors one by one takes longer
+  char* slab = tmp.get<char>(std::max(batch_lo * nb_lo, batch_up * nb_up));
+  {
+    std::vector<DenseWork> w = dense_vectors<double, D>(C, lo, L, nb_lo, slab, st);
+    for (int c0 = 0; c0 < n_lo; c0 += nb_lo * K) {   // B: the cycle from level lo on unit vectors
+      const int nb = std::min(nb_lo, (n_lo - c0 + K - 1) / K);
+      dense_unit<double, D>(C, w, lo, 0, 0, nb, c0, 0, st);
+      dense_down<double, D>(C, w, lo, L, nb, st);
+      hipLaunchKernelGGL((dev::k_coarse_apply_mc<double, D, K, D>), dim3(1, nb), dim3(dev::kBlock), 0, st,
+                         static_cast<int>(C.n_coarse), C.cinv, static_cast<const double*>(w[L].v[0]),
+                         static_cast<double*>(w[L].v[1]));
+      dense_up<double, D>(C, w, lo, L, nb, st);
+      dense_extract<double, D>(C, w, 0, lo, 0, 1, nb, c0, 0, 0, st);
     }
-    // the zero padding blocks of a row multiply the row's own entry of x before
-    // the first sweep has written it
-    launch_fill<T>(static_cast<T*>(w[l].v[1]), len, T(0), st);
-  }
-  auto unit = [&](int l, int q, int v, int nb, int col0, int shift) {
-    const int64_t e = static_cast<int64_t>(C.lev[l].n) * K * D;
-    hipLaunchKernelGGL((dev::k_dense_unit<T, D>), dim3(grid_for(e, dev::kBlock), nb), dim3(dev::kBlock), 0,
-                       st, C.lev[l].n, C.dense_map[q].loc, col0, shift, static_cast<T*>(w[l].v[v]));
-  };
-  auto extract = [&](int which, int l, int q, int v, int nb, int col0, int shift, int second) {
-    const int64_t e = static_cast<int64_t>(C.lev[l].n) * K * D;
-    hipLaunchKernelGGL((dev::k_dense_extract<T, D>), dim3(grid_for(e, dev::kBlock), nb), dim3(dev::kBlock),
-                       0, st, C.lev[l].n, C.dense_map[q], C.dense[which].one, C.dense[which].segs, col0,
-                       shift, second, static_cast<const T*>(w[l].v[v]), static_cast<T*>(C.dense[which].M));
-  };
-  const int nco = static_cast<int>(C.n_coarse);
-  for (int c0 = 0; c0 < n_lo; c0 += nbmax * K) {   // B: the cycle from level lo on unit vectors
-    const int nb = std::min(nbmax, (n_lo - c0 + K - 1) / K);
-    unit(lo, 0, 0, nb, c0, 0);
-    dense_down<T, D>(C, w, lo, L, nb, st);
-    hipLaunchKernelGGL((dev::k_coarse_apply_mc<T, D, K, D>), dim3(1, nb), dim3(dev::kBlock), 0, st, nco,
-                       C.cinv, static_cast<const T*>(w[L].v[0]), static_cast<T*>(w[L].v[1]));
-    dense_up<T, D>(C, w, lo, L, nb, st);
-    extract(0, lo, 0, 1, nb, c0, 0, 0);
   }
   if (ld < lo) {
     // R and S: unit vectors in b_ld with x_lo = 0; Q: unit vectors in x_lo with b_ld = 0
-    for (int c0 = 0; c0 < n_hi + n_lo; c0 += nbmax * K) {
-      const int nb = std::min(nbmax, (n_hi + n_lo - c0 + K - 1) / K);
-      unit(ld, 1, 0, nb, c0, 0);
+    std::vector<DenseWork> w = dense_vectors<T, D>(C, ld, lo, nb_up, slab, st);
+    for (int c0 = 0; c0 < n_up; c0 += nb_up * K) {
+      const int nb = std::min(nb_up, (n_up - c0 + K - 1) / K);
+      dense_unit<T, D>(C, w, ld, 1, 0, nb, c0, 0, st);
       dense_down<T, D>(C, w, ld, lo, nb, st);
-      extract(1, lo, 0, 0, nb, c0, 0, 0);
-      unit(lo, 0, 1, nb, c0, n_hi);
+      dense_extract<T, D>(C, w, 1, lo, 0, 0, nb, c0, 0, 0, st);
+      dense_unit<T, D>(C, w, lo, 0, 1, nb, c0, n_hi, st);
       dense_up<T, D>(C, w, ld, lo, nb, st);
-      extract(2, ld, 1, 1, nb, c0, 0, 0);
-      extract(2, ld, 1, 1, nb, c0, n_hi, 1);
+      dense_extract<T, D>(C, w, 2, ld, 1, 1, nb, c0, 0, 0, st);
+      dense_extract<T, D>(C, w, 2, ld, 1, 1, nb, c0, n_hi, 1, st);
     }
   }
   HIP_CHECK(hipGetLastError());
@@ -2731,7 +2777,7 @@ int64_t estimate_device_bytes(const vasmg_ctx& C) {
   for (int l = 0; l <= last; ++l) {
     const Level& lv = H.levels[l];
     const int64_t n = lv.n, nb = lv.A.nnzb();
-    const bool need64 = l == 0 || !C.vc32, need32 = C.vc32 && vasmg;
+    const bool need64 = l == 0 || !C.vc32 || table64(C, l), need32 = C.vc32 && vasmg;
     const int64_t vb = (need64 ? 8 : 0) + (need32 ? 4 : 0);
     b += n * 4 + 2 * (n + 1) * 4 + nb * (4 + dd * vb);
     if (l > 0 && l < L)

@@ -154,3 +154,27 @@ def test_cells_without_off_cell_blocks(prec):
                 s.gs_sweep_device(l, prec, back, b, y)
             assert torch.isfinite(y).all()
         s.free()
+
+
+@pytest.mark.parametrize("make", [lambda: small3d(9, seed=3), lambda: small2d(21, seed=3, fix="x0")])
+def test_coarsest_solve_of_the_fp32_cycle_is_fp64(make):
+    """The bottom's table, which holds the coarsest solve, has FP64 values in the
+    FP32 cycle (its bytes in the profile), and on a slender body (8 : 1, an
+    ill-conditioned coarsest operator) the cycle is as near to the FP64 one as the
+    oracle's FP32 mode, whose coarsest solve is FP64: 4 times its distance."""
+    m = make()
+    m.coords[:, 0] *= 8.0
+    o = Oracle(m.coords, m.elems, m.E, m.nu, m.fixed)
+    s = V.Solver.from_mesh(m, precision=V.FP32_PRECOND)
+    bottom = [p for p in s.profile_iteration(1) if p["name"] == "bottom"][0]
+    n = s.level_info(bottom["level"])["n_vertices"] * m.dim
+    assert bottom["bytes"] == n * ((8 * n + 15) // 16 * 16)
+    nf = o.A[0].shape[0] // m.dim
+    rng = np.random.default_rng(6)
+    for r in (np.ones(nf * m.dim), rng.normal(size=nf * m.dim), o.A[0] @ rng.normal(size=nf * m.dim)):
+        z = torch.zeros((nf, m.dim), dtype=torch.float64, device="cuda")
+        s.apply_precond_device(torch.from_numpy(r.reshape(nf, m.dim)).cuda(), z)
+        ref, ref32 = (o.apply_precond(r, precision=p) for p in ("fp64", "fp32"))
+        gap = np.linalg.norm(ref32 - ref)
+        assert np.linalg.norm(z.cpu().numpy().ravel() - ref) <= 4 * gap
+    s.free()
