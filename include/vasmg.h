@@ -274,7 +274,9 @@ const char* vasmg_last_error(void);
  * own stream), admitted first in first out as soon as one of `slots`
  * device slots is free and its device bytes (vasmg_device_bytes) fit the HBM
  * budget next to the requests already resident, then uploaded, solved and
- * freed on the slot's own stream; requests overlap on the device. Every request
+ * freed on the slot's own stream; requests overlap on the device. The dense
+ * tables of a request's small levels are left out where they would take more
+ * than an eighth of the budget divided by the slots (and more than 4 MiB). Every request
  * uses the server's options (autotuning off, so a result does not depend on
  * what else is running; block_rhs ignored). Thread-safe.
  * ------------------------------------------------------------------------- */

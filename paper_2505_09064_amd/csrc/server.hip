@@ -30,7 +30,8 @@
 namespace vasmg {
 void set_host_threads(int n);   // setup.cpp: OpenMP threads of the calling thread's setups
 int host_thread_budget();       // setup.cpp: the default OpenMP team size
-int64_t admission_bytes(vasmg_handle h, int64_t budget);   // vasmg.hip
+int64_t plain_bytes(vasmg_handle h);                       // vasmg.hip
+int64_t plan_tables(vasmg_handle h, int64_t allowance);    // vasmg.hip
 }
 
 namespace {
@@ -50,7 +51,7 @@ struct Request {
   std::vector<uint8_t> fixed;
   double rtol = 1e-6;
   vasmg_handle h = nullptr;
-  int64_t bytes = 0;
+  int64_t bytes = 0, tables = 0;       // device bytes: without dense tables, what they add
   int64_t dofs = 0, coarse_dofs = 0;   // fine and coarsest-level DOFs of the hierarchy
   bool done = false;
   vasmg_request_result res{};
@@ -65,6 +66,14 @@ struct vasmg_server {
   Clock::time_point t0;
   int device = 0;
   int64_t budget = 0;
+
+  // What the dense tables of one slot's request or pack may add to its device bytes:
+  // all slots' together an eighth of the budget (or 4 MiB each: a few hundred DOFs).
+  // Fixed per server, so that whether a request has tables does not depend on what
+  // else is running.
+  int64_t table_allowance() const {
+    return std::max(budget / 8 / cfg.slots, static_cast<int64_t>(4) << 20);
+  }
 
   std::mutex mu;
   std::condition_variable cv;
@@ -127,8 +136,11 @@ struct vasmg_server {
       vasmg_handle h = nullptr;
       int st = vasmg_setup(&m, &o, &h);
       if (st != VASMG_OK) note(r, "setup", vasmg_last_error());
-      int64_t bytes = 0;
-      if (st == VASMG_OK) bytes = vasmg::admission_bytes(h, budget);
+      int64_t bytes = 0, tables = 0;
+      if (st == VASMG_OK) {
+        bytes = vasmg::plain_bytes(h);
+        if (bytes <= budget) tables = vasmg::plan_tables(h, std::min(table_allowance(), budget - bytes));
+      }
       if (st == VASMG_OK) {
         int32_t nl = 0, dim = 0;
         int64_t nd = 0, nvc = 0, nb = 0, pn = 0;
@@ -155,7 +167,8 @@ struct vasmg_server {
       }
       r->h = h;
       r->bytes = bytes;
-      r->res.device_bytes = bytes;
+      r->tables = tables;
+      r->res.device_bytes = bytes + tables;
       admit_q.push_back(r);
       cv.notify_all();
     }
@@ -215,6 +228,9 @@ struct vasmg_server {
 
   // Small requests packed into one handle (vasmg_pack): one upload, one solve
   // with a PCG recurrence per request, results split back. statuses[i] per request.
+  // held: the parts' bytes without tables, and the first one's tables; the pack's own
+  // tables are taken if they fit the slot's allowance and what is free now (a
+  // pack's results equal the requests' alone to rounding).
   void run_pack(hipStream_t st, bool have_stream, const std::vector<ReqPtr>& batch,
                 std::vector<int>& statuses, int64_t& held) {
     const int n = static_cast<int>(batch.size());
@@ -229,6 +245,15 @@ struct vasmg_server {
     vasmg_handle ph = nullptr;
     int status = have_stream ? vasmg_pack(hs.data(), n, &ph) : VASMG_EDEVICE;
     const char* what = "pack";
+    if (status == VASMG_OK) {
+      std::lock_guard<std::mutex> g(mu);
+      const int64_t spare = batch[0]->tables;
+      const int64_t more =
+          vasmg::plan_tables(ph, std::min(table_allowance(), budget - in_use + spare)) - spare;
+      in_use += more;
+      held += more;
+      peak = std::max(peak, in_use);
+    }
     if (status == VASMG_OK) {
       status = vasmg_upload(ph, st);
       what = "upload";
@@ -314,14 +339,15 @@ struct vasmg_server {
       {
         std::unique_lock<std::mutex> g(mu);
         cv.wait(g, [&] {
-          if (!admit_q.empty() && in_use + admit_q.front()->bytes <= budget) return true;
+          if (!admit_q.empty() && in_use + admit_q.front()->bytes + admit_q.front()->tables <= budget)
+            return true;
           return stop && admit_q.empty() && setup_q.empty() && setups_active == 0;
         });
         if (admit_q.empty()) break;        // stopping and nothing left to run
         const ReqPtr r0 = admit_q.front();
         admit_q.pop_front();
         batch.push_back(r0);
-        held = r0->bytes;
+        held = r0->bytes + r0->tables;
         if (packable(*r0)) {
           // small requests set up and waiting behind it join it: same dimension
           // and tolerance, their coarsest levels together within kPackCoarseMax
@@ -352,6 +378,7 @@ struct vasmg_server {
             if (timed_out) break;
           }
         }
+        if (batch.size() == 1) r0->bytes = held;
         in_use += held;
         peak = std::max(peak, in_use);
         running += static_cast<int>(batch.size());

@@ -195,7 +195,8 @@ struct vasmg_ctx {
     int64_t elems = 0;
   };
   int dense_lo = -1;
-  bool no_dense = false;            // left out (a server's budget)
+  bool no_dense = false;            // left out (a server's allowance: plan_tables)
+  int64_t dense_work = 0;           // bound of their transient vectors (0: kDenseWorkBytes)
   DenseTable dense[3];
   dev::DenseMap dense_map[2];       // vertices of bottom_lo and dense_lo in part order
   int64_t n_coarse = 0;
@@ -2345,7 +2346,12 @@ int solve_block(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d
 // table: its products would cost what its launches do.
 constexpr int64_t kDenseMaxDofs = 2304;
 constexpr int64_t kDenseMaxBytes = int64_t(256) << 20;
-constexpr int64_t kDenseWorkBytes = int64_t(384) << 20;   // transient vectors of one chunk
+// Transient vectors of one chunk of columns, and the least worth building with. Building
+// takes (ms; bound 384 / 96 / 32 / 16 MiB) 2.8 / 4.1 / 7.2 / 13 for the 1,980 DOFs
+// under a 9^3 mesh in FP64, 2.5 / 2.1 / 4.7 / 5.9 in FP32, 5.5 / 8 / 18 / 33 for a
+// pack of eight 3D parts.
+constexpr int64_t kDenseWorkBytes = int64_t(96) << 20;
+constexpr int64_t kDenseLeastWork = int64_t(16) << 20;
 // FP32 cycles in 2D take tables only up to this stiffness contrast of the mesh.
 // Another rounding of the preconditioner moves the solution of PCG little where it
 // converges in 10 to 20 products, and by 1e-9 and more where it takes 15 to 50 (200
@@ -2404,9 +2410,10 @@ int64_t dense_batch_bytes(const vasmg_ctx& C, int l0, int l1, int64_t value) {
 }
 
 // Column batches per chunk, within the transient vectors' bound.
-int dense_chunk(int64_t cols, int64_t batch_bytes) {
+int dense_chunk(const vasmg_ctx& C, int64_t cols, int64_t batch_bytes) {
+  const int64_t work = C.dense_work > 0 ? C.dense_work : kDenseWorkBytes;
   return static_cast<int>(std::min<int64_t>((cols + dev::kDenseCols - 1) / dev::kDenseCols,
-                                            std::max<int64_t>(1, kDenseWorkBytes / batch_bytes)));
+                                            std::max<int64_t>(1, work / batch_bytes)));
 }
 
 // Upper bound of the tables' bytes before the levels are on the device (any
@@ -2422,8 +2429,13 @@ int64_t dense_bytes_bound(const vasmg_ctx& C, int64_t* work) {
     if (one < 0 || split < 0) continue;
     int64_t part = 0;
     for (size_t p = 0; p + 1 < off.size(); ++p) part = std::max(part, (off[p + 1] - off[p]) * C.d);
-    const int64_t batch = dense_batch_bytes(C, l, L, 8);
-    *work = dense_chunk(2 * part, batch) * batch;
+    auto chunk = [&](int l0, int64_t cols, int64_t value) {
+      const int64_t batch = dense_batch_bytes(C, l0, L, value);
+      return dense_chunk(C, cols, batch) * batch;
+    };
+    int bottom = l;   // FP32 cycle: the FP64 vectors cover the fused bottom only
+    while (C.vc32 && bottom < L - 1 && !table64(C, bottom)) ++bottom;
+    *work = std::max(chunk(l, 2 * part, C.vc32 ? 4 : 8), chunk(bottom, part, 8));
     const int64_t rows = C.H.levels[l].n * 12;   // part order, packed only
     return std::min(std::max(one, split), kDenseMaxBytes) + (C.nseg > 0 ? 2 * rows + 1024 * C.nseg : 0);
   }
@@ -2581,7 +2593,7 @@ void build_dense(vasmg_ctx& C, hipStream_t st) {
   };
   const int n_lo = max_part(off_lo), n_hi = max_part(off_hi), n_up = ld < lo ? n_hi + n_lo : 0;
   const int64_t batch_lo = dense_batch_bytes(C, lo, L, 8), batch_up = dense_batch_bytes(C, ld, lo, sizeof(T));
-  const int nb_lo = dense_chunk(n_lo, batch_lo), nb_up = n_up ? dense_chunk(n_up, batch_up) : 0;
+  const int nb_lo = dense_chunk(C, n_lo, batch_lo), nb_up = n_up ? dense_chunk(C, n_up, batch_up) : 0;
   TempDev tmp(st, C.alloc_stream != nullptr);
   // one slab: freeing the vectors one by one takes longer
   char* slab = tmp.get<char>(std::max(batch_lo * nb_lo, batch_up * nb_up));
@@ -2765,7 +2777,7 @@ void upload_device(vasmg_ctx& C, hipStream_t alloc_stream) {
 // Upper bound of the device bytes upload_device will allocate, from the host
 // hierarchy (every stored block counted as off-diagonal, the transient copy of
 // the largest level's canonical operator included, 5% + 1 MiB margin).
-int64_t estimate_device_bytes(const vasmg_ctx& C) {
+int64_t estimate_device_bytes(const vasmg_ctx& C, bool tables = true) {
   const Hierarchy& H = C.H;
   const int d = C.d, dd = d * d, DP = C.DP, NU = (1 << d) * d;
   const bool vasmg = C.opt.preconditioner == VASMG_PRECOND_VASMG;
@@ -2777,7 +2789,7 @@ int64_t estimate_device_bytes(const vasmg_ctx& C) {
   for (int l = 0; l <= last; ++l) {
     const Level& lv = H.levels[l];
     const int64_t n = lv.n, nb = lv.A.nnzb();
-    const bool need64 = l == 0 || !C.vc32 || table64(C, l), need32 = C.vc32 && vasmg;
+    const bool need64 = l == 0 || !C.vc32 || (tables && table64(C, l)), need32 = C.vc32 && vasmg;
     const int64_t vb = (need64 ? 8 : 0) + (need32 ? 4 : 0);
     b += n * 4 + 2 * (n + 1) * 4 + nb * (4 + dd * vb);
     if (l > 0 && l < L)
@@ -2797,9 +2809,11 @@ int64_t estimate_device_bytes(const vasmg_ctx& C) {
     const Level& lv = H.levels[l];
     transient = std::max(transient, lv.A.nnzb() * (4 + dd * 8) + (lv.n + 1) * 8 + 6 * lv.n * 4);
   }
-  int64_t dense_work = 0;
-  b += dense_bytes_bound(C, &dense_work);
-  transient = std::max(transient, dense_work);
+  if (tables) {
+    int64_t dense_work = 0;
+    b += dense_bytes_bound(C, &dense_work);
+    transient = std::max(transient, dense_work);
+  }
   b += transient;
   const int64_t n0p = H.levels[0].n * DP;
   b += 6 * n0p * 8 + H.levels[0].n * 4 + H.n_coarse_dofs * H.n_coarse_dofs * 16;   // factor + inverse
@@ -2822,16 +2836,23 @@ bool device_available() {
 }  // namespace
 
 namespace vasmg {
-// Device bytes a server admits a host-built handle by. The dense tables are
-// left out (here and at the upload) when they would take the request over the
-// whole budget, so that what fits without them is still served.
-int64_t admission_bytes(vasmg_handle h, int64_t budget) {
-  int64_t b = estimate_device_bytes(*h);
-  if (b > budget && !h->no_dense) {
+// Device bytes of a host-built handle without dense tables.
+int64_t plain_bytes(vasmg_handle h) { return estimate_device_bytes(*h, false); }
+
+// What the tables and their construction add to them; with more than `allowance`
+// the upload leaves the tables out (0). The construction's vectors shrink to fit:
+// the tables' values do not depend on them.
+int64_t plan_tables(vasmg_handle h, int64_t allowance) {
+  const int64_t plain = plain_bytes(h);
+  h->dense_work = kDenseLeastWork;
+  int64_t extra = estimate_device_bytes(*h) - plain;
+  if (extra > allowance) {
     h->no_dense = true;
-    b = estimate_device_bytes(*h);
+    return 0;
   }
-  return b;
+  h->dense_work = std::min(kDenseWorkBytes, kDenseLeastWork + (allowance - extra) / 10 * 9);
+  extra = estimate_device_bytes(*h) - plain;
+  return extra;
 }
 }  // namespace vasmg
 
@@ -3198,7 +3219,6 @@ vasmg_status vasmg_pack(const vasmg_handle* parts, int32_t n_parts, vasmg_handle
     for (int i = 0; i < n_parts; ++i) {
       C->seg_vertex_off.push_back(C->seg_vertex_off.back() + parts[i]->H.n_mesh_vertices);
       C->seg_free_off.push_back(C->seg_free_off.back() + parts[i]->H.levels[0].n);
-      C->no_dense = C->no_dense || parts[i]->no_dense;
     }
     C->seg_level_off.resize(C->L + 1);
     for (int l = 0; l <= C->L; ++l) {   // a part shallower than l repeats its coarsest level

@@ -228,3 +228,24 @@ def test_packed_serving(precision):
     for group in by_admit.values():
         assert all(r["pack_size"] == len(group) for r in group)
         assert len({r["t_done_ms"] for r in group}) == 1
+
+
+def test_small_requests_pack_under_a_modest_budget():
+    """Eight small requests, each a few MiB of levels, under a budget of 1 GiB: the
+    dense tables and their construction (tens to hundreds of MiB a request) do not
+    keep them apart. One worker sets up, so that all wait while the first does."""
+    ms = [small3d(9, seed=i) for i in range(8)]
+    budget = 1 << 30
+    srv = V.Server(slots=1, setup_workers=1, pack_max_dofs=100000, pack_max_parts=8,
+                   pack_wait_ms=5000, hbm_budget_bytes=budget)
+    ids = [srv.submit(m, m.rhs[0], 1e-8) for m in ms]
+    got = [srv.wait(i) for i in ids]
+    st = srv.stats()
+    srv.close()
+    assert st["peak_bytes"] <= budget
+    assert max(res["pack_size"] for _, res in got) >= 6, [res["pack_size"] for _, res in got]
+    for m, (x, res) in zip(ms, got):
+        with V.Solver.from_mesh(m) as s:
+            xa, ia = s.solve(m.rhs[0], 1e-8)
+        assert res["status"] == V.OK and abs(res["info"]["iterations"] - ia["iterations"]) <= 1
+        assert np.linalg.norm(x - xa) / np.linalg.norm(xa) <= 1e-10
