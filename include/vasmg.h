@@ -213,6 +213,13 @@ vasmg_status vasmg_solve_noalloc(vasmg_handle h, const double* rhs, const double
  * ENOMEM, EDEVICE. On failure the handle stays unusable for solves. */
 vasmg_status vasmg_upload(vasmg_handle h, void* stream);
 
+/* Whether the upload of a hierarchy built with host_only = 1 tabulates the small
+ * levels of its cycle (default 1; the tables take 1 to 4 ms to build and up to 256
+ * MiB). on = 0: every level is launched, the last ones by the fused bottom kernel
+ * (a handle that solves once to a loose tolerance; the same results to rounding). A
+ * pack has none if one of its parts has none. EINVAL once uploaded. */
+vasmg_status vasmg_set_dense_tables(vasmg_handle h, int32_t on);
+
 /* Device bytes of the handle: allocated bytes once uploaded, else an upper
  * bound of what vasmg_upload will allocate (admission control). */
 vasmg_status vasmg_device_bytes(vasmg_handle h, int64_t* bytes);

@@ -195,6 +195,7 @@ struct vasmg_ctx {
     int64_t elems = 0;
   };
   int dense_lo = -1;
+  bool dense_off = false;           // not wanted (vasmg_set_dense_tables)
   bool no_dense = false;            // left out (a server's allowance: plan_tables)
   int64_t dense_work = 0;           // bound of their transient vectors (0: kDenseWorkBytes)
   DenseTable dense[3];
@@ -2361,7 +2362,7 @@ constexpr int64_t kDenseLeastWork = int64_t(16) << 20;
 constexpr double kDenseMaxContrast2d = 10.0;
 
 bool dense_wanted(const vasmg_ctx& C) {
-  return !C.no_dense && C.opt.cycle != VASMG_CYCLE_W &&
+  return !C.dense_off && !C.no_dense && C.opt.cycle != VASMG_CYCLE_W &&
          !(C.vc32 && C.d == 2 && C.H.contrast > kDenseMaxContrast2d);
 }
 
@@ -3219,6 +3220,7 @@ vasmg_status vasmg_pack(const vasmg_handle* parts, int32_t n_parts, vasmg_handle
     for (int i = 0; i < n_parts; ++i) {
       C->seg_vertex_off.push_back(C->seg_vertex_off.back() + parts[i]->H.n_mesh_vertices);
       C->seg_free_off.push_back(C->seg_free_off.back() + parts[i]->H.levels[0].n);
+      C->dense_off = C->dense_off || parts[i]->dense_off;
     }
     C->seg_level_off.resize(C->L + 1);
     for (int l = 0; l <= C->L; ++l) {   // a part shallower than l repeats its coarsest level
@@ -3306,6 +3308,15 @@ vasmg_status vasmg_upload(vasmg_handle h, void* stream) {
     g_last_error = "host allocation failed";
     return VASMG_ENOMEM;
   }
+}
+
+vasmg_status vasmg_set_dense_tables(vasmg_handle h, int32_t on) {
+  if (!h || !h->host_only || (on != 0 && on != 1)) {
+    g_last_error = "vasmg_set_dense_tables: needs a host-only handle and 0 or 1";
+    return VASMG_EINVAL;
+  }
+  h->dense_off = on == 0;
+  return VASMG_OK;
 }
 
 vasmg_status vasmg_device_bytes(vasmg_handle h, int64_t* bytes) {

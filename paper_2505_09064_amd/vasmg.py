@@ -31,7 +31,8 @@ EXPORTED = [
     "vasmg_last_error", "vasmg_hierarchy_info", "vasmg_level_info", "vasmg_export_level",
     "vasmg_tree_info", "vasmg_spmv_device", "vasmg_gs_sweep_device", "vasmg_restrict_device",
     "vasmg_prolong_device", "vasmg_apply_precond_device", "vasmg_profile_iteration",
-    "vasmg_upload", "vasmg_device_bytes", "vasmg_server_default_config", "vasmg_server_create",
+    "vasmg_upload", "vasmg_set_dense_tables", "vasmg_device_bytes",
+    "vasmg_server_default_config", "vasmg_server_create",
     "vasmg_server_submit", "vasmg_server_wait", "vasmg_server_stats", "vasmg_server_destroy",
     "vasmg_set_galerkin_window", "vasmg_solve_noalloc", "vasmg_setup_phases", "vasmg_pack",
     "vasmg_packed_info", "vasmg_solve_packed_device", "vasmg_solve_packed",
@@ -151,6 +152,7 @@ def lib():
             "vasmg_profile_iteration": (i32, [vp, i32, vp, C.POINTER(PhaseStat), i32,
                                               C.POINTER(i32)]),
             "vasmg_upload": (i32, [vp, vp]),
+            "vasmg_set_dense_tables": (i32, [vp, i32]),
             "vasmg_device_bytes": (i32, [vp, C.POINTER(i64)]),
             "vasmg_server_default_config": (i32, [C.POINTER(ServerConfig)]),
             "vasmg_server_create": (i32, [C.POINTER(ServerConfig), C.POINTER(vp)]),
@@ -337,6 +339,11 @@ class Solver:
         return out[0] if n_rhs == 1 else out
 
     # -- introspection ------------------------------------------------------
+    def set_dense_tables(self, on: bool) -> None:
+        """Whether the upload of this host-only handle (or of a pack that takes it as
+        a part) tabulates the small levels of its cycle."""
+        _check(lib().vasmg_set_dense_tables(self._h, int(on)))
+
     def hierarchy_info(self):
         nl, nd, dim = C.c_int32(), C.c_int64(), C.c_int32()
         _check(lib().vasmg_hierarchy_info(self._h, C.byref(nl), C.byref(nd), C.byref(dim)))
