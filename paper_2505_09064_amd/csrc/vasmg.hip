@@ -1488,11 +1488,9 @@ void enqueue_precond(vasmg_ctx& C, const int* done, hipStream_t st) {
 // -------------------------------------------------------------------------
 // PCG graphs
 // -------------------------------------------------------------------------
-template <int D>
-void enqueue_iter_A(vasmg_ctx& C, hipStream_t st) {
-  const DevLevel& l0 = C.lev[0];
-  const int* done = &C.sc->done;
-  const int np = launch_spmv<double, D>(l0, C.P, C.Q, C.partial, C.n_partial, done, st);
+// alpha from the SpMV's np partial sums; x, r updates; ||r||, the stopping test and the
+// report.
+void enqueue_update(vasmg_ctx& C, int np, hipStream_t st) {
   if (C.n0p <= dev::kSmallFlat) {
     const int n = static_cast<int>(C.n0p);
     if (C.vc32)
@@ -1513,6 +1511,12 @@ void enqueue_iter_A(vasmg_ctx& C, hipStream_t st) {
                        C.n0p, C.sc, C.P, C.Q, C.X, C.R, static_cast<double*>(nullptr), C.partial);
   hipLaunchKernelGGL((dev::k_finalize<dev::FIN_RES>), dim3(1), dim3(1024), 0, st, C.partial,
                      kFlatGrid, C.sc, C.mail);
+}
+
+template <int D>
+void enqueue_iter_A(vasmg_ctx& C, hipStream_t st) {
+  const int np = launch_spmv<double, D>(C.lev[0], C.P, C.Q, C.partial, C.n_partial, &C.sc->done, st);
+  enqueue_update(C, np, st);
 }
 
 // rho = r.z; beta; p = z + beta p
@@ -1717,11 +1721,10 @@ bool wait_reports(const int* mail, int n, int it, hipStream_t st) {
 // -------------------------------------------------------------------------
 // Packed problems: the shared SpMV and V-cycle, per-segment scalars
 // -------------------------------------------------------------------------
-// q = A p; alpha_s; x, r updates; ||r||_s, the stopping test and the report
+// alpha_s; x, r updates; ||r||_s, the stopping test and the report
 template <int D>
-void enqueue_packed_A(vasmg_ctx& C, hipStream_t st) {
+void enqueue_packed_update(vasmg_ctx& C, hipStream_t st) {
   constexpr int DP = dev::Pad<D>::value;
-  launch_spmv<double, D>(C.lev[0], C.P, C.Q, nullptr, 0, nullptr, st);
   if (C.vc32)
     hipLaunchKernelGGL((dev::k_seg_xr<float, DP>), dim3(C.nseg), dim3(dev::kSegBlock), 0, st, C.seg_ptr,
                        C.seg_rows, C.ssc, C.P, C.Q, C.X, C.R, static_cast<float*>(C.lev[0].b), C.mail);
@@ -1730,17 +1733,30 @@ void enqueue_packed_A(vasmg_ctx& C, hipStream_t st) {
                        C.seg_rows, C.ssc, C.P, C.Q, C.X, C.R, static_cast<double*>(nullptr), C.mail);
 }
 
-// z = B r (the whole packed V-cycle); rho_s, beta_s; p = z + beta_s p
+// rho_s, beta_s; p = z + beta_s p
 template <int D>
-void enqueue_packed_B(vasmg_ctx& C, hipStream_t st) {
+void enqueue_packed_direction(vasmg_ctx& C, hipStream_t st) {
   constexpr int DP = dev::Pad<D>::value;
-  enqueue_precond<D>(C, nullptr, st);
   if (C.vc32)
     hipLaunchKernelGGL((dev::k_seg_p<float, DP>), dim3(C.nseg), dim3(dev::kSegBlock), 0, st, C.seg_ptr,
                        C.seg_rows, C.ssc, C.R, static_cast<const float*>(C.lev[0].x), C.P);
   else
     hipLaunchKernelGGL((dev::k_seg_p<double, DP>), dim3(C.nseg), dim3(dev::kSegBlock), 0, st, C.seg_ptr,
                        C.seg_rows, C.ssc, C.R, static_cast<const double*>(C.lev[0].x), C.P);
+}
+
+// q = A p and the update
+template <int D>
+void enqueue_packed_A(vasmg_ctx& C, hipStream_t st) {
+  launch_spmv<double, D>(C.lev[0], C.P, C.Q, nullptr, 0, nullptr, st);
+  enqueue_packed_update<D>(C, st);
+}
+
+// z = B r (the whole packed V-cycle) and the direction
+template <int D>
+void enqueue_packed_B(vasmg_ctx& C, hipStream_t st) {
+  enqueue_precond<D>(C, nullptr, st);
+  enqueue_packed_direction<D>(C, st);
 }
 
 template <int D>
@@ -3628,9 +3644,16 @@ vasmg_status vasmg_profile_iteration(vasmg_handle h, int32_t reps, void* stream,
       launch_fill<float>(static_cast<float*>(C.lev[0].b), C.n0p, 1.0f, st);
     else
       launch_fill<double>(static_cast<double*>(C.lev[0].b), C.n0p, 1.0, st);
-    const int zero = 0;
-    HIP_CHECK(hipMemcpyAsync(&C.sc->done, &zero, sizeof(int), hipMemcpyHostToDevice, st));
-    HIP_CHECK(hipStreamSynchronize(st));
+    // running iterations that no step of these replays stops
+    Scalars running{};
+    running.rho = running.normF = 1.0;
+    const std::vector<Scalars> state(std::max(C.nseg, 1), running);
+    auto restart = [&] {
+      HIP_CHECK(hipMemcpyAsync(C.sc, state.data(), sizeof(Scalars), hipMemcpyHostToDevice, st));
+      if (C.nseg > 0)
+        HIP_CHECK(hipMemcpyAsync(C.ssc, state.data(), sizeof(Scalars) * C.nseg, hipMemcpyHostToDevice, st));
+      HIP_CHECK(hipStreamSynchronize(st));
+    };
     Profiler prof{st, {}, {}, {}};
     const DevLevel& l0 = C.lev[0];
     const double n0 = l0.n, dd = C.d * C.d;
@@ -3641,28 +3664,22 @@ vasmg_status vasmg_profile_iteration(vasmg_handle h, int32_t reps, void* stream,
     for (int r = 0; r < reps; ++r) {
       auto body = [&](auto dtag) {
         constexpr int D = decltype(dtag)::value;
+        int np = 0;
+        restart();
         run_phase(&prof, "spmv_f64", 0, 1, spmv_bytes, [&] {
-          launch_spmv<double, D>(l0, C.P, C.Q, C.partial, C.n_partial, nullptr, st);
+          np = launch_spmv<double, D>(l0, C.P, C.Q, C.nseg > 0 ? nullptr : C.partial, C.n_partial, nullptr, st);
         });
-        run_phase(&prof, "pcg_vectors", -1, 3, vec_bytes, [&] {
-          if (C.vc32) {
-            hipLaunchKernelGGL((dev::k_update_xr<float>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st,
-                               C.n0p, C.sc, C.P, C.Q, C.X, C.R, static_cast<float*>(C.lev[0].b),
-                               C.partial);
-            hipLaunchKernelGGL((dev::k_dot<float>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st,
-                               C.n0p, C.R, static_cast<const float*>(C.lev[0].x), C.partial,
-                               nullptr);
-            hipLaunchKernelGGL((dev::k_update_p<float>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st,
-                               C.n0p, C.sc, static_cast<const float*>(C.lev[0].x), C.P);
+        const int launches = C.nseg > 0 || C.n0p <= dev::kSmallFlat ? 2 : 6;
+        run_phase(&prof, "pcg_vectors", -1, launches, vec_bytes, [&] {
+          if (C.nseg > 0) {
+            enqueue_packed_update<D>(C, st);
+            enqueue_packed_direction<D>(C, st);
           } else {
-            hipLaunchKernelGGL((dev::k_update_xr<double>), dim3(kFlatGrid), dim3(dev::kBlock), 0,
-                               st, C.n0p, C.sc, C.P, C.Q, C.X, C.R, static_cast<double*>(nullptr),
-                               C.partial);
-            hipLaunchKernelGGL((dev::k_dot<double>), dim3(kFlatGrid), dim3(dev::kBlock), 0, st,
-                               C.n0p, C.R, static_cast<const double*>(C.lev[0].x), C.partial,
-                               nullptr);
-            hipLaunchKernelGGL((dev::k_update_p<double>), dim3(kFlatGrid), dim3(dev::kBlock), 0,
-                               st, C.n0p, C.sc, static_cast<const double*>(C.lev[0].x), C.P);
+            enqueue_update(C, np, st);
+            if (C.vc32)
+              enqueue_direction(C, static_cast<const float*>(C.lev[0].x), st);
+            else
+              enqueue_direction(C, static_cast<const double*>(C.lev[0].x), st);
           }
         });
         if (C.vc32)

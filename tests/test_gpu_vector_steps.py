@@ -88,3 +88,24 @@ def test_pack_of_many_parts():
             assert abs(infos[i]["iterations"] - ia["iterations"]) <= 1
             assert _rel(X[i], c * xa) <= 1e-10
     pk.free()
+
+
+def test_profile_replays_the_vector_steps_of_the_solve():
+    """One iteration's vector steps: two launches up to the size that one workgroup
+    takes and in packs, six above; they cost time in every replay (no step of a replay
+    stops the iteration it replays), and a solve afterwards is the same."""
+    f = lambda ph: [p for p in ph if p["name"] == "pcg_vectors"]  # noqa: E731
+    for make, small in SIZES.values():
+        m = make()
+        with V.Solver.from_mesh(m, autotune=0) as s:
+            x, _ = s.solve(m.rhs[0], 1e-6)
+            vec = f(s.profile_iteration(2))
+            assert len(vec) == 1 and vec[0]["launches"] == 2 * (2 if small else 6) and vec[0]["ms"] > 0
+            assert np.array_equal(s.solve(m.rhs[0], 1e-6)[0], x)
+    ms = [small2d(9, seed=1), small2d(67, seed=2)]
+    pk = V.PackedSolver([V.Solver.from_mesh(m, host_only=1) for m in ms])
+    x, _ = pk.solve_packed([m.rhs[0] for m in ms], 1e-6)
+    assert f(pk.profile_iteration(2))[0]["launches"] == 4
+    y, _ = pk.solve_packed([m.rhs[0] for m in ms], 1e-6)
+    assert all(np.array_equal(a, b) for a, b in zip(x, y))
+    pk.free()
