@@ -1352,9 +1352,7 @@ __global__ __launch_bounds__((CellPack<D, GR>::threads)) void k_cell_apply(
 // ---------------------------------------------------------------------------
 template <typename T, int D, bool FIRST>
 __global__ __launch_bounds__(kBlock) void k_jacobi_step(int n, const T* __restrict__ dinv, T omega,
-                                                        const T* __restrict__ v, T* __restrict__ x,
-                                                        const int* __restrict__ done) {
-  if (done && *done) return;
+                                                        const T* __restrict__ v, T* __restrict__ x) {
   constexpr int DP = Pad<D>::value;
   const int i = blockIdx.x * kBlock + threadIdx.x;
   if (i >= n) return;
@@ -1442,9 +1440,7 @@ constexpr int kCoarseMax = 4096;
 
 template <typename T, int D>
 __global__ __launch_bounds__(kBlock) void k_coarse_solve(int n, const double* __restrict__ L,
-                                                         const T* __restrict__ b, T* __restrict__ x,
-                                                         const int* __restrict__ done) {
-  if (done && *done) return;
+                                                         const T* __restrict__ b, T* __restrict__ x) {
   constexpr int DP = Pad<D>::value;
   __shared__ double y[kCoarseMax];
   for (int i = threadIdx.x; i < n; i += blockDim.x)
@@ -1475,9 +1471,7 @@ __global__ __launch_bounds__(kBlock) void k_coarse_solve(int n, const double* __
 constexpr int kCoarseInvMax = 256;
 template <typename T, int D>
 __global__ __launch_bounds__(kBlock) void k_coarse_apply(int n, const double* __restrict__ Minv,
-                                                         const T* __restrict__ b, T* __restrict__ x,
-                                                         const int* __restrict__ done) {
-  if (done && *done) return;
+                                                         const T* __restrict__ b, T* __restrict__ x) {
   constexpr int DP = Pad<D>::value;
   __shared__ double y[kCoarseInvMax];
   for (int i = threadIdx.x; i < n; i += blockDim.x)
@@ -1712,9 +1706,7 @@ __device__ __forceinline__ void bottom_transfer(int nrows, const int* ptr, const
 }
 
 template <typename T, int D>
-__global__ __launch_bounds__(kBottomThreads) void k_bottom(BottomArgs<T> a,
-                                                           const int* __restrict__ done) {
-  if (done && *done) return;
+__global__ __launch_bounds__(kBottomThreads) void k_bottom(BottomArgs<T> a) {
   constexpr int DP = Pad<D>::value;
   extern __shared__ __align__(16) unsigned char bottom_smem[];
   __shared__ double cy[kCoarseInvMax];

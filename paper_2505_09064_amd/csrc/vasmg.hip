@@ -214,7 +214,6 @@ struct vasmg_ctx {
   double* h_rtol = nullptr;         // pinned
   int* mail = nullptr;              // pinned: reports of the iteration (one per column or part)
   int* big_mail = nullptr;          // own allocation, more than kMailWords parts
-  int* zero_flag = nullptr;         // device int 0 (debug entry points)
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t gA = nullptr, gB = nullptr;
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -847,8 +846,6 @@ void upload_all(vasmg_ctx& C) {
   C.partial = C.dalloc<double>(C.n_partial);
   C.sc = C.dalloc<Scalars>(1);
   C.clear(C.sc, sizeof(Scalars));
-  C.zero_flag = C.dalloc<int>(1);
-  C.clear(C.zero_flag, sizeof(int));
   // pinned: Scalars at 0, rtol at 256, block scalars [16] at 512, reports [kMailWords] at 2048
   static_assert(512 + 16 * sizeof(Scalars) <= 2048 && 2048 + kMailWords * sizeof(int) <= PinnedPool::kBytes,
                 "pinned block too small");
@@ -994,8 +991,7 @@ void select_bottom(vasmg_ctx& C) {
 
 // Returns the number of workgroups (= partial sums written when partial != NULL).
 template <typename T, int D>
-int launch_spmv(const DevLevel& lv, const T* x, T* y, double* partial, int n_partial,
-                const int* done, hipStream_t st) {
+int launch_spmv(const DevLevel& lv, const T* x, T* y, double* partial, int n_partial, hipStream_t st) {
   const int G = lv.Gspmv;
   int used = 0;
   DISPATCH_G(G, {
@@ -1017,8 +1013,7 @@ int launch_spmv(const DevLevel& lv, const T* x, T* y, double* partial, int n_par
 
 
 template <typename T, int D>
-void launch_gs_color(const DevLevel& lv, int c, int mode, const T* b, T* x, T* s_save,
-                     const int* done, hipStream_t st) {
+void launch_gs_color(const DevLevel& lv, int c, int mode, const T* b, T* x, T* s_save, hipStream_t st) {
   const int r0 = lv.color_ptr[c], nr = lv.color_ptr[c + 1] - r0;
   if (nr <= 0) return;
   DISPATCH_G(lv.G, {
@@ -1074,8 +1069,7 @@ void launch_gs_blocks(const DevLevel& lv, int c, int mode, const T* b, T* x, T* 
 }
 
 template <typename T, int D>
-void launch_gs_cells(const DevLevel& lv, int c, int mode, const T* b, T* x, T* s_save,
-                     const int* done, hipStream_t st) {
+void launch_gs_cells(const DevLevel& lv, int c, int mode, const T* b, T* x, T* s_save, hipStream_t st) {
   if (lv.blocks) {
     launch_gs_blocks<T, D>(lv, c, mode, b, x, s_save, st);
     return;
@@ -1100,7 +1094,7 @@ void launch_gs_cells(const DevLevel& lv, int c, int mode, const T* b, T* x, T* s
 }
 
 template <typename T, int D, int KIND>
-void launch_cell_apply(const DevLevel& lv, const T* base, const T* x, T* out, const int* done,
+void launch_cell_apply(const DevLevel& lv, const T* base, const T* x, T* out,
                        hipStream_t st) {
   const dev::Part<T> Ep = LevelMats<T>::E(lv), Fp = LevelMats<T>::F(lv);
   DISPATCH_GR(lv.G, {
@@ -1119,29 +1113,29 @@ void launch_cell_apply(const DevLevel& lv, const T* base, const T* x, T* out, co
 
 template <typename T, int D>
 void launch_gs_sweep(const DevLevel& lv, bool backward, bool zero_guess, const T* b, T* x,
-                     T* s_save, const int* done, hipStream_t st) {
+                     T* s_save, hipStream_t st) {
   if (lv.cells) {
     if (!backward) {
       for (int c = 0; c < lv.ncolors; ++c)
-        launch_gs_cells<T, D>(lv, c, zero_guess ? 0 : 1, b, x, s_save, done, st);
+        launch_gs_cells<T, D>(lv, c, zero_guess ? 0 : 1, b, x, s_save, st);
     } else {
-      for (int c = lv.ncolors - 1; c >= 0; --c) launch_gs_cells<T, D>(lv, c, 2, b, x, nullptr, done, st);
+      for (int c = lv.ncolors - 1; c >= 0; --c) launch_gs_cells<T, D>(lv, c, 2, b, x, nullptr, st);
     }
     return;
   }
   if (!backward) {
     for (int c = 0; c < lv.ncolors; ++c)
-      launch_gs_color<T, D>(lv, c, zero_guess ? 0 : 1, b, x, s_save, done, st);
+      launch_gs_color<T, D>(lv, c, zero_guess ? 0 : 1, b, x, s_save, st);
   } else {
-    for (int c = lv.ncolors - 1; c >= 0; --c) launch_gs_color<T, D>(lv, c, 2, b, x, nullptr, done, st);
+    for (int c = lv.ncolors - 1; c >= 0; --c) launch_gs_color<T, D>(lv, c, 2, b, x, nullptr, st);
   }
 }
 
 template <typename T, int D>
-void launch_residual_upper(const DevLevel& lv, const T* s, const T* x, T* r, const int* done,
+void launch_residual_upper(const DevLevel& lv, const T* s, const T* x, T* r,
                            hipStream_t st) {
   if (lv.cells) {
-    launch_cell_apply<T, D, 0>(lv, s, x, r, done, st);
+    launch_cell_apply<T, D, 0>(lv, s, x, r, st);
     return;
   }
   DISPATCH_G(lv.G, {
@@ -1152,10 +1146,10 @@ void launch_residual_upper(const DevLevel& lv, const T* s, const T* x, T* r, con
 }
 
 template <typename T, int D>
-void launch_residual_full(const DevLevel& lv, const T* b, const T* x, T* r, const int* done,
+void launch_residual_full(const DevLevel& lv, const T* b, const T* x, T* r,
                           hipStream_t st) {
   if (lv.cells) {
-    launch_cell_apply<T, D, 1>(lv, b, x, r, done, st);
+    launch_cell_apply<T, D, 1>(lv, b, x, r, st);
     return;
   }
   DISPATCH_G(lv.G, {
@@ -1169,27 +1163,27 @@ void launch_residual_full(const DevLevel& lv, const T* b, const T* x, T* r, cons
 constexpr int kRestrictLanes = 8, kProlongLanes = 4;
 
 template <typename T, int D>
-void launch_jacobi(const DevLevel& lv, bool first, const T* v, T* x, const int* done,
+void launch_jacobi(const DevLevel& lv, bool first, const T* v, T* x,
                    hipStream_t st) {
   const dim3 grid(grid_for(lv.n, dev::kBlock)), blk(dev::kBlock);
   const T om = static_cast<T>(lv.omega);
   if (first)
     hipLaunchKernelGGL((dev::k_jacobi_step<T, D, true>), grid, blk, 0, st, lv.n,
-                       LevelMats<T>::dinv(lv), om, v, x, done);
+                       LevelMats<T>::dinv(lv), om, v, x);
   else
     hipLaunchKernelGGL((dev::k_jacobi_step<T, D, false>), grid, blk, 0, st, lv.n,
-                       LevelMats<T>::dinv(lv), om, v, x, done);
+                       LevelMats<T>::dinv(lv), om, v, x);
 }
 
 template <typename T, int D>
-void launch_restrict(const DevLevel& lv, const T* r, T* bc, const int* done, hipStream_t st) {
+void launch_restrict(const DevLevel& lv, const T* r, T* bc, hipStream_t st) {
   hipLaunchKernelGGL((dev::k_restrict<T, D, kRestrictLanes>),
                      dim3(grid_for(lv.nnext, dev::kBlock / kRestrictLanes)), dim3(dev::kBlock), 0,
                      st, lv.nnext, lv.pt_ptr, lv.pt_idx, LevelMats<T>::ptw(lv), r, bc);
 }
 
 template <typename T, int D>
-void launch_prolong(const DevLevel& lv, const T* e, T* x, const int* done, hipStream_t st) {
+void launch_prolong(const DevLevel& lv, const T* e, T* x, hipStream_t st) {
   hipLaunchKernelGGL((dev::k_prolong_add<T, D, kProlongLanes>),
                      dim3(grid_for(lv.n, dev::kBlock / kProlongLanes)), dim3(dev::kBlock), 0, st,
                      lv.n, lv.p_ptr, lv.p_idx, LevelMats<T>::pw(lv), e, x, lv.fixed);
@@ -1318,7 +1312,7 @@ void launch_dense(const vasmg_ctx& C, int which, const T* v1, const T* v2, T* ou
 // `visits` coarse visits (2 for the W-cycle above the coarsest level),
 // prolongation and post-smoothing.
 template <typename T, int D>
-void enqueue_level(vasmg_ctx& C, int l, bool zero_guess, const int* done, hipStream_t st,
+void enqueue_level(vasmg_ctx& C, int l, bool zero_guess, hipStream_t st,
                    Profiler* prof) {
   const int L = C.L;
   const int tb = sizeof(T);
@@ -1327,11 +1321,11 @@ void enqueue_level(vasmg_ctx& C, int l, bool zero_guess, const int* done, hipStr
       if (C.cinv)
         hipLaunchKernelGGL((dev::k_coarse_apply<T, D>), dim3(1), dim3(dev::kBlock), 0, st,
                            static_cast<int>(C.n_coarse), C.cinv, static_cast<const T*>(C.lev[L].b),
-                           static_cast<T*>(C.lev[L].x), done);
+                           static_cast<T*>(C.lev[L].x));
       else
         hipLaunchKernelGGL((dev::k_coarse_solve<T, D>), dim3(1), dim3(dev::kBlock), 0, st,
                            static_cast<int>(C.n_coarse), C.chol, static_cast<const T*>(C.lev[L].b),
-                           static_cast<T*>(C.lev[L].x), done);
+                           static_cast<T*>(C.lev[L].x));
     });
     return;
   }
@@ -1376,8 +1370,7 @@ void enqueue_level(vasmg_ctx& C, int l, bool zero_guess, const int* done, hipStr
       }
     const size_t lds = static_cast<size_t>(C.bottom_vec) * sizeof(T) + C.bottom_int * sizeof(int);
     run_phase(prof, "bottom", l, 1, bytes, [&] {
-      hipLaunchKernelGGL((dev::k_bottom<T, D>), dim3(1), dim3(dev::kBottomThreads), lds, st, a,
-                         done);
+      hipLaunchKernelGGL((dev::k_bottom<T, D>), dim3(1), dim3(dev::kBottomThreads), lds, st, a);
     });
     return;
   }
@@ -1387,56 +1380,56 @@ void enqueue_level(vasmg_ctx& C, int l, bool zero_guess, const int* done, hipStr
     run_phase(prof, "jacobi_pre", l, 2 * npre, npre * by.gs_fwd, [&] {
       for (int k = 0; k < npre; ++k) {
         if (zero_guess && k == 0) {
-          launch_jacobi<T, D>(lv, true, b, x, done, st);
+          launch_jacobi<T, D>(lv, true, b, x, st);
         } else {
-          launch_residual_full<T, D>(lv, b, x, r, done, st);
-          launch_jacobi<T, D>(lv, false, r, x, done, st);
+          launch_residual_full<T, D>(lv, b, x, r, st);
+          launch_jacobi<T, D>(lv, false, r, x, st);
         }
       }
     });
     run_phase(prof, "residual_full", l, 2, by.gs_fwd, [&] {
       if (npre == 0 && zero_guess) launch_fill<T>(x, static_cast<int64_t>(lv.n) * C.DP, T(0), st);
-      launch_residual_full<T, D>(lv, b, x, r, done, st);
+      launch_residual_full<T, D>(lv, b, x, r, st);
     });
   } else if (npre == 0) {
     run_phase(prof, "residual_full", l, 2, by.gs_fwd, [&] {
       if (zero_guess) launch_fill<T>(x, static_cast<int64_t>(lv.n) * C.DP, T(0), st);
-      launch_residual_full<T, D>(lv, b, x, r, done, st);
+      launch_residual_full<T, D>(lv, b, x, r, st);
     });
   } else {
     for (int k = 0; k < npre; ++k) {
       const bool z = zero_guess && k == 0;
       run_phase(prof, z ? "gs_fwd_zero" : "gs_fwd", l, lv.ncolors, z ? by.gs_fwd0 : by.gs_fwd,
-                [&] { launch_gs_sweep<T, D>(lv, false, z, b, x, s, done, st); });
+                [&] { launch_gs_sweep<T, D>(lv, false, z, b, x, s, st); });
     }
     run_phase(prof, "residual", l, 1, by.residual,
-              [&] { launch_residual_upper<T, D>(lv, s, x, r, done, st); });
+              [&] { launch_residual_upper<T, D>(lv, s, x, r, st); });
   }
   run_phase(prof, "restrict", l, 1, by.restrict_,
-            [&] { launch_restrict<T, D>(lv, r, static_cast<T*>(C.lev[l + 1].b), done, st); });
+            [&] { launch_restrict<T, D>(lv, r, static_cast<T*>(C.lev[l + 1].b), st); });
   const int visits = (C.opt.cycle == VASMG_CYCLE_W && l + 1 < L) ? 2 : 1;
-  for (int v = 0; v < visits; ++v) enqueue_level<T, D>(C, l + 1, v == 0, done, st, prof);
+  for (int v = 0; v < visits; ++v) enqueue_level<T, D>(C, l + 1, v == 0, st, prof);
   run_phase(prof, "prolong", l, 1, by.prolong, [&] {
-    launch_prolong<T, D>(lv, static_cast<const T*>(C.lev[l + 1].x), x, done, st);
+    launch_prolong<T, D>(lv, static_cast<const T*>(C.lev[l + 1].x), x, st);
   });
   for (int k = 0; k < npost; ++k) {
     if (jac)
       run_phase(prof, "jacobi_post", l, 2, by.gs_bwd, [&] {
-        launch_residual_full<T, D>(lv, b, x, r, done, st);
-        launch_jacobi<T, D>(lv, false, r, x, done, st);
+        launch_residual_full<T, D>(lv, b, x, r, st);
+        launch_jacobi<T, D>(lv, false, r, x, st);
       });
     else
       run_phase(prof, "gs_bwd", l, lv.ncolors, by.gs_bwd,
-                [&] { launch_gs_sweep<T, D>(lv, true, false, b, x, nullptr, done, st); });
+                [&] { launch_gs_sweep<T, D>(lv, true, false, b, x, nullptr, st); });
   }
 }
 
 // z = B r with r in lev[0].b, z in lev[0].x (V- or W-cycle, or the additive
 // two-level form S r + P_0 B_1 P_0^T r with B_1 the V-cycle of levels 1..L).
 template <typename T, int D>
-void enqueue_vcycle(vasmg_ctx& C, const int* done, hipStream_t st, Profiler* prof = nullptr) {
+void enqueue_vcycle(vasmg_ctx& C, hipStream_t st, Profiler* prof = nullptr) {
   if (C.opt.cycle != VASMG_CYCLE_ADDITIVE || C.L == 0) {
-    enqueue_level<T, D>(C, 0, true, done, st, prof);
+    enqueue_level<T, D>(C, 0, true, st, prof);
     return;
   }
   const int tb = sizeof(T);
@@ -1446,8 +1439,8 @@ void enqueue_vcycle(vasmg_ctx& C, const int* done, hipStream_t st, Profiler* pro
   T* s = static_cast<T*>(l0.s);
   const LevelBytes by = prof ? level_bytes(C, 0, tb) : LevelBytes{};
   run_phase(prof, "restrict", 0, 1, by.restrict_,
-            [&] { launch_restrict<T, D>(l0, b, static_cast<T*>(C.lev[1].b), done, st); });
-  enqueue_level<T, D>(C, 1, true, done, st, prof);     // V-cycle below (cycle != W)
+            [&] { launch_restrict<T, D>(l0, b, static_cast<T*>(C.lev[1].b), st); });
+  enqueue_level<T, D>(C, 1, true, st, prof);     // V-cycle below (cycle != W)
   if (C.opt.smoother == VASMG_SMOOTHER_JACOBI) {
     T* r = static_cast<T*>(l0.r);
     const int steps = C.opt.n_pre + C.opt.n_post;
@@ -1455,34 +1448,34 @@ void enqueue_vcycle(vasmg_ctx& C, const int* done, hipStream_t st, Profiler* pro
     for (int k = 0; k < steps; ++k)
       run_phase(prof, "jacobi", 0, k == 0 ? 1 : 2, by.gs_fwd, [&] {
         if (k == 0) {
-          launch_jacobi<T, D>(l0, true, b, x, done, st);
+          launch_jacobi<T, D>(l0, true, b, x, st);
         } else {
-          launch_residual_full<T, D>(l0, b, x, r, done, st);
-          launch_jacobi<T, D>(l0, false, r, x, done, st);
+          launch_residual_full<T, D>(l0, b, x, r, st);
+          launch_jacobi<T, D>(l0, false, r, x, st);
         }
       });
   } else {
     for (int k = 0; k < C.opt.n_pre; ++k)
       run_phase(prof, k == 0 ? "gs_fwd_zero" : "gs_fwd", 0, l0.ncolors,
                 k == 0 ? by.gs_fwd0 : by.gs_fwd,
-                [&] { launch_gs_sweep<T, D>(l0, false, k == 0, b, x, s, done, st); });
+                [&] { launch_gs_sweep<T, D>(l0, false, k == 0, b, x, s, st); });
     if (C.opt.n_pre == 0)
       launch_fill<T>(x, static_cast<int64_t>(l0.n) * C.DP, T(0), st);
     for (int k = 0; k < C.opt.n_post; ++k)
       run_phase(prof, "gs_bwd", 0, l0.ncolors, by.gs_bwd,
-                [&] { launch_gs_sweep<T, D>(l0, true, false, b, x, nullptr, done, st); });
+                [&] { launch_gs_sweep<T, D>(l0, true, false, b, x, nullptr, st); });
   }
   run_phase(prof, "prolong", 0, 1, by.prolong, [&] {
-    launch_prolong<T, D>(l0, static_cast<const T*>(C.lev[1].x), x, done, st);
+    launch_prolong<T, D>(l0, static_cast<const T*>(C.lev[1].x), x, st);
   });
 }
 
 template <int D>
-void enqueue_precond(vasmg_ctx& C, const int* done, hipStream_t st) {
+void enqueue_precond(vasmg_ctx& C, hipStream_t st) {
   if (C.vc32)
-    enqueue_vcycle<float, D>(C, done, st);
+    enqueue_vcycle<float, D>(C, st);
   else
-    enqueue_vcycle<double, D>(C, done, st);
+    enqueue_vcycle<double, D>(C, st);
 }
 
 // -------------------------------------------------------------------------
@@ -1515,7 +1508,7 @@ void enqueue_update(vasmg_ctx& C, int np, hipStream_t st) {
 
 template <int D>
 void enqueue_iter_A(vasmg_ctx& C, hipStream_t st) {
-  const int np = launch_spmv<double, D>(C.lev[0], C.P, C.Q, C.partial, C.n_partial, &C.sc->done, st);
+  const int np = launch_spmv<double, D>(C.lev[0], C.P, C.Q, C.partial, C.n_partial, st);
   enqueue_update(C, np, st);
 }
 
@@ -1542,7 +1535,7 @@ void enqueue_iter_B(vasmg_ctx& C, hipStream_t st) {
   if (pc == VASMG_PRECOND_VASMG) {
     // the host launches this graph only while the iteration has not stopped, so
     // the V-cycle kernels do not read the flag (it would head their load chains)
-    enqueue_precond<D>(C, nullptr, st);
+    enqueue_precond<D>(C, st);
     if (C.vc32)
       enqueue_direction(C, static_cast<const float*>(C.lev[0].x), st);
     else
@@ -1574,9 +1567,9 @@ double time_level(vasmg_ctx& C, int l, hipStream_t st) {
   std::vector<float> t;
   for (int rep = 0; rep < 4; ++rep) {
     HIP_CHECK(hipEventRecord(e0, st));
-    launch_gs_sweep<T, D>(lv, false, true, b, x, s, nullptr, st);
-    launch_residual_upper<T, D>(lv, s, x, r, nullptr, st);
-    launch_gs_sweep<T, D>(lv, true, false, b, x, nullptr, nullptr, st);
+    launch_gs_sweep<T, D>(lv, false, true, b, x, s, st);
+    launch_residual_upper<T, D>(lv, s, x, r, st);
+    launch_gs_sweep<T, D>(lv, true, false, b, x, nullptr, st);
     HIP_CHECK(hipEventRecord(e1, st));
     HIP_CHECK(hipEventSynchronize(e1));
     float ms = 0.f;
@@ -1597,7 +1590,7 @@ double time_spmv(vasmg_ctx& C, hipStream_t st) {
   std::vector<float> t;
   for (int rep = 0; rep < 4; ++rep) {
     HIP_CHECK(hipEventRecord(e0, st));
-    launch_spmv<double, D>(C.lev[0], C.P, C.Q, C.partial, C.n_partial, nullptr, st);
+    launch_spmv<double, D>(C.lev[0], C.P, C.Q, C.partial, C.n_partial, st);
     HIP_CHECK(hipEventRecord(e1, st));
     HIP_CHECK(hipEventSynchronize(e1));
     float ms = 0.f;
@@ -1748,14 +1741,14 @@ void enqueue_packed_direction(vasmg_ctx& C, hipStream_t st) {
 // q = A p and the update
 template <int D>
 void enqueue_packed_A(vasmg_ctx& C, hipStream_t st) {
-  launch_spmv<double, D>(C.lev[0], C.P, C.Q, nullptr, 0, nullptr, st);
+  launch_spmv<double, D>(C.lev[0], C.P, C.Q, nullptr, 0, st);
   enqueue_packed_update<D>(C, st);
 }
 
 // z = B r (the whole packed V-cycle) and the direction
 template <int D>
 void enqueue_packed_B(vasmg_ctx& C, hipStream_t st) {
-  enqueue_precond<D>(C, nullptr, st);
+  enqueue_precond<D>(C, st);
   enqueue_packed_direction<D>(C, st);
 }
 
@@ -1802,7 +1795,7 @@ int solve_packed(vasmg_ctx& C, const double* d_rhs, double* d_x, double rtol, hi
     }
   }
   // true residuals, scatter
-  launch_spmv<double, D>(C.lev[0], C.X, C.Q, nullptr, 0, nullptr, st);
+  launch_spmv<double, D>(C.lev[0], C.X, C.Q, nullptr, 0, st);
   hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_TRUE, true, DP>), dim3(nseg), dim3(dev::kSegBlock), 0, st,
                      C.seg_ptr, C.seg_rows, C.F, C.Q, C.ssc);
   launch_fill<double>(d_x, C.H.n_mesh_vertices * D, 0.0, st);
@@ -1860,7 +1853,7 @@ int solve_one(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d_x
     hipLaunchKernelGGL((dev::k_gather_user<double, double, D>), dim3(grid_for(n0, dev::kBlock)),
                        dim3(dev::kBlock), 0, st, n0, C.user_map, d_x0, C.X,
                        static_cast<const uint8_t*>(C.lev[0].fixed));
-    launch_spmv<double, D>(C.lev[0], C.X, C.Q, nullptr, 0, nullptr, st);
+    launch_spmv<double, D>(C.lev[0], C.X, C.Q, nullptr, 0, st);
     hipLaunchKernelGGL(dev::k_sub_norm, dim3(gflat), dim3(dev::kBlock), 0, st, n0p, C.F, C.Q, C.R,
                        C.partial);
     hipLaunchKernelGGL((dev::k_finalize<dev::FIN_TRUE>), dim3(1), dim3(1024), 0, st, C.partial, gflat,
@@ -1923,7 +1916,7 @@ int solve_one(vasmg_ctx& C, const double* d_rhs, const double* d_x0, double* d_x
     }
   }
   // true residual, scatter
-  launch_spmv<double, D>(C.lev[0], C.X, C.Q, nullptr, 0, nullptr, st);
+  launch_spmv<double, D>(C.lev[0], C.X, C.Q, nullptr, 0, st);
   hipLaunchKernelGGL(dev::k_sub_norm, dim3(gflat), dim3(dev::kBlock), 0, st, n0p, C.F, C.Q,
                      static_cast<double*>(nullptr), C.partial);
   hipLaunchKernelGGL((dev::k_finalize<dev::FIN_TRUE>), dim3(1), dim3(1024), 0, st, C.partial, gflat,
@@ -3472,9 +3465,9 @@ vasmg_status vasmg_spmv_device(vasmg_handle h, int32_t level, int32_t precision,
       }
       debug_gather<T, D>(*h, level, d_x, xin, st);
       if (lv.cells)
-        launch_cell_apply<T, D, 2>(lv, nullptr, xin, yout, nullptr, st);
+        launch_cell_apply<T, D, 2>(lv, nullptr, xin, yout, st);
       else
-        launch_spmv<T, D>(lv, xin, yout, nullptr, 0, nullptr, st);
+        launch_spmv<T, D>(lv, xin, yout, nullptr, 0, st);
       debug_scatter<T, D>(*h, level, yout, d_y, st);
     };
     if (precision == VASMG_FP64) {
@@ -3508,7 +3501,7 @@ vasmg_status vasmg_gs_sweep_device(vasmg_handle h, int32_t level, int32_t precis
       T* x = static_cast<T*>(lv.x);
       debug_gather<T, D>(*h, level, d_b, b, st);
       debug_gather<T, D>(*h, level, d_x, x, st);
-      launch_gs_sweep<T, D>(lv, backward != 0, false, b, x, static_cast<T*>(lv.s), nullptr, st);
+      launch_gs_sweep<T, D>(lv, backward != 0, false, b, x, static_cast<T*>(lv.s), st);
       debug_scatter<T, D>(*h, level, x, d_x, st);
     };
     if (precision == VASMG_FP64) {
@@ -3540,7 +3533,7 @@ vasmg_status vasmg_restrict_device(vasmg_handle h, int32_t level, int32_t precis
       T* r = static_cast<T*>(lv.r);
       T* bc = static_cast<T*>(nx.b);
       debug_gather<T, D>(*h, level, d_r, r, st, true);
-      launch_restrict<T, D>(lv, r, bc, nullptr, st);
+      launch_restrict<T, D>(lv, r, bc, st);
       debug_scatter<T, D>(*h, level + 1, bc, d_bc, st);
     };
     if (precision == VASMG_FP64) {
@@ -3573,7 +3566,7 @@ vasmg_status vasmg_prolong_device(vasmg_handle h, int32_t level, int32_t precisi
       T* x = static_cast<T*>(lv.x);
       debug_gather<T, D>(*h, level + 1, d_e, e, st);
       debug_gather<T, D>(*h, level, d_x, x, st);
-      launch_prolong<T, D>(lv, e, x, nullptr, st);
+      launch_prolong<T, D>(lv, e, x, st);
       debug_scatter<T, D>(*h, level, x, d_x, st);
     };
     if (precision == VASMG_FP64) {
@@ -3605,12 +3598,12 @@ vasmg_status vasmg_apply_precond_device(vasmg_handle h, const double* d_r, doubl
       debug_gather<T, D>(*h, 0, d_r, b, st);
       if (h->L == 0 && h->cinv) {
         hipLaunchKernelGGL((dev::k_coarse_apply<T, D>), dim3(1), dim3(dev::kBlock), 0, st,
-                           static_cast<int>(h->n_coarse), h->cinv, b, x, h->zero_flag);
+                           static_cast<int>(h->n_coarse), h->cinv, b, x);
       } else if (h->L == 0) {
         hipLaunchKernelGGL((dev::k_coarse_solve<T, D>), dim3(1), dim3(dev::kBlock), 0, st,
-                           static_cast<int>(h->n_coarse), h->chol, b, x, h->zero_flag);
+                           static_cast<int>(h->n_coarse), h->chol, b, x);
       } else {
-        enqueue_vcycle<T, D>(*h, h->zero_flag, st);
+        enqueue_vcycle<T, D>(*h, st);
       }
       debug_scatter<T, D>(*h, 0, x, d_z, st);
     };
@@ -3667,7 +3660,7 @@ vasmg_status vasmg_profile_iteration(vasmg_handle h, int32_t reps, void* stream,
         int np = 0;
         restart();
         run_phase(&prof, "spmv_f64", 0, 1, spmv_bytes, [&] {
-          np = launch_spmv<double, D>(l0, C.P, C.Q, C.nseg > 0 ? nullptr : C.partial, C.n_partial, nullptr, st);
+          np = launch_spmv<double, D>(l0, C.P, C.Q, C.nseg > 0 ? nullptr : C.partial, C.n_partial, st);
         });
         const int launches = C.nseg > 0 || C.n0p <= dev::kSmallFlat ? 2 : 6;
         run_phase(&prof, "pcg_vectors", -1, launches, vec_bytes, [&] {
@@ -3683,9 +3676,9 @@ vasmg_status vasmg_profile_iteration(vasmg_handle h, int32_t reps, void* stream,
           }
         });
         if (C.vc32)
-          enqueue_vcycle<float, D>(C, C.zero_flag, st, &prof);
+          enqueue_vcycle<float, D>(C, st, &prof);
         else
-          enqueue_vcycle<double, D>(C, C.zero_flag, st, &prof);
+          enqueue_vcycle<double, D>(C, st, &prof);
       };
       if (C.d == 2)
         body(std::integral_constant<int, 2>());
