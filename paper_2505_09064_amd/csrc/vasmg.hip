@@ -1719,10 +1719,10 @@ template <int D>
 void enqueue_packed_update(vasmg_ctx& C, hipStream_t st) {
   constexpr int DP = dev::Pad<D>::value;
   if (C.vc32)
-    hipLaunchKernelGGL((dev::k_seg_xr<float, DP>), dim3(C.nseg), dim3(dev::kSegBlock), 0, st, C.seg_ptr,
+    hipLaunchKernelGGL((dev::k_seg_xr<float, DP>), dim3(C.nseg), dim3(dev::kBlock), 0, st, C.seg_ptr,
                        C.seg_rows, C.ssc, C.P, C.Q, C.X, C.R, static_cast<float*>(C.lev[0].b), C.mail);
   else
-    hipLaunchKernelGGL((dev::k_seg_xr<double, DP>), dim3(C.nseg), dim3(dev::kSegBlock), 0, st, C.seg_ptr,
+    hipLaunchKernelGGL((dev::k_seg_xr<double, DP>), dim3(C.nseg), dim3(dev::kBlock), 0, st, C.seg_ptr,
                        C.seg_rows, C.ssc, C.P, C.Q, C.X, C.R, static_cast<double*>(nullptr), C.mail);
 }
 
@@ -1731,10 +1731,10 @@ template <int D>
 void enqueue_packed_direction(vasmg_ctx& C, hipStream_t st) {
   constexpr int DP = dev::Pad<D>::value;
   if (C.vc32)
-    hipLaunchKernelGGL((dev::k_seg_p<float, DP>), dim3(C.nseg), dim3(dev::kSegBlock), 0, st, C.seg_ptr,
+    hipLaunchKernelGGL((dev::k_seg_p<float, DP>), dim3(C.nseg), dim3(dev::kBlock), 0, st, C.seg_ptr,
                        C.seg_rows, C.ssc, C.R, static_cast<const float*>(C.lev[0].x), C.P);
   else
-    hipLaunchKernelGGL((dev::k_seg_p<double, DP>), dim3(C.nseg), dim3(dev::kSegBlock), 0, st, C.seg_ptr,
+    hipLaunchKernelGGL((dev::k_seg_p<double, DP>), dim3(C.nseg), dim3(dev::kBlock), 0, st, C.seg_ptr,
                        C.seg_rows, C.ssc, C.R, static_cast<const double*>(C.lev[0].x), C.P);
 }
 
@@ -1772,7 +1772,7 @@ int solve_packed(vasmg_ctx& C, const double* d_rhs, double* d_x, double rtol, hi
   hipLaunchKernelGGL((dev::k_gather_user<double, double, D>), dim3(grid_for(n0, dev::kBlock)),
                      dim3(dev::kBlock), 0, st, n0, C.user_map, d_rhs, C.F,
                      static_cast<const uint8_t*>(C.lev[0].fixed));
-  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_NORMF, false, DP>), dim3(nseg), dim3(dev::kSegBlock), 0, st,
+  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_NORMF, false, DP>), dim3(nseg), dim3(dev::kBlock), 0, st,
                      C.seg_ptr, C.seg_rows, C.F, C.F, C.ssc);
   clear_reports(C.mail, nseg);
   hipLaunchKernelGGL(dev::k_seg_start, dim3(grid_for(nseg, dev::kBlock)), dim3(dev::kBlock), 0, st, nseg,
@@ -1796,7 +1796,7 @@ int solve_packed(vasmg_ctx& C, const double* d_rhs, double* d_x, double rtol, hi
   }
   // true residuals, scatter
   launch_spmv<double, D>(C.lev[0], C.X, C.Q, nullptr, 0, st);
-  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_TRUE, true, DP>), dim3(nseg), dim3(dev::kSegBlock), 0, st,
+  hipLaunchKernelGGL((dev::k_seg_dot<dev::FIN_TRUE, true, DP>), dim3(nseg), dim3(dev::kBlock), 0, st,
                      C.seg_ptr, C.seg_rows, C.F, C.Q, C.ssc);
   launch_fill<double>(d_x, C.H.n_mesh_vertices * D, 0.0, st);
   hipLaunchKernelGGL((dev::k_scatter_user<double, double, D>), dim3(grid_for(n0, dev::kBlock)),
