@@ -178,3 +178,29 @@ def test_coarsest_solve_of_the_fp32_cycle_is_fp64(make):
         gap = np.linalg.norm(ref32 - ref)
         assert np.linalg.norm(z.cpu().numpy().ravel() - ref) <= 4 * gap
     s.free()
+
+
+@pytest.mark.parametrize("prec", [V.FP64, V.FP32_PRECOND])
+def test_pack_tables_apply_each_part_s_cycle(prec):
+    """One application of a pack's preconditioner through its tables, part by part
+    against the part's oracle (the bars of the single tables): a wrong block of one
+    part's table would hide behind a converged solve."""
+    for ms in ([small3d(5, seed=1), small3d(11, seed=2, fix="symmetry"), small3d(7, seed=3)],
+               [small2d(30, seed=4), small2d(8, seed=5), small2d(17, seed=6, fix="symmetry")]):
+        dim = ms[0].dim
+        pk = V.PackedSolver([V.Solver.from_mesh(m, precision=prec, host_only=1) for m in ms])
+        assert any(p["name"] == "dense_up" for p in pk.profile_iteration(1))
+        os_ = [Oracle(m.coords, m.elems, m.E, m.nu, m.fixed) for m in ms]
+        r = [np.random.default_rng(i).normal(size=o.A[0].shape[0]) for i, o in enumerate(os_)]
+        z = torch.zeros((sum(v.size for v in r) // dim, dim), dtype=torch.float64, device="cuda")
+        pk.apply_precond_device(torch.from_numpy(np.concatenate(r).reshape(-1, dim)).cuda(), z)
+        z = np.split(z.cpu().numpy().ravel(), np.cumsum([v.size for v in r])[:-1])
+        for o, ri, zi in zip(os_, r, z):
+            ref = o.apply_precond(ri, precision="fp64")
+            err = np.linalg.norm(zi - ref) / np.linalg.norm(ref)
+            if prec == V.FP64:
+                assert err < 1e-11
+            else:
+                gap = np.linalg.norm(o.apply_precond(ri, precision="fp32") - ref) / np.linalg.norm(ref)
+                assert err <= max(4 * gap, 16 * 2.0 ** -24), (err, gap)
+        pk.free()
