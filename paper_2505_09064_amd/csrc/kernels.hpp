@@ -364,58 +364,33 @@ __device__ __forceinline__ void load_own(const T* __restrict__ diag, const T* __
   }
 }
 
-// One part of a point-level row, a lane group of G taking its blocks in order (lane
-// l blocks l, l + G, ...). Rows hold about 7 blocks per part, so a part is one
-// round, a chain of three dependent loads (row range -> column -> neighbour): the
-// caller takes the ranges of both parts together, then opens both (columns and
-// values of the first round), and only then fetches neighbours; longer rows loop.
-// A lane without a block reads its row's last one (or, in an empty row, the block
-// before; an empty part has one zero block) times zero.
-template <typename T, int D, int G>
-struct PointWalk {
-  static constexpr int DP = Pad<D>::value;
-  int k = 0, ke = 0, j;
-  T m[D * D], xv[D];
-  __device__ __forceinline__ void range(const Part<T>& p, int i) {
-    k = p.ptr[i];
-    ke = p.ptr[i + 1];
+// Off-diagonal products of a point-level row (LO / UP: which parts), a lane group of
+// G taking the blocks of each part in order (lane l: blocks l, l + G, ... of L, then
+// of U). Rows hold about 7 blocks per part, unevenly (a colour's rows have most of
+// theirs in one part), so a row is a chain of three dependent loads (row ranges ->
+// columns -> neighbours): the ranges of both parts come together, and columns and
+// values of a lane's first UN blocks, whichever part they are in, go out before the
+// first neighbour is waited for; only longer rows loop. A lane without a block reads
+// its part's last one (or, in an empty row, the block before; an empty part has one
+// zero block) times zero.
+// lo and up get the parts' sums, in every lane of the group; BOTH: lo gets the one
+// running sum over L's blocks, then U's.
+template <typename T, int D, int G, bool LO, bool UP, bool BOTH = false>
+struct PointRow {
+  static constexpr int DP = Pad<D>::value, UN = LO && UP ? 2 : 1;
+  int l0 = 0, le = 0, u0 = 0, ue = 0;
+  __device__ __forceinline__ void ranges(const Part<T>& L, const Part<T>& U, int i) {
+    if (LO) { l0 = L.ptr[i]; le = L.ptr[i + 1]; }
+    if (UP) { u0 = U.ptr[i]; ue = U.ptr[i + 1]; }
   }
-  __device__ __forceinline__ void open(const Part<T>& p, int lane) {
-    k += lane;
-    const int kc = max(min(k, ke - 1), 0);
-    j = p.col[kc];
-#pragma unroll
-    for (int e = 0; e < D * D; ++e) m[e] = p.val[e * p.nnz + kc];
-  }
-  __device__ __forceinline__ void gather(const T* __restrict__ x) {
-    VecIO<T, D>::load(x + static_cast<int64_t>(j) * DP, xv);
-  }
-  // (the compiler would sink a load whose value is only selected)
-  __device__ __forceinline__ void pin() {
-#pragma unroll
-    for (int b = 0; b < D; ++b) asm volatile("" : "+v"(xv[b]));
-  }
-  __device__ __forceinline__ void add(const Part<T>& p, const T* __restrict__ x, T* acc) {
-    const bool in = k < ke;
+  // acc += block k of a part, where `in`
+  static __device__ __forceinline__ void add(const T* m, const T* xv, bool in, T* acc) {
 #pragma unroll
     for (int b = 0; b < D; ++b) {
       const T xb = in ? xv[b] : T(0);
 #pragma unroll
       for (int a = 0; a < D; ++a) acc[a] += m[a * D + b] * xb;
     }
-    if (k + G < ke) row_product<T, D, G>(k + G, ke, 0, p.col, p.val, p.nnz, x, acc);
-  }
-};
-
-// Off-diagonal products of a point-level row (LO / UP: which parts): lo and up get
-// the parts' sums, in every lane of the group; BOTH: lo gets the one running sum
-// over L's blocks, then U's.
-template <typename T, int D, int G, bool LO, bool UP, bool BOTH = false>
-struct PointRow {
-  PointWalk<T, D, G> l, u;
-  __device__ __forceinline__ void ranges(const Part<T>& L, const Part<T>& U, int i) {
-    if (LO) l.range(L, i);
-    if (UP) u.range(U, i);
   }
   __device__ __forceinline__ void sum(const Part<T>& L, const Part<T>& U, int lane,
                                       const T* __restrict__ x, T* lo, T* up) {
@@ -424,15 +399,63 @@ struct PointRow {
       if (LO) lo[a] = T(0);
       if (UP && !BOTH) up[a] = T(0);
     }
-    if (LO) l.open(L, lane);
-    if (UP) u.open(U, lane);
+    // the lane's blocks: nl of L, then those of U
+    const int kl = l0 + lane, ku = u0 + lane;
+    const int nl = LO ? max(le - kl + G - 1, 0) / G : 0;
+    T m[UN][D * D], xv[UN][D];
+    int j[UN];
+    bool isu[UN], in[UN];
+#pragma unroll
+    for (int t = 0; t < UN; ++t) {
+      isu[t] = !LO || (UP && t >= nl);
+      int k = isu[t] ? ku + (t - nl) * G : kl + t * G;
+      const int end = isu[t] ? ue : le;
+      in[t] = k < end;
+      k = max(min(k, end - 1), 0);
+      const int* col = isu[t] ? U.col : L.col;
+      const T* val = isu[t] ? U.val : L.val;
+      const int64_t nnz = isu[t] ? U.nnz : L.nnz;
+      j[t] = col[k];
+#pragma unroll
+      for (int e = 0; e < D * D; ++e) m[t][e] = val[e * nnz + k];
+    }
     __builtin_amdgcn_sched_barrier(0);
-    if (LO) l.gather(x);
-    if (UP) u.gather(x);
-    if (LO) l.pin();
-    if (UP) u.pin();
-    if (LO) l.add(L, x, lo);
-    if (UP) u.add(U, x, BOTH ? lo : up);
+#pragma unroll
+    for (int t = 0; t < UN; ++t) VecIO<T, D>::load(x + static_cast<int64_t>(j[t]) * DP, xv[t]);
+    // (pinned here: the compiler would sink a load whose value is only selected)
+#pragma unroll
+    for (int t = 0; t < UN; ++t) {
+#pragma unroll
+      for (int b = 0; b < D; ++b) asm volatile("" : "+v"(xv[t][b]));
+    }
+#pragma unroll
+    for (int t = 0; t < UN; ++t) {
+      if (BOTH || !UP) {
+        add(m[t], xv[t], in[t], lo);
+      } else if (!LO) {
+        add(m[t], xv[t], in[t], up);
+      } else {
+        add(m[t], xv[t], in[t] && !isu[t], lo);
+        add(m[t], xv[t], in[t] && isu[t], up);
+      }
+    }
+    // the rest, part by part
+    if (LO) {
+      const int k = kl + UN * G;
+      for (int q = k; q < le; q += G) {
+        T xj[D];
+        VecIO<T, D>::load(x + static_cast<int64_t>(L.col[q]) * DP, xj);
+        block_fma<T, D>(L.val, L.nnz, q, xj, lo);
+      }
+    }
+    if (UP) {
+      const int k = ku + max(UN - nl, 0) * G;
+      for (int q = k; q < ue; q += G) {
+        T xj[D];
+        VecIO<T, D>::load(x + static_cast<int64_t>(U.col[q]) * DP, xj);
+        block_fma<T, D>(U.val, U.nnz, q, xj, BOTH ? lo : up);
+      }
+    }
 #pragma unroll
     for (int a = 0; a < D; ++a) {
       if (LO) lo[a] = group_sum<T, G>(lo[a]);
@@ -523,7 +546,10 @@ __global__ __launch_bounds__(kBlock) void k_gs_color(
   const int g = xcd_block() * (kBlock / G) + threadIdx.x / G;
   if (g >= nrows) return;
   const int i = row0 + g;
-  PointRow<T, D, G, true, MODE != 0> row;
+  // 3D: the backward sweep, which does not want s = b - L x on its own, takes one
+  // sum over both parts (2D: two, the order of the operations is part of the result)
+  constexpr bool BOTH = D == 3 && MODE == 2;
+  PointRow<T, D, G, true, MODE != 0, BOTH> row;
   row.ranges(L, U, i);
   // what finishes the row, before the products
   T dg[D * D], xi[D], bi[D];
