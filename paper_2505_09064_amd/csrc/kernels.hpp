@@ -646,6 +646,25 @@ struct CellRec {
   static_assert(U + NV + 1 <= ints, "record too small");
 };
 
+// The records of all cells, one int per thread (on the host, and uploaded, they took
+// 6 ms of the set-up of a graded 513 x 513 mesh).
+template <int D>
+__global__ __launch_bounds__(kBlock) void k_cell_records(int ncells, const int* __restrict__ cell_ptr,
+                                                         const int* __restrict__ Lptr,
+                                                         const int* __restrict__ Uptr, int* __restrict__ rec) {
+  using R = CellRec<D>;
+  const int64_t e = blockIdx.x * int64_t(kBlock) + threadIdx.x;
+  if (e >= static_cast<int64_t>(ncells) * R::ints) return;
+  const int c = static_cast<int>(e / R::ints), k = static_cast<int>(e % R::ints);
+  const int v0 = cell_ptr[c], m = cell_ptr[c + 1] - v0;
+  int v = 0;
+  if (k == 0) v = v0;
+  else if (k == 1) v = m;
+  else if (k < R::U) v = Lptr[v0 + min(k - R::L, m)];
+  else if (k <= R::U + R::NV) v = Uptr[v0 + min(k - R::U, m)];
+  rec[e] = v;
+}
+
 // Cells per workgroup: one per workgroup when a cell's NV * GR lanes fill a
 // wavefront or more (its wavefront 0 runs the in-cell sweep); otherwise as many
 // as share one wavefront (2D cells with 4 or 8 lanes per row), each with its own

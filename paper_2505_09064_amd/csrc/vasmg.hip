@@ -697,19 +697,15 @@ void upload_level_device(vasmg_ctx& C, int l, bool need32, bool need64, const st
   }
   if (dl.cells) {
     dl.cell_ptr = C.upload(cell_ptr);
-    const int NV = 1 << d, ints = cell_rec_ints(d);
-    std::vector<int> rec(static_cast<size_t>(dl.ncells) * ints, 0);
-    for (int c = 0; c < dl.ncells; ++c) {
-      const int v0 = cell_ptr[c], m = cell_ptr[c + 1] - v0;
-      int* r = rec.data() + static_cast<size_t>(c) * ints;
-      r[0] = v0;
-      r[1] = m;
-      for (int k = 0; k <= NV; ++k) {
-        r[2 + k] = Lptr[v0 + std::min(k, m)];
-        r[3 + NV + k] = Uptr[v0 + std::min(k, m)];
-      }
-    }
-    dl.cell_rec = C.upload(rec);
+    const int64_t words = static_cast<int64_t>(dl.ncells) * cell_rec_ints(d);
+    dl.cell_rec = C.dalloc<int>(words);
+    const dim3 grid((words + dev::kBlock - 1) / dev::kBlock), blk(dev::kBlock);
+    if (d == 2)
+      hipLaunchKernelGGL((dev::k_cell_records<2>), grid, blk, 0, st, dl.ncells, dl.cell_ptr, dl.Lptr, dl.Uptr,
+                         dl.cell_rec);
+    else
+      hipLaunchKernelGGL((dev::k_cell_records<3>), grid, blk, 0, st, dl.ncells, dl.cell_ptr, dl.Lptr, dl.Uptr,
+                         dl.cell_rec);
   }
   const int64_t m_len = dl.cells ? static_cast<int64_t>(dl.ncells) * NU * NU : static_cast<int64_t>(n) * dd;
   if (need64) {
