@@ -472,7 +472,9 @@ vasmg_status vasmg_set_galerkin_window(int32_t cols);
  * replayed reps times outside the captured graphs with hipEvents around each
  * phase; phases are aggregated by (name, level). names: spmv_f64, pcg_vectors,
  * gs_fwd_zero, gs_fwd, residual, residual_full, restrict, coarse_solve,
- * prolong, gs_bwd. bytes is the algorithmic HBM traffic of the phase (every
+ * prolong, gs_bwd, bottom (the last levels and the coarsest solve: the fused
+ * kernel or, where the handle has dense tables, one product), dense_down and
+ * dense_up (products over the levels above it). bytes is the algorithmic HBM traffic of the phase (every
  * matrix/vector array it touches read or written once per launch, the gathered
  * neighbour vector once per launch). Uses the handle's work buffers (their
  * contents are overwritten); level -1 = PCG vectors.

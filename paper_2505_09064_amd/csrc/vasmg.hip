@@ -2363,7 +2363,7 @@ constexpr int64_t kDenseLeastWork = int64_t(16) << 20;
 // converges in 10 to 20 products, and by 1e-9 and more where it takes 15 to 50 (200
 // 2D problems of up to 60,000 vertices each, FP32 tables against the level launches,
 // largest relative change: contrast 1 1.4e-12, 4 9e-13, 10 3.4e-11, 30 1.3e-9, 100
-// 7.9e-9; 3D, contrast 100, 2.5e-10).
+// 1.2e-8; 1,700 3D problems, contrast 100, 9.5e-10).
 constexpr double kDenseMaxContrast2d = 10.0;
 
 bool dense_wanted(const vasmg_ctx& C) {
