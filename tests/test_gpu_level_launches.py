@@ -174,3 +174,36 @@ def test_dense_tables_are_chosen_before_the_upload():
         with pytest.raises(V.VasmgError):
             pk.set_dense_tables(True)
         pk.free()
+
+
+def _contrast(m, E=1.0, nu=None):
+    """Every second element E times as stiff (or of Poisson ratio nu)."""
+    m.E = np.where(np.arange(m.elems.shape[0]) % 2 == 0, 1.0, E)
+    if nu is not None:
+        m.nu = np.where(np.arange(m.elems.shape[0]) % 2 == 0, m.nu, nu)
+    return m
+
+
+@pytest.mark.parametrize("make,prec,tables", [
+    (lambda: _contrast(small2d(17, seed=1), 10.0), V.FP32_PRECOND, True),
+    (lambda: _contrast(small2d(17, seed=1), 10.5), V.FP32_PRECOND, False),
+    (lambda: _contrast(small2d(17, seed=1, nu=0.0), nu=0.495), V.FP32_PRECOND, False),
+    (lambda: _contrast(small2d(17, seed=1), 100.0), V.FP64, True),
+    (lambda: _contrast(small3d(8, seed=1), 100.0), V.FP32_PRECOND, True),
+])
+def test_tables_by_stiffness_contrast(make, prec, tables):
+    """The FP32 cycle in 2D tabulates up to a contrast of 10 (of E, or of lambda + 2 mu),
+    alone and as part of a pack; FP64 and 3D whatever the contrast."""
+    m = make()
+    even = small2d(9, seed=2) if m.dim == 2 else small3d(5, seed=2)
+    parts = [V.Solver.from_mesh(x, precision=prec, host_only=1) for x in (even, m)]
+    for s in (V.Solver.from_mesh(m, precision=prec), V.PackedSolver(parts)):
+        ph = s.profile_iteration(1)
+        lo = [p for p in ph if p["name"] == "bottom"][0]["level"]
+        smoothed = [p for p in ph if p["name"] == "gs_bwd" and p["level"] >= 1]
+        dense = [p for p in ph if p["name"].startswith("dense")]
+        if tables:
+            assert not smoothed and len(dense) == (2 if lo > 1 else 0)
+        else:
+            assert not dense and len(smoothed) == lo - 1
+        s.free()
