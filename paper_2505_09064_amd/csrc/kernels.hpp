@@ -1998,9 +1998,9 @@ __global__ __launch_bounds__(kBlock) void k_update_p(int64_t n, const Scalars* _
 // Small problems (n <= kSmallFlat entries): the vector steps of an iteration are
 // launches that do next to nothing, so one workgroup takes a run of them. After the
 // SpMV: alpha from its partial sums, x += alpha p, r -= alpha q, ||r||, the stopping
-// test and the report. FP32-cycle iteration, separate launches and this way: 4,232
-// entries 78.8 and 73.6 us, 16,200 entries 131 and 139 us.
-constexpr int kSmallFlat = 8192;
+// test and the report. FP32-cycle iteration, separate launches and this way: 968
+// entries 73 and 68 us, 4,232 79 and 76, 5,832 82 and 81, 8,112 110 and 114.
+constexpr int kSmallFlat = 6144;
 constexpr int kSmallRounds = kSmallFlat / 1024;   // entries per thread
 
 // Sum over the workgroup, thread t holding entries t, t + 1024, ...: in the order of

@@ -92,12 +92,13 @@ def test_pack_of_many_parts():
 
 def test_profile_replays_the_vector_steps_of_the_solve():
     """One iteration's vector steps: two launches up to the size that one workgroup
-    takes and in packs, six above; they cost time in every replay (no step of a replay
+    takes (6,144 entries) and in packs, six above; they cost time in every replay (no step of a replay
     stops the iteration it replays), and a solve afterwards is the same."""
     f = lambda ph: [p for p in ph if p["name"] == "pcg_vectors"]  # noqa: E731
-    for make, small in SIZES.values():
-        m = make()
+    for m, small in ((small2d(57, seed=1), True), (small2d(58, seed=1), False), (small3d(11, seed=2), True),
+                     (small3d(13, seed=2), False)):
         with V.Solver.from_mesh(m, autotune=0) as s:
+            assert (s.hierarchy_info()[1] // m.dim * (2 if m.dim == 2 else 4) <= 6144) == small
             x, _ = s.solve(m.rhs[0], 1e-6)
             vec = f(s.profile_iteration(2))
             assert len(vec) == 1 and vec[0]["launches"] == 2 * (2 if small else 6) and vec[0]["ms"] > 0
